@@ -105,10 +105,6 @@ sptrsv_schedule_t effective_sched(const Plan &P, int32_t nrhs) {
   return it != P.tuned.end() ? it->second : P.sched;
 }
 
-static int64_t win_bytes(int64_t rows, int64_t ents, int64_t nl, int32_t nrhs) {
-  return thin_window_bytes(rows, ents, nl, nrhs);
-}
-
 // Wide levels whose rows have at least kLongRow off-diagonals on average are
 // solved with a workgroup per row when there are 2 to 256 right-hand sides:
 // a (row, column) item alone would sum them one after another.
@@ -130,44 +126,71 @@ int32_t thin_width(const sptrsv_schedule_t &sc, int32_t nrhs) {
 // so it needs no overflow records.
 bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs) {
   const int64_t rows = P.h_level_ptr[l + 1] - P.h_level_ptr[l];
-  return win_bytes(rows, 0, 1, nrhs) <= thin_win_bytes();
+  return thin_window_bytes(rows, 0, 1, nrhs, kWidths) <= thin_win_bytes();
 }
 
-// Upper bound on the overflow records of level l's rows in a window that
-// starts at level ws: dependencies (beyond each row's two at the highest
-// levels) at most l - ws levels up, counted by whole distance buckets.
-static int64_t extras_in(const Plan &P, int32_t l, int32_t ws) {
+// Upper bound on the overflow records of level l's rows in a window of width
+// class kc that starts at level ws: dependencies (beyond each row's K at the
+// highest levels) at most l - ws levels up, counted by whole distance buckets.
+static int64_t extras_in(const Plan &P, int kc, int32_t l, int32_t ws) {
   const int32_t d = l - ws;
-  const int32_t *hx = P.h_xh.data() + (size_t)l * kExtraBuckets;
+  const int32_t *hx = P.h_xh[kc].data() + (size_t)l * kExtraBuckets;
   int64_t e = 0;
   for (int b = 0; b < kExtraBuckets && kExtraLo[b] <= d; ++b) e += hx[b];
   return e;
 }
 
 // Cut levels [l0, l1) into LDS windows; flag windows whose levels fit one wave
-// (bit 0) or one item per thread of a workgroup of wg threads (bit 1), and
-// give each window its bound on overflow records. Appends the windows and a
-// terminator holding l1; returns the number of windows.
+// (bit 0) or one item per thread of a workgroup of wg threads (bit 1), with
+// their width class in bits 2-3, and give each window its bound on overflow
+// records. Appends the windows and a terminator holding l1; returns the number
+// of windows.
+// The width class of a window is the one with the least estimated time per
+// level: a window costs about 1 us beside its levels (so narrow records, which
+// hold more levels, win where rows have few dependencies inside), a level
+// about 60 ns on one wave and 160 on several, 5 more per inline dependency,
+// and each round of four overflow records beyond the inline ones two dependent
+// LDS round trips, about 90 ns.
 int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, std::vector<int4> &out) {
   const int64_t cap = thin_win_bytes();
   const size_t first = out.size();
   int32_t ws = l0;
-  int64_t rows = 0, ents = 0, maxit = 0;
-  auto flags = [&]() { return (maxit <= 64 ? 1 : 0) | (maxit <= wg ? 2 : 0); };
-  for (int32_t l = l0; l < l1; ++l) {
-    const int64_t rl = P.h_level_ptr[l + 1] - P.h_level_ptr[l];
-    int64_t el = extras_in(P, l, ws);
-    if (l > ws && win_bytes(rows + rl, ents + el, l - ws + 1, nrhs) > cap) {
-      out.push_back(int4{ws, flags(), (int32_t)ents, 0});
-      ws = l;
-      rows = ents = maxit = 0;
-      el = 0;
+  while (ws < l1) {
+    int32_t end = ws, kc = kWidths;
+    int64_t ents = 0, maxit = 0;
+    double best = 0.0;
+    for (int k = 0; k < kWidths; ++k) {
+      int64_t rows = 0, en = 0, mi = 0;
+      double ns = 1000.0;
+      int32_t l = ws;
+      for (; l < l1; ++l) {
+        const int64_t rl = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
+        const int64_t el = extras_in(P, k, l, ws);
+        if (thin_window_bytes(rows + rl, en + el, l - ws + 1, nrhs, k) > cap) break;
+        rows += rl;
+        en += el;
+        mi = std::max<int64_t>(mi, rl * nrhs);
+        const int64_t per = (rl * nrhs + wg - 1) / wg;
+        ns += (rl * nrhs <= 64 ? 60.0 : 160.0 * (double)per) + 5.0 * width_of(k) +
+              90.0 * (double)((el + 4 * rl - 1) / (4 * rl));
+      }
+      if (l > ws && (end == ws || ns / (l - ws) < best)) {
+        best = ns / (l - ws);
+        end = l;
+        kc = k;
+        ents = en;
+        maxit = mi;
+      }
     }
-    rows += rl;
-    ents += el;
-    maxit = std::max<int64_t>(maxit, rl * nrhs);
+    if (end <= ws + 1) {  // a level alone: no dependency inside the window
+      end = ws + 1;
+      kc = kWidths;
+      ents = 0;
+      maxit = (int64_t)(P.h_level_ptr[(size_t)end] - P.h_level_ptr[(size_t)ws]) * nrhs;
+    }
+    out.push_back(int4{ws, (maxit <= 64 ? 1 : 0) | (maxit <= wg ? 2 : 0) | (kc << 2), (int32_t)ents, 0});
+    ws = end;
   }
-  out.push_back(int4{ws, flags(), (int32_t)ents, 0});
   const int32_t nw = (int32_t)(out.size() - first);
   out.push_back(int4{l1, -1, 0, 0});
   return nw;
@@ -176,7 +199,7 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
 // Static images of every window in P.h_win (entries with y >= 0; the others
 // end a run): exact overflow counts replace the host bounds in .z, image
 // offsets (16-byte units) go to .w, and the table is uploaded.
-sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, hipStream_t s) {
+sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s) {
   const int32_t nent = (int32_t)P.h_win.size();
   if (nent == 0 || P.n == 0) return SPTRSV_OK;
   std::vector<int32_t> lvl_win((size_t)P.nlev, -1);
@@ -223,14 +246,14 @@ sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, hipStream_t s) {
     const int64_t R = P.h_level_ptr[(size_t)P.h_win[(size_t)e + 1].x] - P.h_level_ptr[(size_t)W.x];
     W.z = (int32_t)no;
     W.w = (int32_t)units;
-    units += window_image_units(R, no);
+    units += window_image_units(R, no, (W.y >> 2) & 3);
     if (units >= ((int64_t)1 << 31)) return set_err(h, SPTRSV_ERR_OVERFLOW, "window images exceed int32 indexing");
   }
   HIPCHK(h, P.img.reserve((size_t)units));
   HIPCHK(h, P.ext.reserve((size_t)next));
   HIPCHK(h, hipMemcpyAsync(P.win.p, P.h_win.data(), sizeof(int4) * (size_t)nent, hipMemcpyHostToDevice, s));
   HIPCHK(h, launch_img_fill(n, P.level_ptr.p, P.nlev, d_lw.p, P.win.p, P.srp.p, P.sci.p, P.sva.p, P.sdg.p, oex.p,
-                            P.ext_ptr.p, P.img.p, P.ext.p, io_perm(P), s));
+                            P.ext_ptr.p, P.img.p, P.ext.p, io_perm(P), ncol, s));
   HIPCHK(h, hipStreamSynchronize(s));
   return SPTRSV_OK;
 }
@@ -393,7 +416,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   for (int32_t l = 0; l < P.nlev; ++l) {
     const int64_t rows = rows_of(l);
     bool thin = sc.mode == 2 || ((sc.mode == 0 || flow) && rows <= thr);
-    if (win_bytes(rows, 0, 1, gw) > cap) thin = false;  // must fit one window alone
+    if (thin_window_bytes(rows, 0, 1, gw, kWidths) > cap) thin = false;  // must fit one window alone
     // a wide level whose rows average many dependencies, with several
     // right-hand sides, is a launch of its own with a workgroup per row
     const bool longr = !thin && long_rows(P, l, nrhs);
@@ -433,7 +456,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
     r.nw = cut_windows(P, r.l0, r.l1, gw, sc.wg_threads, P.h_win);
   }
   P.runs_nrhs = -1;  // until the images are built
-  STCHK(build_images(h, P, s));
+  STCHK(build_images(h, P, gw, s));
   if (flow) STCHK(build_flow(h, P, nrhs, sc, s));
   STCHK(build_overlap(h, P, nrhs, sc, s));
   P.runs_nrhs = nrhs;
@@ -623,20 +646,22 @@ static void prof_end(sptrsv_ctx *h, int slot, hipStream_t s) {
 
 ThinArgs thin_args(const Plan &P) { return thin_args(P, P.bp.p, P.xp.p); }
 ThinArgs thin_args(const Plan &P, double *bp, double *xp) {
-  return ThinArgs{P.level_ptr.p, P.sdg.p, P.img.p, P.ext_ptr.p, P.ext.p, bp, xp, P.tp.p};
+  return ThinArgs{P.level_ptr.p, P.img.p, P.ext_ptr.p, P.ext.p, bp, xp, P.tp.p};
 }
 
-// The level-distance histogram of the dependencies that need overflow records
-// (host copy, for cutting LDS windows).
+// The level-distance histograms of the dependencies that need overflow records
+// (host copies, for cutting LDS windows).
 sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s) {
-  P.h_xh.assign((size_t)P.nlev * kExtraBuckets, 0);
+  const size_t len = (size_t)P.nlev * kExtraBuckets;
+  for (auto &v : P.h_xh) v.assign(len, 0);
   if (P.n == 0 || P.nlev == 0) return SPTRSV_OK;
   DArr<int32_t> lop, hist;
   HIPCHK(h, lop.alloc(P.n));
-  HIPCHK(h, hist.alloc(P.h_xh.size()));
-  HIPCHK(h, hipMemsetAsync(hist.p, 0, sizeof(int32_t) * P.h_xh.size(), s));
+  HIPCHK(h, hist.alloc(kWidths * len));
+  HIPCHK(h, hipMemsetAsync(hist.p, 0, sizeof(int32_t) * kWidths * len, s));
   HIPCHK(h, launch_extra_hist(P.n, P.level_ptr.p, P.nlev, P.srp.p, P.sci.p, lop.p, hist.p, s));
-  HIPCHK(h, hipMemcpyAsync(P.h_xh.data(), hist.p, sizeof(int32_t) * P.h_xh.size(), hipMemcpyDeviceToHost, s));
+  for (int k = 0; k < kWidths; ++k)
+    HIPCHK(h, hipMemcpyAsync(P.h_xh[k].data(), hist.p + (size_t)k * len, sizeof(int32_t) * len, hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));
   return SPTRSV_OK;
 }

@@ -110,7 +110,7 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
   HIPCHK(h, h->b_order.reserve(std::max<size_t>(q.size(), 1)));
   if (!q.empty()) HIPCHK(h, hipMemcpy(h->b_order.p, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice));
   h->b_win_nrhs = -1;  // until the images are built
-  STCHK(build_images(h, P, s));
+  STCHK(build_images(h, P, nrhs, s));
   HIPCHK(h, h->b_mwin.alloc((size_t)h->b_nmat + 1));
   HIPCHK(h, hipMemcpy(h->b_mwin.p, h->b_h_mwin.data(), sizeof(int32_t) * ((size_t)h->b_nmat + 1),
                       hipMemcpyHostToDevice));

@@ -146,7 +146,7 @@ sptrsv_status_t put_plan(sptrsv_ctx *h, Writer &w, uint32_t base, const Plan &P)
   STCHK(put(h, w, base + 11, P.lv_cost, nl));
   STCHK(put(h, w, base + 12, P.ell_c, n));
   STCHK(put(h, w, base + 13, P.ell_v, 2 * n));
-  w.vec(base + 14, P.h_xh);
+  w.vec(base + 14, P.h_xh[0]);  // the wider classes' histograms are rebuilt on load
   w.vec(base + 15, P.h_level_ptr);
   w.vec(base + 16, P.h_lv_nnz);
   std::vector<TunedEntry> tuned;
@@ -192,8 +192,8 @@ sptrsv_status_t get_plan(sptrsv_ctx *h, Reader &r, uint32_t base, Plan &P) {
   STCHK(get(h, r, base + 12, P.ell_c, n));
   STCHK(get(h, r, base + 13, P.ell_v, 2 * n));
   std::vector<TunedEntry> tuned;
-  if (!r.vec(base + 14, &P.h_xh) || !r.vec(base + 15, &P.h_level_ptr) || !r.vec(base + 16, &P.h_lv_nnz) ||
-      !r.vec(base + 17, &tuned) || P.h_xh.size() != nl * kExtraBuckets || P.h_level_ptr.size() != nl + 1 ||
+  if (!r.vec(base + 14, &P.h_xh[0]) || !r.vec(base + 15, &P.h_level_ptr) || !r.vec(base + 16, &P.h_lv_nnz) ||
+      !r.vec(base + 17, &tuned) || P.h_xh[0].size() != nl * kExtraBuckets || P.h_level_ptr.size() != nl + 1 ||
       P.h_lv_nnz.size() != nl)
     return set_err(h, SPTRSV_ERR_ARG, "plan file: host tables of plan %u", base);
   for (size_t l = 0; l < nl; ++l)
@@ -221,6 +221,7 @@ sptrsv_status_t get_plan(sptrsv_ctx *h, Reader &r, uint32_t base, Plan &P) {
   HIPCHK(h, P.tp.alloc(4));
   HIPCHK(h, hipMemset(P.tp.p, 0, 4 * sizeof(unsigned)));
   HIPCHK(h, P.sf_ticket.alloc(1));
+  STCHK(build_extra_hist(h, P, nullptr));
   P.ready = true;
   return SPTRSV_OK;
 }

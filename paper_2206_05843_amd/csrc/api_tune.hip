@@ -27,7 +27,7 @@ std::vector<sptrsv_schedule_t> candidates(int32_t nrhs) {
     if (nrhs > 1 && lpr > 1) continue;
     c.push_back(sptrsv_schedule_t{1, 0, 512, 256, lpr, 0, 0, 0});
     for (int thr : thin_list) {
-      if (thin_window_bytes(thr, 0, 1, gw) > thin_win_bytes()) continue;
+      if (thin_window_bytes(thr, 0, 1, gw, kWidths) > thin_win_bytes()) continue;
       for (int wg : wg_list) c.push_back(sptrsv_schedule_t{0, thr, wg, 256, lpr, 0, 0, tc});
     }
   }
@@ -36,7 +36,7 @@ std::vector<sptrsv_schedule_t> candidates(int32_t nrhs) {
   // dataflow runs of the wide levels (chunk sizes from the workgroup size), thin runs below
   for (int wt : {128, 256, 512})
     for (int thr : {0, 64, 1024}) {
-      if (thin_window_bytes(thr, 0, 1, gw) > thin_win_bytes()) continue;
+      if (thin_window_bytes(thr, 0, 1, gw, kWidths) > thin_win_bytes()) continue;
       c.push_back(sptrsv_schedule_t{4, thr, 1024, wt, 1, 0, 0, thr > 0 ? tc : 0});
     }
   // consecutive wide levels in one persistent launch (one lane per item; 4096
@@ -45,7 +45,7 @@ std::vector<sptrsv_schedule_t> candidates(int32_t nrhs) {
   for (int g : grids) {
     c.push_back(sptrsv_schedule_t{1, 0, 512, 256, 1, g});
     for (int thr : thin_list) {
-      if (thin_window_bytes(thr, 0, 1, gw) > thin_win_bytes()) continue;
+      if (thin_window_bytes(thr, 0, 1, gw, kWidths) > thin_win_bytes()) continue;
       c.push_back(sptrsv_schedule_t{0, thr, 1024, 256, 1, g, 0, tc});
     }
   }

@@ -61,20 +61,26 @@ struct DArr {
   }
 };
 
-// One in-window dependency beyond a row's two inline ones: weight scaled by
-// 1/diagonal and the slot (row of the window) it reads.
+// One in-window dependency beyond a row's inline ones: its weight and the slot
+// it reads (row of the window times the window's columns, in doubles).
 struct __align__(16) Dep {
   double w;
   int32_t slot, pad;
 };
 
-// One dependency on a row before the row's LDS window: the unscaled weight,
-// the position whose final x it reads, and that position's row in the
-// caller's numbering (where a solve by rows reads it).
+// One dependency on a row before the row's LDS window: its weight, the
+// position whose final x it reads, and that position's row in the caller's
+// numbering (where a solve by rows reads it).
 struct __align__(16) ExtDep {
   double w;
   int32_t col, row;
 };
+
+// Inline dependencies per row of an LDS window, by the window's width class
+// (bits 2-3 of its flags). Class 3: a window of one level, whose rows have no
+// dependency inside it and take no records at all.
+constexpr int kWidths = 3;
+__host__ __device__ constexpr int32_t width_of(int kc) { return kc == 0 ? 2 : kc == 1 ? 6 : kc == 2 ? 10 : 0; }
 
 // One run of the solve schedule: a range of levels done inside one workgroup
 // (thin) or a single level spread over the device (wide).
@@ -140,8 +146,10 @@ struct Plan {
   std::vector<int64_t> h_lv_tnnz;      // per level: off-diagonal nnz of T
   DArr<int4> ell_c;                    // [n] first four off-diagonal columns per position (-1: none)
   DArr<double2> ell_v;                 // [2n] their values
-  std::vector<int32_t> h_xh;           // [nlev * kExtraBuckets] level-distance histogram of dependencies
-                                       // that need overflow records when inside an LDS window
+  // [nlev * kExtraBuckets] per width class of an LDS window's inline records
+  // (2, 6, 10): level-distance histogram of the dependencies that need
+  // overflow records when inside a window
+  std::vector<int32_t> h_xh[kWidths];
   int64_t total_cost = 0;
   double avg_cost = 0.0;
   sptrsv_schedule_t sched{};           // knobs in force (mode 0 = automatic)
@@ -315,26 +323,30 @@ hipError_t launch_fill_t(int32_t n, const int32_t *perm, const int32_t *trp, con
 hipError_t launch_level_stats(int32_t nlev, const int32_t *level_ptr, const int32_t *srp, int64_t *rows,
                               int64_t *nnz, int64_t *cost, long long *total, hipStream_t s);
 
-// LDS bytes of a thin-run window of `rows` rows, `ovf` overflow dependency
-// records and `nl` levels: per row the partial sum or x of every RHS (8 nrhs),
-// two inline weights (16) and packed slots/count/offset (8); one zero entry
-// per RHS that absent dependencies point to; 16 per overflow record; the level
-// bounds; 16 for aligning the window's sections.
-__host__ __device__ inline int64_t thin_window_bytes(int64_t rows, int64_t ovf, int64_t nl, int32_t nrhs) {
-  return rows * (8 * (int64_t)nrhs + 24) + 8 * (int64_t)nrhs + ovf * 16 + 4 * (nl + 1) + 16;
+// Bytes of a row's record in a window of width class kc: the K inline weights
+// (8 each), the diagonal with its reciprocal (16), then 16-bit fields: the K
+// slots, the in-window dependency count and the first overflow record. The middle
+// one is padded by 8 bytes, so that the rows of a level, read by
+// consecutive lanes, start in different LDS banks.
+__host__ __device__ constexpr int32_t row_record_bytes(int kc) {
+  return kc == 0 ? 40 : kc == 1 ? 88 : kc == 2 ? 120 : 16;
 }
-
-// Inline record of a row: slots, in-window dependency count and first
-// overflow record, 16 bits each (a window holds far fewer than 65536 rows or
-// records).
-__host__ __device__ inline uint2 pack_rix(int32_t s0, int32_t s1, int32_t cnt, int32_t ob) {
-  return make_uint2((uint32_t)s0 | ((uint32_t)s1 << 16), (uint32_t)cnt | ((uint32_t)ob << 16));
+// Bytes of the x part of a window in LDS (one zero entry per column behind the
+// rows, which absent dependencies read), rounded to 16.
+__host__ __device__ inline int64_t window_x_bytes(int64_t rows, int32_t ncol) {
+  return (8 * (rows + 1) * ncol + 15) & ~(int64_t)15;
 }
-
-// 16-byte units of a window's static image: weights (one unit per row),
-// overflow records (one each), packed records (two rows per unit).
-__host__ __device__ inline int64_t window_image_units(int64_t rows, int64_t ovf) {
-  return rows + ovf + ((rows + 1) >> 1);
+// 16-byte units of a window's static image: the row records, then the overflow
+// records (one unit each).
+__host__ __device__ inline int64_t window_record_units(int64_t rows, int kc) {
+  return (rows * row_record_bytes(kc) + 15) >> 4;
+}
+__host__ __device__ inline int64_t window_image_units(int64_t rows, int64_t ovf, int kc) {
+  return window_record_units(rows, kc) + ovf;
+}
+// LDS bytes of a window: x (partial sums first), the image, the level bounds.
+__host__ __device__ inline int64_t thin_window_bytes(int64_t rows, int64_t ovf, int64_t nl, int32_t ncol, int kc) {
+  return window_x_bytes(rows, ncol) + 16 * window_image_units(rows, ovf, kc) + 4 * (nl + 2);
 }
 
 // Level-distance buckets of the overflow-record histogram: lower bounds of
@@ -350,9 +362,6 @@ inline int grid_for(int64_t items, int threads, int cap = 1 << 20) {
   return (int)g;
 }
 
-// Device arrays a thin run reads: level bounds, diagonal, the static window
-// images and each position's dependencies before its window (CSR), and the
-// work vectors.
 // Right-hand sides stored by rows (b null: the work vectors only): b is read
 // at b[perm[pos] * nrhs + c] except where tflag[pos] marks a row of T with
 // off-diagonals (b' already in the work vector), and x is written to
@@ -368,9 +377,10 @@ struct RowsIO {
   const int32_t *sci_r;  // the level-ordered copy's columns as caller rows
 };
 
+// Device arrays a thin run reads: level bounds, the static window images and
+// each position's dependencies before its window (CSR), and the work vectors.
 struct ThinArgs {
   const int32_t *level_ptr;
-  const double *sdg;
   const uint4 *img;
   const int32_t *ext_ptr;
   const ExtDep *ext;
@@ -415,6 +425,7 @@ hipError_t launch_max_abs_diff(int32_t n, const double *x0, const double *x1, un
 // First and last position of the rows of every caller-row tile of 64 rows.
 hipError_t launch_tile_span(int32_t n, const int32_t *iperm, int32_t *first, int32_t *last, hipStream_t s);
 int thin_win_bytes();
+// hist: kWidths arrays of nlev * kExtraBuckets, back to back, zeroed by the caller
 hipError_t launch_extra_hist(int32_t n, const int32_t *level_ptr, int32_t nlev, const int32_t *srp,
                              const int32_t *sci, int32_t *lop, int32_t *hist, hipStream_t s);
 // ng: right-hand sides per solver workgroup (a divisor of nrhs; 0 = all)
@@ -513,7 +524,7 @@ hipError_t launch_win_prefix(int32_t nent, const int4 *win, const int32_t *level
 hipError_t launch_img_fill(int32_t n, const int32_t *level_ptr, int32_t nlev, const int32_t *lvl_win, const int4 *win,
                            const int32_t *srp, const int32_t *sci, const double *sva, const double *sdg,
                            const long long *ovf_ex, const int32_t *ext_ptr, uint4 *img, ExtDep *ext,
-                           const int32_t *perm, hipStream_t s);
+                           const int32_t *perm, int32_t ncol, hipStream_t s);
 // Batched launchers (k_solve.hip) -------------------------------------------------
 hipError_t launch_batch_run(int wg, int32_t nmat, int32_t grid, const int32_t *order, const int32_t *mwin,
                             const int4 *win, int32_t nrhs, const ThinArgs &a, unsigned *q, int *err, hipStream_t s);
@@ -531,7 +542,8 @@ bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs);
 int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, std::vector<int4> &out);
 sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s);
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s);
-sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, hipStream_t s);
+// ncol: right-hand sides per window (slots are premultiplied by it)
+sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s);
 sptrsv_status_t ensure_work(sptrsv_ctx *h, Plan &P, int32_t nrhs);
 
 // Plan building (api.hip) --------------------------------------------------------

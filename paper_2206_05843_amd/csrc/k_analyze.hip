@@ -364,19 +364,47 @@ __global__ void k_ptr_from_scan(const long long *__restrict__ ex, const long lon
 
 // Level-ordered copy: the row at position p keeps its column order; columns
 // become positions so the solve reads its work vectors contiguously per level.
+// The level-ordered copy of row perm[p] at position p, its off-diagonals in
+// ascending position: dependencies at low levels come first, so an executor
+// that subtracts them in this order has summed everything else when the last
+// one it waits for (the row of the level before) arrives, and a window's
+// dependencies on earlier windows precede those inside it. Every executor sums
+// in this order, so the schedule does not change a solution's bits.
+// kFillLanes lanes share a row: each ranks its entries against the row's
+// others, kFillLanes at a time through shuffles. Rows longer than kSortMax
+// (the ranking is quadratic) keep the caller's column order.
+constexpr int kFillLanes = 8;
+constexpr int32_t kSortMax = 512;
+
 __global__ void k_fill_solve(int32_t n, const int32_t *__restrict__ perm, const int32_t *__restrict__ iperm,
                              const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                              const double *__restrict__ va, const int32_t *__restrict__ srp, int32_t *sci,
                              double *sva, double *sdg) {
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
+  const int sub = threadIdx.x % kFillLanes;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x / kFillLanes;
+  for (int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kFillLanes; p < n; p += stride) {
     const int32_t r = perm[p];
     const int32_t b = rp[r], e = rp[r + 1] - 1;
-    int32_t o = srp[p];
-    for (int32_t q = b; q < e; ++q, ++o) {
-      sci[o] = iperm[ci[q]];
-      sva[o] = va[q];
+    const int32_t o = srp[p];
+    const bool sort = e - b <= kSortMax;
+    for (int32_t q0 = b; q0 < e; q0 += kFillLanes) {
+      const int32_t q = q0 + sub;
+      const int32_t pos = q < e ? iperm[ci[q]] : INT32_MAX;
+      int32_t at = q - b;
+      if (sort) {
+        at = 0;
+        for (int32_t w0 = b; w0 < e; w0 += kFillLanes) {
+          const int32_t other = w0 == q0 ? pos : w0 + sub < e ? iperm[ci[w0 + sub]] : INT32_MAX;
+#pragma unroll
+          for (int j = 0; j < kFillLanes; ++j) at += __shfl(other, j, kFillLanes) < pos ? 1 : 0;
+        }
+      }
+      if (q < e) {
+        sci[o + at] = pos;
+        sva[o + at] = va[q];
+      }
     }
-    sdg[p] = va[e];
+    if (sub == 0) sdg[p] = va[e];
   }
 }
 
@@ -558,8 +586,8 @@ hipError_t launch_ptr_from_scan(const long long *ex, const long long *cnt, int32
 hipError_t launch_fill_solve(int32_t n, const int32_t *perm, const int32_t *iperm, const int32_t *rp,
                              const int32_t *ci, const double *va, const int32_t *srp, int32_t *sci, double *sva,
                              double *sdg, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_solve, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n, perm, iperm, rp, ci, va,
-                     srp, sci, sva, sdg);
+  hipLaunchKernelGGL(k_fill_solve, dim3(grid_for((int64_t)n * kFillLanes, kBlock, 1 << 16)), dim3(kBlock), 0, s, n, perm,
+                     iperm, rp, ci, va, srp, sci, sva, sdg);
   return hipGetLastError();
 }
 
@@ -591,40 +619,31 @@ __global__ void k_level_of_pos(int32_t n, const int32_t *__restrict__ level_ptr,
   }
 }
 
-// Per level, a histogram of the level distance l - level(k) over each row's
-// dependencies k except the two at the highest levels (a row keeps two
-// in-window dependencies inline; the others need overflow records). Distance
-// buckets: 1, 2, 3, 4, 5-8, 9-16, 17-32, 33-64, 65-256, >256.
-__global__ void k_extra_hist(int32_t n, const int32_t *__restrict__ srp, const int32_t *__restrict__ sci,
-                             const int32_t *__restrict__ lop, int32_t *hist) {
+// Per level and width class (2, 6, 10 inline dependencies per row of an LDS
+// window), a histogram of the level distance l - level(k) over each row's
+// dependencies k except those at the K highest levels (a row keeps K in-window
+// dependencies inline; the others need overflow records). Rows are in
+// ascending position, so the K last entries are at the highest levels; a row
+// that is not (kept in column order for its length, or read from a plan file
+// of an earlier version) counts all its entries, still an upper bound.
+// Distance buckets: 1, 2, 3, 4, 5-8, 9-16, 17-32, 33-64, 65-256, >256.
+__global__ void k_extra_hist(int32_t n, int32_t nlev, const int32_t *__restrict__ srp,
+                             const int32_t *__restrict__ sci, const int32_t *__restrict__ lop, int32_t *hist) {
+  const int64_t cls = (int64_t)nlev * kExtraBuckets;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
     const int32_t qb = srp[p], qe = srp[p + 1];
-    if (qe - qb <= 2) continue;
+    if (qe - qb <= width_of(0)) continue;
     const int32_t l = lop[p];
-    int32_t m1 = -1, m2 = -1;  // the two highest dependency levels (with multiplicity)
-    for (int32_t q = qb; q < qe; ++q) {
-      const int32_t a = lop[sci[q]];
-      if (a > m1) {
-        m2 = m1;
-        m1 = a;
-      } else if (a > m2) {
-        m2 = a;
-      }
-    }
-    bool skip1 = false, skip2 = false;
-    for (int32_t q = qb; q < qe; ++q) {
-      const int32_t a = lop[sci[q]];
-      if (!skip1 && a == m1) {
-        skip1 = true;
-        continue;
-      }
-      if (!skip2 && a == m2) {
-        skip2 = true;
-        continue;
-      }
-      const int32_t d = l - a;
+    bool sorted = true;
+    for (int32_t q = qb + 1; q < qe; ++q) sorted = sorted && sci[q - 1] < sci[q];
+    const int32_t last = sorted ? qe - width_of(0) : qe;
+    for (int32_t q = qb; q < last; ++q) {
+      const int32_t d = l - lop[sci[q]];
       const int32_t b = d <= 4 ? d - 1 : d <= 8 ? 4 : d <= 16 ? 5 : d <= 32 ? 6 : d <= 64 ? 7 : d <= 256 ? 8 : 9;
-      atomicAdd(hist + (int64_t)l * kExtraBuckets + b, 1);
+      int32_t *at = hist + (int64_t)l * kExtraBuckets + b;
+      atomicAdd(at, 1);
+      if (!sorted || q < qe - width_of(1)) atomicAdd(at + cls, 1);
+      if (!sorted || q < qe - width_of(2)) atomicAdd(at + 2 * cls, 1);
     }
   }
 }
@@ -634,6 +653,6 @@ hipError_t launch_extra_hist(int32_t n, const int32_t *level_ptr, int32_t nlev, 
                              const int32_t *sci, int32_t *lop, int32_t *hist, hipStream_t s) {
   if (n == 0 || nlev == 0) return hipSuccess;
   hipLaunchKernelGGL(k_level_of_pos, dim3(grid_for(n, kBlock, 4096)), dim3(kBlock), 0, s, n, level_ptr, nlev, lop);
-  hipLaunchKernelGGL(k_extra_hist, dim3(grid_for(n, kBlock, 4096)), dim3(kBlock), 0, s, n, srp, sci, lop, hist);
+  hipLaunchKernelGGL(k_extra_hist, dim3(grid_for(n, kBlock, 4096)), dim3(kBlock), 0, s, n, nlev, srp, sci, lop, hist);
   return hipGetLastError();
 }

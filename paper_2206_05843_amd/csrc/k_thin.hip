@@ -34,87 +34,206 @@ struct Ctl {
 // A thin run is cut into LDS windows (consecutive levels, chosen on the host so
 // that the window's rows and dependency records fit in LDS). Per window:
 //  phase 1 (all rows in parallel): the window's static image, built once per
-//    schedule, is streamed into LDS: per row an inline record {w0, w1 | slot0,
-//    slot1, count, first overflow} of its first two in-window dependencies
-//    (weights scaled by 1/L(pos,pos); absent ones point to a zero entry with
-//    weight 0, so phase 2 needs no predication) and a list of {weight, slot}
-//    records for its third and later ones. Meanwhile each thread loads, for
-//    several rows at once, b', the diagonal and the row's range of
-//    dependencies on earlier windows, then forms
-//    v = (b' - sum of L(pos,k) x(k)) / L(pos,pos) over those (final values,
-//    read from global memory, in the row's column order);
-//  phase 2 (level by level): x = v - sum over in-window dependencies of w x,
-//    in LDS only;
+//    schedule, is streamed into LDS: per row its first K in-window
+//    dependencies (weights and slots; absent ones point to a zero entry with
+//    weight 0, so phase 2 needs no predication), its diagonal with the
+//    reciprocal, and a list of {weight, slot} records for the dependencies
+//    beyond K. Meanwhile each thread loads, for several rows at once, b' and
+//    the row's range of dependencies on earlier windows, then forms
+//    v = b' - sum of L(pos,k) x(k) over those (final values, read from global
+//    memory, in the row's order);
+//  phase 2 (level by level): x = (v - sum over in-window dependencies) / d, in
+//    LDS only;
 //  then the window's x goes to global memory in one coalesced pass (where the
 //    finiteness check happens too), before the next window reads it.
-// When every level of the window has at most one item per thread, phase 2 is
-// software-pipelined: the next level's records are requested before the
-// current level is computed, and the level bounds are read from registers,
-// so a level waits only for the x values it reads. Windows whose levels have
-// at most 64 items run phase 2 on one wave without workgroup barriers.
+// Rows are in ascending position, so the earlier windows' dependencies come
+// first whatever the cut, and the sums and quotients are those of the other
+// executors bit for bit.
+// A level of phase 2 waits for the x of the level before, and a single wave
+// issues an instruction every four or five cycles, so what a level costs is one
+// LDS round trip and its instructions. All of a row's x (K inline dependencies)
+// are requested at once and the next level's records behind them; a record has
+// one address; lanes past the level's end repeat its last row instead of being
+// masked; waves without a row of the level go straight to the barrier. K is the
+// window's width class: 2, 6 or 10 (cut_windows has the rule).
+// Levels' records are requested one level ahead and the level bounds read from
+// registers when every level of the window has at most one item per thread.
+// Windows whose levels have at most 64 items run phase 2 on one wave without
+// workgroup barriers.
+// Measured (one right-hand side): a 2,000-row window matrix, 277 levels of five
+// dependencies a row, 49 us a solve against 95 with two inline dependencies,
+// the others in records read two dependent round trips per four, and sections
+// with addresses of their own (about 110 and 280 ns a level); the 2D stencil's
+// 4,602 levels 888 us against 1,130, its rewritten form 2.69 ms against 2.95.
 // win[i] = {first level, flags}; the run's last entry holds the end level.
 // kTimed (used only to label levels for the learned policy): thread 0 stamps the
 // device wall clock around every level and writes per-level times (ns).
 constexpr int kBatch = 4;
 
-// acc - sum_j w_j x(slot_j, c) over n overflow records starting at d, in order,
-// in batches of 4 (tail clamped to a valid record).
-template <bool kOne>
-__device__ __forceinline__ double ovf_sum(double acc, const Dep *__restrict__ d, int32_t n, const double *v,
-                                          int32_t nr, int32_t c) {
+// LDS by byte address: these kernels have no static LDS, so their dynamic LDS
+// starts at address 0 and an item's address needs no base added to it.
+typedef __attribute__((address_space(3))) double lds_f64;
+typedef __attribute__((address_space(3))) const uint32_t lds_u32;
+__device__ __forceinline__ lds_f64 *lds_d(uint32_t byte) { return (lds_f64 *)(uintptr_t)byte; }
+__device__ __forceinline__ uint32_t lds_u(uint32_t byte) { return *(lds_u32 *)(uintptr_t)byte; }
+
+// A window in LDS (byte addresses). v, the partial sums and then x, comes
+// first, at kCtlBytes: [(R + 1) * gw] doubles, row R zero; then the row
+// records, the overflow records and the level bounds.
+struct Win {
+  uint32_t rec, ovf;
+  const int32_t *lv;   // [NL + 2] level bounds from the window's first position (the last one twice)
+  int32_t NL, gw;
+};
+
+// acc - sum_j w_j x over n overflow records from record ob on, in order, in
+// batches of 4 (tail clamped to a valid record); c8: the column's byte offset.
+__device__ __forceinline__ double ovf_sum(const Win &W, double acc, int32_t ob, int32_t n, uint32_t c8) {
+  const uint32_t d = W.ovf + 16u * (uint32_t)ob;
   for (int32_t i0 = 0; i0 < n; i0 += kBatch) {
     const int32_t cnt = n - i0;
-    double w[kBatch];
-    int32_t e[kBatch];
+    double w[kBatch], xv[kBatch];
+    uint32_t e[kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
-      const Dep dj = d[i0 + (j < cnt ? j : 0)];
-      w[j] = dj.w;
-      e[j] = dj.slot;
+      const uint32_t at = d + 16u * (uint32_t)(i0 + (j < cnt ? j : 0));
+      w[j] = *lds_d(at);
+      e[j] = lds_u(at + 8);
     }
-    double xv[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) xv[j] = v[(int64_t)e[j] * (kOne ? 1 : nr) + c];
+    for (int j = 0; j < kBatch; ++j) xv[j] = *lds_d(8u * e[j] + c8 + kCtlBytes);
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) acc = j < cnt ? acc - w[j] * xv[j] : acc;
+    for (int j = 0; j < kBatch; ++j) acc = j < cnt ? fma(-w[j], xv[j], acc) : acc;
   }
   return acc;
 }
 
-// The static inputs of one (row, rhs) item in phase 2.
+// The static inputs of one (row, rhs) item in phase 2: its record, its partial
+// sum and where its x goes (the packed fields are unpacked where they are used).
+template <int K>
 struct Item {
-  double acc, w0, w1;
-  uint2 r;  // packed slots/count/offset, unpacked where used (a prefetch never waits for it)
-  int32_t s, c, act;
+  double acc, d, r;
+  double w[K > 0 ? K : 1];
+  uint32_t ix[K > 0 ? K / 2 + 1 : 1];
+  uint32_t at;
 };
 
-template <bool kOne>
-__device__ __forceinline__ Item load_item(int32_t pb, int32_t items, int32_t t, int32_t nr, const double *v,
-                                          const double2 *rw, const uint2 *rix) {
-  Item it;
-  it.act = t < items;
-  it.s = kOne ? pb + t : pb + t / nr;
-  it.c = kOne ? 0 : t - (it.s - pb) * nr;
-  const int32_t ss = it.act ? it.s : pb;
-  const double2 w = rw[ss];
-  it.w0 = w.x;
-  it.w1 = w.y;
-  it.r = rix[ss];
-  it.acc = v[(int64_t)ss * nr + (it.act ? it.c : 0)];
-  return it;
+template <int K, bool kOne>
+__device__ __forceinline__ void load_item(const Win &W, int32_t row, uint32_t c8, Item<K> &it) {
+  constexpr int kBytes = row_record_bytes(K == 2 ? 0 : K == 6 ? 1 : K == 10 ? 2 : 3);
+  const uint32_t rec = __umul24((uint32_t)row, kBytes) + W.rec;
+  if constexpr (K > 0) {
+#pragma unroll
+    for (int j = 0; j < K / 2 + 1; ++j) it.ix[j] = lds_u(rec + 8 * (K + 2) + 4 * j);
+#pragma unroll
+    for (int j = 0; j < K; ++j) it.w[j] = *lds_d(rec + 8 * j);
+  }
+  it.d = *lds_d(rec + 8 * K);
+  it.r = *lds_d(rec + 8 * (K + 1));
+  it.at = kOne ? 8u * (uint32_t)row : __umul24((uint32_t)row, 8u * (uint32_t)W.gw) + c8;
+  it.acc = *lds_d(it.at + kCtlBytes);
 }
 
-template <bool kOne>
-__device__ __forceinline__ double solve_item(const Item &it, int32_t nr, const double *v, const Dep *ovf) {
-  const int32_t c = it.c;
-  const int32_t s0 = (int32_t)(it.r.x & 0xffffu), s1 = (int32_t)(it.r.x >> 16);
-  const int32_t cnt = (int32_t)(it.r.y & 0xffffu), ob = (int32_t)(it.r.y >> 16);
-  const double xa = v[(int64_t)s0 * (kOne ? 1 : nr) + c];
-  const double xb = v[(int64_t)s1 * (kOne ? 1 : nr) + c];
-  double acc = it.acc - it.w0 * xa;
-  acc = acc - it.w1 * xb;
-  if (cnt > 2) acc = ovf_sum<kOne>(acc, ovf + ob, cnt - 2, v, nr, c);
-  return acc;
+// The x an item reads, all requested at once. Slots hold byte offsets of one
+// column's x, or (several columns) counts of doubles.
+template <int K, bool kOne>
+__device__ __forceinline__ void load_x(const Item<K> &it, uint32_t c8, double (&xv)[K > 0 ? K : 1]) {
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const uint32_t s = j & 1 ? it.ix[j >> 1] >> 16 : it.ix[j >> 1] & 0xffffu;
+    xv[j] = *lds_d((kOne ? s : 8u * s + c8) + kCtlBytes);
+  }
+}
+
+template <int K, bool kOne, bool kOvf>
+__device__ __forceinline__ double solve_item(const Win &W, const Item<K> &it, uint32_t c8,
+                                             const double (&xv)[K > 0 ? K : 1]) {
+  double acc = it.acc;
+  if constexpr (K > 0) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) acc = fma(-it.w[j], xv[j], acc);
+    if constexpr (kOvf) {
+      const int32_t cnt = (int32_t)(it.ix[K / 2] & 0xffffu), ob = (int32_t)(it.ix[K / 2] >> 16);
+      if (cnt > K) acc = ovf_sum(W, acc, ob, cnt - K, kOne ? 0u : c8);
+    }
+  }
+  return div_by(acc, it.d, it.r);
+}
+
+// Phase 2 of a window of width K (flags as in the window table). kOvf: the
+// window has overflow records. kOneWave: every level has at most 64 items and
+// the calling wave solves them all.
+template <int WG, bool kOne, int K, bool kOvf, bool kOneWave, bool kTimed>
+__device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_t lA, float *times, float ns_per_tick,
+                                             unsigned long long t_prev, float p1_per_row) {
+  const int tid = threadIdx.x;
+  const int32_t gw = kOne ? 1 : W.gw;
+  const int32_t *lv = W.lv;
+  auto stamp = [&](int32_t lg) {
+    if (kTimed && tid == 0) {
+      const unsigned long long now = wall_clock64();
+      times[lA + lg] = (float)(now - t_prev) * ns_per_tick + p1_per_row * (float)(lv[lg + 1] - lv[lg]);
+      t_prev = now;
+    }
+  };
+  if (kOneWave || (flags & 2)) {
+    // one item per thread: row s0 of the level, column c8 / 8
+    const int32_t s0 = kOne ? tid : tid / gw;
+    const uint32_t c8 = kOne ? 0u : 8u * (uint32_t)(tid - s0 * gw);
+    const int32_t wave0 = kOneWave ? 0 : __builtin_amdgcn_readfirstlane((kOne ? (tid & ~63) : (tid & ~63) / gw));
+    const int lane = tid & 63;
+    // levels in chunks of 62: lane i holds the bound of level l0 + i, read
+    // once per chunk, so a level's bounds come from registers; the level past
+    // a chunk's (or the window's) end is loaded and dropped
+    constexpr int kChunk = 62;
+    for (int32_t l0 = 0; l0 < W.NL; l0 += kChunk) {
+      const int32_t nlc = W.NL - l0 < kChunk ? W.NL - l0 : kChunk;
+      const int32_t lvreg = lv[l0 + lane <= W.NL ? l0 + lane : W.NL];
+      int32_t pb = __builtin_amdgcn_readlane(lvreg, 0), pe = __builtin_amdgcn_readlane(lvreg, 1);
+      bool on = kOneWave || wave0 < pe - pb;
+      Item<K> a, b;
+      if (on) load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, a);
+      auto step = [&](int32_t l, Item<K> &cur, Item<K> &nxt) {
+        // the level's x first, then the next level's records, which do not
+        // depend on it (LDS returns in order)
+        double xv[K > 0 ? K : 1];
+        if (on) load_x<K, kOne>(cur, c8, xv);
+        pb = pe;
+        pe = __builtin_amdgcn_readlane(lvreg, l + 2);
+        const bool on_next = kOneWave || wave0 < pe - pb;
+        if (on_next) load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        if (on) *lds_d(cur.at + kCtlBytes) = solve_item<K, kOne, kOvf>(W, cur, c8, xv);
+        on = on_next;
+        if (kOneWave)
+          wave_lds_barrier();
+        else
+          lds_barrier();  // LDS only: the global x is read only across a window restart
+        stamp(l0 + l);
+      };
+      int32_t l = 0;
+      for (; l + 1 < nlc; l += 2) {
+        step(l, a, b);
+        step(l + 1, b, a);
+      }
+      if (l < nlc) step(l, a, b);
+    }
+  } else {
+    for (int32_t l = 0; l < W.NL; ++l) {
+      const int32_t pb = lv[l], items = (lv[l + 1] - pb) * gw;
+      for (int32_t t = tid; t < items; t += WG) {
+        const int32_t s = kOne ? t : t / gw;
+        const uint32_t c8 = kOne ? 0u : 8u * (uint32_t)(t - s * gw);
+        Item<K> it;
+        load_item<K, kOne>(W, pb + s, c8, it);
+        double xv[K > 0 ? K : 1];
+        load_x<K, kOne>(it, c8, xv);
+        *lds_d(it.at + kCtlBytes) = solve_item<K, kOne, kOvf>(W, it, c8, xv);
+      }
+      lds_barrier();
+      stamp(l);
+    }
+  }
 }
 
 // Phase 1: (row, rhs) items per thread whose loads are in flight together,
@@ -140,13 +259,11 @@ template <int WG, bool kOne, bool kTimed, bool kSplit = false>
 __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restrict__ win, int32_t nwin, int32_t nrhs,
                                              int32_t ng, int32_t c0_arg, const ThinArgs &A, float *times,
                                              float ns_per_tick, unsigned *prog = nullptr, unsigned ptag = 0) {
-  double *lds = reinterpret_cast<double *>(lds_raw + kCtlBytes);
   const int32_t nr = kOne && !kSplit ? 1 : nrhs;  // stride of the global vectors
   const int32_t gw = kOne ? 1 : ng;               // columns in LDS and per row of items
   const int32_t c0 = kSplit ? c0_arg : 0;         // the first of those columns
   const int tid = threadIdx.x;
   const int32_t *__restrict__ level_ptr = A.level_ptr;
-  const double *__restrict__ sdg = A.sdg;
   const int32_t *__restrict__ ext_ptr = A.ext_ptr;
   const ExtDep *__restrict__ ext = A.ext;
   const double *__restrict__ bp = A.bp;
@@ -164,21 +281,25 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
     const int32_t R = P1 - P0;
     const int32_t NO = W.z;  // the window's overflow records
     const int32_t NL = lB - lA;
+    const int kc = (flags >> 2) & 3;
     // the host sizes windows to fit, and 16-bit slots and offsets must hold R and NO
-    if (thin_window_bytes(R, NO, NL, gw) > kWinBytes - kCtlBytes || R >= 65536 || NO >= 65536) return bits | EB_ARG;
-    double2 *rw = reinterpret_cast<double2 *>(lds);          // [R] w0, w1 (scaled by 1/diagonal)
-    Dep *ovf = reinterpret_cast<Dep *>(rw + R);               // [NO] third and later dependencies
-    uint2 *rix = reinterpret_cast<uint2 *>(ovf + NO);         // [R, padded to even] slot0, slot1, count, overflow
-    double *v = reinterpret_cast<double *>(rix + ((R + 1) & ~1));  // [(R + 1) * gw] partial sums, then x; zero row R
-    int32_t *lv = reinterpret_cast<int32_t *>(v + (int64_t)(R + 1) * gw);  // [NL + 1] level bounds from P0
-    // phase 1. Each thread requests its items' right-hand side, diagonal and
-    // range of dependencies before the window; in the first round it streams
+    if (thin_window_bytes(R, NO, NL, gw, kc) > kWinBytes - kCtlBytes || R >= 65536 || NO >= 65536) return bits | EB_ARG;
+    Win X;
+    X.rec = kCtlBytes + (uint32_t)window_x_bytes(R, gw);
+    X.ovf = X.rec + 16 * (uint32_t)window_record_units(R, kc);
+    int32_t *lv = reinterpret_cast<int32_t *>(lds_raw + X.ovf + 16 * NO);
+    X.lv = lv;
+    X.NL = NL, X.gw = gw;
+    const int32_t nu = (int32_t)window_image_units(R, NO, kc);
+    double *v = reinterpret_cast<double *>(lds_raw + kCtlBytes);
+    // phase 1. Each thread requests its items' right-hand side and range of
+    // dependencies before the window; in the first round it streams
     // the window's static image into LDS while those are in flight; then it
     // subtracts the dependencies before the window (in the row's column order).
     const int32_t nitems = R * gw;
     constexpr int kI = p1_items<WG, kOne>();
     for (int32_t base = 0; base < nitems; base += WG * kI) {
-      double acc[kI], dg[kI];
+      double acc[kI];
       int32_t e0[kI], e1[kI];
 #pragma unroll
       for (int j = 0; j < kI; ++j) {
@@ -193,16 +314,14 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
           acc[j] = A.rio.b[(int64_t)A.rio.perm[pos] * nr + cj];
         else
           acc[j] = bp[(int64_t)pos * nr + cj];
-        dg[j] = sdg[pos];
         e0[j] = ext_ptr[pos];
         e1[j] = it < nitems ? ext_ptr[pos + 1] : e0[j];
       }
       if (base == 0) {
-        for (int32_t i = tid; i <= NL; i += WG) lv[i] = level_ptr[lA + i] - P0;
+        for (int32_t i = tid; i <= NL + 1; i += WG) lv[i] = level_ptr[lA + (i <= NL ? i : NL)] - P0;
         for (int32_t i = tid; i < gw; i += WG) v[(int64_t)R * gw + i] = 0.0;
         const uint4 *__restrict__ im = A.img + W.w;
-        uint4 *dst = reinterpret_cast<uint4 *>(lds);
-        const int32_t nu = (int32_t)window_image_units(R, NO);
+        uint4 *dst = reinterpret_cast<uint4 *>(lds_raw + X.rec);
         constexpr int kC = p1_copy<WG>();
         for (int32_t u0 = 0; u0 < nu; u0 += WG * kC) {
           uint4 t[kC];
@@ -238,9 +357,9 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
           for (int d = 0; d < kBatch; ++d) xv[d] = xs[(int64_t)k[d] * nr + c];
 #pragma unroll
           for (int d = 0; d < kBatch; ++d)
-            if (e + d < e1[j]) a -= wv[d] * xv[d];
+            if (e + d < e1[j]) a = fma(-wv[d], xv[d], a);
         }
-        v[(int64_t)it] = a * (1.0 / dg[j]);
+        v[(int64_t)it] = a;
       }
     }
     __syncthreads();
@@ -248,56 +367,26 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
       t_prev = wall_clock64();
       p1_per_row = R > 0 ? (float)(t_prev - t_w0) * ns_per_tick / (float)R : 0.f;
     }
-    // phase 2
-    if (flags & 3) {
-      const bool one_wave = flags & 1;
-      if (!one_wave || tid < 64) {
-        const int lane = tid & 63;
-        // levels in chunks of 63: lane i holds the bound of level c0 + i, read
-        // once per chunk, so a level's bounds come from registers
-        for (int32_t c0 = 0; c0 < NL; c0 += 63) {
-          const int32_t nlc = NL - c0 < 63 ? NL - c0 : 63;
-          const int32_t lvreg = lv[c0 + lane <= NL ? c0 + lane : NL];
-          int32_t pb = __builtin_amdgcn_readlane(lvreg, 0);
-          int32_t items = (__builtin_amdgcn_readlane(lvreg, 1) - pb) * gw;
-          Item cur = load_item<kOne>(pb, items, tid, gw, v, rw, rix);
-          for (int32_t l = 0; l < nlc; ++l) {
-            Item nxt = cur;
-            if (l + 1 < nlc) {
-              pb = __builtin_amdgcn_readlane(lvreg, l + 1);
-              items = (__builtin_amdgcn_readlane(lvreg, l + 2) - pb) * gw;
-              nxt = load_item<kOne>(pb, items, tid, gw, v, rw, rix);
-            }
-            if (cur.act) v[(int64_t)cur.s * gw + cur.c] = solve_item<kOne>(cur, gw, v, ovf);
-            if (one_wave)
-              wave_lds_barrier();
-            else
-              lds_barrier();  // LDS only: the global x is read only across a window restart
-            if (kTimed && tid == 0) {
-              const int32_t lg = c0 + l;
-              const unsigned long long now = wall_clock64();
-              times[lA + lg] = (float)(now - t_prev) * ns_per_tick + p1_per_row * (float)(lv[lg + 1] - lv[lg]);
-              t_prev = now;
-            }
-            cur = nxt;
-          }
-        }
-      }
+#define LEVELS(K, OVF)                                                                                              \
+  if (flags & 1) {                                                                                                  \
+    if (tid < 64) solve_levels<WG, kOne, K, OVF, true, kTimed>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row); \
+  } else {                                                                                                          \
+    solve_levels<WG, kOne, K, OVF, false, kTimed>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row);             \
+  }
+    if (kc == 0 && NO == 0) {
+      LEVELS(2, false)
+    } else if (kc == 0) {
+      LEVELS(2, true)
+    } else if (kc == 1 && NO == 0) {
+      LEVELS(6, false)
+    } else if (kc == 1) {
+      LEVELS(6, true)
+    } else if (kc == 2) {
+      LEVELS(10, true)
     } else {
-      for (int32_t l = 0; l < NL; ++l) {
-        const int32_t pb = lv[l], items = (lv[l + 1] - pb) * gw;
-        for (int32_t t = tid; t < items; t += WG) {
-          const Item it = load_item<kOne>(pb, items, t, gw, v, rw, rix);
-          v[(int64_t)it.s * gw + it.c] = solve_item<kOne>(it, gw, v, ovf);
-        }
-        lds_barrier();
-        if (kTimed && tid == 0) {
-          const unsigned long long now = wall_clock64();
-          times[lA + l] = (float)(now - t_prev) * ns_per_tick + p1_per_row * (float)(lv[l + 1] - lv[l]);
-          t_prev = now;
-        }
-      }
+      LEVELS(0, false)
     }
+#undef LEVELS
     __syncthreads();  // every x of the window is in LDS
     for (int32_t i = tid; i < nitems; i += WG) {
       const double x = v[i];
@@ -370,12 +459,11 @@ __device__ void prefetch_windows(char *lds_raw, const int4 *__restrict__ win, in
     if (!s_go) break;
     const int4 W = win[j];
     const int32_t P0 = A.level_ptr[W.x], P1 = A.level_ptr[win[j + 1].x], R = P1 - P0;
-    const int32_t nu = (int32_t)window_image_units(R, W.z);
+    const int32_t nu = (int32_t)window_image_units(R, W.z, (W.y >> 2) & 3);
     const uint4 *im = A.img + W.w;
     for (int32_t u = tid * 8; u < nu; u += WG * 8) sink ^= im[u].x;
     const double *bw = A.bp + (int64_t)P0 * nrhs;
     for (int32_t u = tid * 16; u < R * nrhs; u += WG * 16) sink ^= (unsigned)__double_as_longlong(bw[u]);
-    for (int32_t u = tid * 16; u < R; u += WG * 16) sink ^= (unsigned)__double_as_longlong(A.sdg[P0 + u]);
     for (int32_t u = tid * 32; u <= R; u += WG * 32) sink ^= (unsigned)A.ext_ptr[P0 + u];
     const int32_t e0 = A.ext_ptr[P0], e1 = A.ext_ptr[P1];
     for (int32_t e = e0 + tid * 8; e < e1; e += WG * 8) sink ^= (unsigned)A.ext[e].col;

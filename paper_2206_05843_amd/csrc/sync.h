@@ -5,6 +5,25 @@
 
 #include <cstdint>
 
+// a / d with 1/d at hand: the quotient estimate a (1/d) corrected by its exact
+// residual (Markstein's division), three dependent operations in place of the
+// dozen of a full division on a chain that waits for a. The result is that of
+// a / d; where the residual is not finite (a or the quotient is not) the
+// estimate stands, which is then the infinity or NaN of a / d.
+// recip_of gives the 1/d to pass: NaN where d is so large or small that the
+// correction would leave the normal range; such a division is done in full.
+__device__ __forceinline__ double recip_of(double d) {
+  const double m = fabs(d);
+  return m >= 0x1p-1000 && m <= 0x1p1000 ? 1.0 / d : __builtin_nan("");
+}
+__device__ __forceinline__ double div_by(double a, double d, double r) {
+  const double q = a * r;
+  const double e = fma(-d, q, a);
+  double x = fma(e, r, q);
+  if (__builtin_expect(!isfinite(e), 0)) x = r == r ? q : a / d;
+  return x;
+}
+
 // Workgroup barrier that orders LDS only: global stores may still be in
 // flight. Separates consecutive levels inside a thin run.
 __device__ __forceinline__ void lds_barrier() {

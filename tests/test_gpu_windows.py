@@ -1,0 +1,84 @@
+"""LDS windows of the thin runs: every width class of the inline records (2, 6
+and 10 dependencies a row, overflow records beyond, windows of one level), one
+wave and several, one column and several, against the oracle and, bit for bit,
+against the wide-level launches (every executor sums a row's products in
+ascending position and divides once)."""
+import numpy as np
+import pytest
+import torch
+
+import gen
+import oracle
+from tests.gpu_util import dev, to_dev
+
+pytestmark = pytest.mark.gpu
+sp = pytest.importorskip("paper_2206_05843_amd")
+
+TOL = 1e-10
+
+
+def _solve(h, b, nrhs, **sched):
+    h.set_schedule(sp.ORIGINAL, **sched)
+    x = h.solve(b)
+    h.check()
+    return x
+
+
+@pytest.mark.parametrize("draws", [1, 2, 3, 6, 7, 10, 13])
+@pytest.mark.parametrize("n,window", [(1, 64), (2, 64), (65, 4), (1000, 64), (4099, 700), (9001, 3000)])
+def test_widths(draws, n, window):
+    m = gen.window_random(n, 17 * draws + n, window, draws)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    for nrhs in (1, 3):
+        b = gen.rhs(m, nrhs)
+        ref = oracle.solve(m, b)
+        wide = _solve(h, to_dev(b), nrhs, mode=1)
+        assert oracle.relerr(wide.cpu().numpy(), ref) <= TOL
+        for wg in (256, 512, 1024):
+            assert torch.equal(_solve(h, to_dev(b), nrhs, mode=2, wg_threads=wg), wide), (nrhs, wg)
+        assert torch.equal(_solve(h, to_dev(b), nrhs, mode=2, wg_threads=1024, thin_cols=1), wide)
+        assert torch.equal(_solve(h, to_dev(b), nrhs, mode=3), wide)
+
+
+def test_long_rows_keep_their_order():
+    # rows beyond the sorted length, with levels that do not follow the columns
+    rng = np.random.default_rng(5)
+    n = 1400
+    a = np.zeros((n, n))
+    for i in range(1, n):
+        a[i, rng.integers(0, i, size=2)] = rng.uniform(-1, 1, size=2)
+    for i in (700, 1399):
+        a[i, rng.permutation(i)[:650]] = rng.uniform(-1, 1, size=650)
+    a[np.arange(n), np.arange(n)] = 1.0 + np.abs(a).sum(1)
+    m = gen.from_dense_lower(a)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    b = gen.rhs(m, 1)
+    ref = oracle.solve(m, b)
+    for mode in (0, 1, 2, 3):
+        assert oracle.relerr(_solve(h, to_dev(b), 1, mode=mode).cpu().numpy(), ref) <= TOL, mode
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+def test_division_at_the_ends_of_the_range(mode):
+    # diagonals whose reciprocal leaves the normal range are divided in full
+    d = np.array([2.0 ** -1060, -2.0 ** -1010, 2.0 ** 1015, 3.0, -7.0, 2.0 ** -1000, 2.0 ** 1000, 1e-300])
+    b = np.array([2.0 ** -1050, 2.0 ** -1020, 2.0 ** 1010, 1.0, 0.0, 3.0 * 2.0 ** -990, 2.0 ** 990, 5e-299])
+    m = gen.from_dense_lower(np.diag(d))
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    x = _solve(h, to_dev(b), 1, mode=mode).cpu().numpy()
+    assert np.array_equal(x, b / d)
+
+
+@pytest.mark.parametrize("mode", [1, 2, 3])
+def test_infinities_stay_infinities(mode):
+    m = gen.from_dense_lower(np.array([[0.5, 0, 0], [0, 2.0, 0], [1.0, 0, 4.0]]))
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    h.set_schedule(sp.ORIGINAL, mode=mode)
+    x = h.solve(to_dev(np.array([1.7e308, np.inf, 1.0]))).cpu().numpy()
+    assert x[0] == np.inf and x[1] == np.inf and x[2] == -np.inf
+    with pytest.raises(sp.SptrsvError):
+        h.check()
