@@ -551,8 +551,8 @@ sptrsv_status_t build_plan(sptrsv_ctx *h, Plan &P, int32_t n, int64_t nnz, const
   HIPCHK(h, launch_fill_ell(n, P.srp.p, P.sci.p, P.sva.p, P.ell_c.p, P.ell_v.p, s));
   HIPCHK(h, P.wbar.alloc(kGridBarWords));
   HIPCHK(h, hipMemsetAsync(P.wbar.p, 0, kGridBarWords * sizeof(unsigned), s));
-  HIPCHK(h, P.tp.alloc(4));
-  HIPCHK(h, hipMemsetAsync(P.tp.p, 0, 4 * sizeof(unsigned), s));
+  HIPCHK(h, P.tp.alloc(kThinCtlWords));
+  HIPCHK(h, hipMemsetAsync(P.tp.p, 0, kThinCtlWords * sizeof(unsigned), s));
   HIPCHK(h, P.sf_ticket.alloc(1));
   if (trp) {
     P.has_t = true;
@@ -668,10 +668,11 @@ sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s) {
 
 // b (caller's layout) -> bp (level order, interleaved); for the rewritten
 // system b' = T b, where only the rows of T with off-diagonals differ from b:
-// those are recomputed from the caller's b after the plain gather.
-sptrsv_status_t gather_b(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b, int64_t ldb, double *bp,
+// those are recomputed from the caller's b after the plain gather. xp (one
+// right-hand side only, may be null) is marked as not solved yet.
+sptrsv_status_t gather_b(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b, int64_t ldb, double *bp, double *xp,
                          hipStream_t s) {
-  HIPCHK(h, launch_gather(P.n, nrhs, b, ldb, io_iperm(P), bp, s));
+  HIPCHK(h, launch_gather(P.n, nrhs, b, ldb, io_iperm(P), bp, xp, s));
   if (P.has_t && P.n_tpos > 0)
     HIPCHK(h, launch_apply_t(P.n_tpos, nrhs, P.t_lanes, P.tpos.p, io_perm(P), P.trp.p, P.tci.p, P.tva.p, b, 1, ldb,
                              bp, s));
@@ -681,14 +682,19 @@ sptrsv_status_t gather_b(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b, 
 // One solve over the plan's runs, built for (nrhs, its schedule), with the
 // work vectors bp and xp (n * nrhs doubles each). Allocates nothing.
 // One run of the level chain (not the synchronisation-free executor).
+// pending: the x of the plan's rows is already marked as not solved yet.
 static sptrsv_status_t launch_run(sptrsv_ctx *h, Plan &P, const Run &r, int32_t nrhs, const ThinArgs &ta, double *bp,
-                                  double *xp, hipStream_t s) {
+                                  double *xp, bool pending, hipStream_t s) {
   const sptrsv_schedule_t &sc = P.runs_sched;
   int *err = h->d_err.p;
   const int slot = h->prof ? prof_begin(h, r.thin ? 1 : 2, run_bytes(P, r.l0, r.l1, nrhs), s) : -1;
   if (r.thin) {
+    const unsigned long long lim = wait_limit(h);
+    if (!pending && thin_piped(r.nw, lim))
+      HIPCHK(h, launch_fill_pending(P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1] - P.h_level_ptr[(size_t)r.l0],
+                                    nrhs, ta.rio.x ? ta.rio.perm : nullptr, ta.rio.x ? ta.rio.x : xp, s));
     HIPCHK(h, launch_thin_run(sc.wg_threads, P.win.p + r.wi, r.nw, nrhs, ta, err, s, nullptr, 0.f,
-                              thin_width(sc, nrhs)));
+                              thin_width(sc, nrhs), lim));
   } else if (r.longr) {
     const int64_t rows = P.h_level_ptr[r.l1] - P.h_level_ptr[r.l0];
     const int32_t avg = (int32_t)std::min<int64_t>((P.h_lv_nnz[(size_t)r.l0] - rows) / std::max<int64_t>(rows, 1),
@@ -746,7 +752,7 @@ static sptrsv_status_t solve_overlapped(sptrsv_ctx *h, Plan &P, int32_t nrhs, co
   for (int32_t k = 0; k < nseg; ++k) {
     HIPCHK(h, hipStreamWaitEvent(s, ev[1 + k], 0));
     for (int32_t ri = P.seg_run[(size_t)k]; ri < P.seg_run[(size_t)k + 1]; ++ri)
-      STCHK(launch_run(h, P, P.runs[(size_t)ri], nrhs, ta, bp, xp, s));
+      STCHK(launch_run(h, P, P.runs[(size_t)ri], nrhs, ta, bp, xp, false, s));
     const int32_t n_sc = P.s_off[(size_t)k + 1] - P.s_off[(size_t)k];
     if (k + 1 < nseg) {
       HIPCHK(h, hipEventRecord(ev[1 + nseg + k], s));
@@ -770,7 +776,11 @@ sptrsv_status_t solve_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   int *err = h->d_err.p;
   const double vec_bytes = 16.0 * (double)P.n * nrhs + 4.0 * P.n;
   int slot = prof_begin(h, 0, vec_bytes + (P.has_t ? 12.0 * (double)P.nnz_t_off + 4.0 * P.n : 0.0), s);
-  STCHK(gather_b(h, P, nrhs, b, ldb, bp, s));
+  // one right-hand side: the gather marks x for all spread thin runs
+  bool pending = false;
+  if (nrhs == 1 && sc.mode != 3)
+    for (const Run &r : P.runs) pending = pending || (r.thin && thin_piped(r.nw, wait_limit(h)));
+  STCHK(gather_b(h, P, nrhs, b, ldb, bp, pending ? xp : nullptr, s));
   prof_end(h, slot, s);
   if (sc.mode == 3) {  // synchronisation-free: one launch for the whole solve (profiled with the wide class)
     slot = h->prof ? prof_begin(h, 2, run_bytes(P, 0, P.nlev, nrhs), s) : -1;
@@ -781,7 +791,7 @@ sptrsv_status_t solve_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   const ThinArgs ta = thin_args(P, bp, xp);
   for (const Run &r : P.runs) {
     if (sc.mode == 3) break;
-    STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, s));
+    STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, pending, s));
   }
   slot = prof_begin(h, 3, vec_bytes, s);
   HIPCHK(h, launch_scatter(P.n, nrhs, xp, io_iperm(P), x, ldx, s));
@@ -839,7 +849,7 @@ sptrsv_status_t solve_rows(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
                                s));
     ThinArgs ta = thin_args(P, bp, xp);
     ta.rio = RowsIO{b, x, perm, P.has_t ? P.tflag.p : nullptr, P.ell_r.p, P.sci_r.p};
-    for (const Run &r : P.runs) STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, s));
+    for (const Run &r : P.runs) STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, false, s));
     return SPTRSV_OK;
   }
   HIPCHK(h, launch_gather_rows(P.n, nrhs, b, perm, bp, s));
@@ -850,7 +860,7 @@ sptrsv_status_t solve_rows(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
                               sc.wide_grid, wait_limit(h), s));
   } else {
     const ThinArgs ta = thin_args(P, bp, xp);
-    for (const Run &r : P.runs) STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, s));
+    for (const Run &r : P.runs) STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, false, s));
   }
   HIPCHK(h, launch_scatter_rows(P.n, nrhs, xp, perm, x, s));
   return SPTRSV_OK;

@@ -125,9 +125,13 @@ sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipSt
   const sptrsv_schedule_t d = default_schedule();
   for (const BatchWide &bw : h->b_wide)
     for (const Run &r : bw.runs) {
-      if (r.thin)
-        HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s));
-      else
+      if (r.thin) {
+        const int32_t p0 = P.h_level_ptr[(size_t)r.l0];
+        if (thin_piped(r.nw, wait_limit(h)))
+          HIPCHK(h, launch_fill_pending(p0, P.h_level_ptr[(size_t)r.l1] - p0, nrhs, nullptr, P.xp.p, s));
+        HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f, 0,
+                                  wait_limit(h)));
+      } else
         HIPCHK(h, launch_wide_level(d.wide_threads, 1, P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1], nrhs,
                                     P.srp.p, P.sci.p, P.sva.p, P.sdg.p, P.ell_c.p, P.ell_v.p, P.bp.p, P.xp.p,
                                     h->d_err.p, s));
@@ -275,6 +279,8 @@ sptrsv_status_t sptrsv_batch_analyze(sptrsv_handle_t h, int32_t nmat, const int3
   HIPCHK(h, P.ell_c.alloc(n));
   HIPCHK(h, P.ell_v.alloc((size_t)2 * n));
   HIPCHK(h, launch_fill_ell(n, P.srp.p, P.sci.p, P.sva.p, P.ell_c.p, P.ell_v.p, s));
+  HIPCHK(h, P.tp.alloc(kThinCtlWords));
+  HIPCHK(h, hipMemsetAsync(P.tp.p, 0, kThinCtlWords * sizeof(unsigned), s));
   HIPCHK(h, P.lv_rows.alloc(nlev));
   HIPCHK(h, P.lv_nnz.alloc(nlev));
   HIPCHK(h, P.lv_cost.alloc(nlev));
@@ -337,9 +343,12 @@ sptrsv_status_t sptrsv_batch_solve_looped(sptrsv_handle_t h, int32_t nrhs, const
   const int32_t wg = effective_sched(P, nrhs).wg_threads;
   STCHK(batch_windows(h, nrhs, wg, s));
   HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, P.bp.p, s));
+  HIPCHK(h, launch_fill_pending(0, P.n, nrhs, nullptr, P.xp.p, s));
   for (int32_t m = 0; m < h->b_nmat; ++m) {
     const int32_t wi = h->b_h_mwin[(size_t)m], nw = h->b_h_mwin[(size_t)m + 1] - wi - 1;
-    if (nw >= 1) HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s));
+    if (nw >= 1)
+      HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f, 0,
+                                wait_limit(h)));
   }
   STCHK(batch_wide_solves(h, nrhs, wg, s));
   HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, d_x_cat, s));

@@ -124,7 +124,7 @@ sptrsv_status_t sptrsv_level_finish_times(sptrsv_handle_t h, int which, int32_t 
   HIPCHK(h, stamp.alloc((size_t)P->n * (size_t)nrhs));
   HIPCHK(h, lmax.alloc((size_t)P->nlev + 1));
   HIPCHK(h, hipMemsetAsync(lmax.p + P->nlev, 0xff, sizeof(unsigned long long), s));
-  STCHK(gather_b(h, *P, nrhs, d_b, P->n, P->bp.p, s));
+  STCHK(gather_b(h, *P, nrhs, d_b, P->n, P->bp.p, nullptr, s));
   HIPCHK(h, launch_syncfree(P->n, nrhs, P->srp.p, P->sci.p, P->sva.p, P->sdg.p, P->bp.p, P->xp.p, P->sf_ticket.p,
                             h->d_err.p, blocks, wait_limit(h), s, stamp.p));
   HIPCHK(h, launch_stamp_levels(P->nlev, nrhs, P->level_ptr.p, stamp.p, lmax.p, lmax.p + P->nlev, ns_per_tick,
@@ -147,10 +147,11 @@ sptrsv_status_t sptrsv_level_times(sptrsv_handle_t h, int which, int32_t nrhs, c
   sptrsv_schedule_t sc{2, 0, 512, 256, 1};  // every level that fits runs in one workgroup
   STCHK(make_runs(h, *P, nrhs, sc, s));
   HIPCHK(h, hipMemsetAsync(d_times, 0, sizeof(float) * (size_t)P->nlev, s));
-  STCHK(gather_b(h, *P, nrhs, d_b, P->n, P->bp.p, s));
+  STCHK(gather_b(h, *P, nrhs, d_b, P->n, P->bp.p, nullptr, s));
   for (const Run &r : P->runs) {
     if (r.thin) {
-      HIPCHK(h, launch_thin_run(512, P->win.p + r.wi, r.nw, nrhs, thin_args(*P), h->d_err.p, s, d_times, ns_per_tick));
+      HIPCHK(h, launch_thin_run(512, P->win.p + r.wi, r.nw, nrhs, thin_args(*P), h->d_err.p, s, d_times, ns_per_tick,
+                                0, 0));
     } else {
       HIPCHK(h, launch_wide_level(256, 1, P->h_level_ptr[r.l0], P->h_level_ptr[r.l1], nrhs, P->srp.p, P->sci.p,
                                   P->sva.p, P->sdg.p, P->ell_c.p, P->ell_v.p, P->bp.p, P->xp.p, h->d_err.p, s));

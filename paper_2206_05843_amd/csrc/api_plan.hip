@@ -218,8 +218,8 @@ sptrsv_status_t get_plan(sptrsv_ctx *h, Reader &r, uint32_t base, Plan &P) {
   // per-launch control words start at zero, as build_plan leaves them
   HIPCHK(h, P.wbar.alloc(kGridBarWords));
   HIPCHK(h, hipMemset(P.wbar.p, 0, kGridBarWords * sizeof(unsigned)));
-  HIPCHK(h, P.tp.alloc(4));
-  HIPCHK(h, hipMemset(P.tp.p, 0, 4 * sizeof(unsigned)));
+  HIPCHK(h, P.tp.alloc(kThinCtlWords));
+  HIPCHK(h, hipMemset(P.tp.p, 0, kThinCtlWords * sizeof(unsigned)));
   HIPCHK(h, P.sf_ticket.alloc(1));
   STCHK(build_extra_hist(h, P, nullptr));
   P.ready = true;

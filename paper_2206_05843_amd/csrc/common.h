@@ -181,7 +181,7 @@ struct Plan {
   DArr<unsigned> flow_flags, flow_ctl;
   std::vector<int32_t> h_srp, h_sci;   // host copy of the level-ordered pattern (built on first use)
   DArr<double> bp, xp;                 // [n * nrhs] permuted, RHS-interleaved
-  DArr<unsigned> tp;                   // [4] thin-run launches: epoch, progress, helper sink
+  DArr<unsigned> tp;                   // [kThinCtlWords] tickets of spread thin runs (zero between launches)
   DArr<unsigned long long> sf_ticket;  // [1] ticket counter of the synchronisation-free solve
   DArr<unsigned> wbar;                 // [2] barrier counters of persistent wide runs (zero between launches)
   int32_t work_nrhs = 0;
@@ -386,13 +386,14 @@ struct ThinArgs {
   const ExtDep *ext;
   const double *bp;
   double *xp;
-  unsigned *tp;  // pacing words of the L2 prefetch helpers of a single-run launch (null: no helpers)
+  unsigned *tp;  // ticket words of a spread run
   RowsIO rio;
 };
 
 // Launchers (k_solve.hip) ------------------------------------------------------
+// xp (nrhs = 1 only, may be null): set to kPendingX on the way
 hipError_t launch_gather(int32_t n, int32_t nrhs, const double *b, int64_t ldb, const int32_t *iperm, double *bp,
-                         hipStream_t s);
+                         double *xp, hipStream_t s);
 // lanes: 1 (a thread per row and column of b) or 4, 16, 64 (a group per row)
 // b's entry (row, c) at b[row * rs + c * cs]: rs = 1, cs = ldb column-major;
 // rs = nrhs, cs = 1 by rows.
@@ -424,13 +425,27 @@ hipError_t launch_max_abs_diff(int32_t n, const double *x0, const double *x1, un
                                hipStream_t s);
 // First and last position of the rows of every caller-row tile of 64 rows.
 hipError_t launch_tile_span(int32_t n, const int32_t *iperm, int32_t *first, int32_t *last, hipStream_t s);
+// x of a row that is not solved yet where other workgroups wait for it (see
+// k_syncfree.hip): a signalling NaN that arithmetic never produces.
+constexpr unsigned long long kPendingX = 0x7ff4dead5eed5a1dull;
+// Control words of a spread thin run: workgroups done, then a ticket counter per
+// XCD, each in a 128-byte line of its own.
+constexpr int kTicketStride = 32;
+constexpr int kThinCtlWords = kTicketStride * 9;
 int thin_win_bytes();
 // hist: kWidths arrays of nlev * kExtraBuckets, back to back, zeroed by the caller
 hipError_t launch_extra_hist(int32_t n, const int32_t *level_ptr, int32_t nlev, const int32_t *srp,
                              const int32_t *sci, int32_t *lop, int32_t *hist, hipStream_t s);
-// ng: right-hand sides per solver workgroup (a divisor of nrhs; 0 = all)
+// ng: right-hand sides per workgroup (a divisor of nrhs; 0 = all). tlimit > 0:
+// a run of several windows is spread over workgroups, whose waits end at that
+// wall-clock limit; the x of the run's rows must read as kPendingX before the
+// launch (launch_fill_pending, or launch_gather1 with it). 0: one workgroup per
+// group of columns solves the windows one after another.
 hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err,
-                           hipStream_t s, float *times = nullptr, float ns_per_tick = 0.f, int32_t ng = 0);
+                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit);
+bool thin_piped(int32_t nwin, unsigned long long tlimit);
+// x of positions [p0, p0 + rows) = kPendingX (perm: x by caller rows)
+hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s);
 hipError_t launch_fill_ell(int32_t n, const int32_t *srp, const int32_t *sci, const double *sva, int4 *ell_c,
                            double2 *ell_v, hipStream_t s);
 hipError_t launch_wide_level(int threads, int lanes_per_row, int32_t pb, int32_t pe, int32_t nrhs,
@@ -581,7 +596,7 @@ hipError_t launch_rev_io(int32_t n, const int32_t *perm, const int32_t *iperm, i
                          hipStream_t s);
 ThinArgs thin_args(const Plan &P);
 ThinArgs thin_args(const Plan &P, double *bp, double *xp);
-sptrsv_status_t gather_b(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b, int64_t ldb, double *bp,
+sptrsv_status_t gather_b(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b, int64_t ldb, double *bp, double *xp,
                          hipStream_t s);
 // The plan a solve entry point addresses after checking its arguments (null
 // with *st set on failure).

@@ -23,7 +23,7 @@
 
 namespace {
 
-constexpr unsigned long long kPending = 0x7ff4dead5eed5a1dull;
+constexpr unsigned long long kPending = kPendingX;
 constexpr int kBlock = 256;
 constexpr int kDeps = 4;  // dependencies requested together (6 or 8 were slower)
 // pause of a wave none of whose lanes moved, in units of 64 cycles: on the 2D

@@ -15,6 +15,8 @@
 //    global copies visible) when it is full.
 //  * wide levels: one launch over the device per level (kernel boundaries order
 //    the levels).
+#include <algorithm>
+
 #include "common.h"
 #include "sync.h"
 
@@ -69,6 +71,12 @@ struct Ctl {
 // kTimed (used only to label levels for the learned policy): thread 0 stamps the
 // device wall clock around every level and writes per-level times (ns).
 constexpr int kBatch = 4;
+
+// x of a row not yet solved, where other workgroups wait for it: a signalling
+// NaN that arithmetic never produces.
+__device__ __forceinline__ bool is_pending(double x) {
+  return (unsigned long long)__double_as_longlong(x) == kPendingX;
+}
 
 // LDS by byte address: these kernels have no static LDS, so their dynamic LDS
 // starts at address 0 and an item's address needs no base added to it.
@@ -160,15 +168,27 @@ __device__ __forceinline__ double solve_item(const Win &W, const Item<K> &it, ui
   return div_by(acc, it.d, it.r);
 }
 
+// An x that other workgroups of the launch read: device-coherent.
+__device__ __forceinline__ void put_x(double *p, double x) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), (unsigned long long)__double_as_longlong(x),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Phase 2 of a window of width K (flags as in the window table). kOvf: the
 // window has overflow records. kOneWave: every level has at most 64 items and
-// the calling wave solves them all.
-template <int WG, bool kOne, int K, bool kOvf, bool kOneWave, bool kTimed>
+// the calling wave solves them all. kNow: an x also goes to global memory as it
+// is solved, to byte gmul times its place in the window behind gx, for the
+// workgroups that wait for it.
+template <int WG, bool kOne, int K, bool kOvf, bool kOneWave, bool kTimed, bool kNow>
 __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_t lA, float *times, float ns_per_tick,
-                                             unsigned long long t_prev, float p1_per_row) {
+                                             unsigned long long t_prev, float p1_per_row, double *gx, uint32_t gmul) {
   const int tid = threadIdx.x;
   const int32_t gw = kOne ? 1 : W.gw;
   const int32_t *lv = W.lv;
+  auto put = [&](uint32_t at, double x) {
+    *lds_d(at + kCtlBytes) = x;
+    if constexpr (kNow) put_x(reinterpret_cast<double *>(reinterpret_cast<char *>(gx) + (uint64_t)at * gmul), x);
+  };
   auto stamp = [&](int32_t lg) {
     if (kTimed && tid == 0) {
       const unsigned long long now = wall_clock64();
@@ -203,7 +223,7 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
         const bool on_next = kOneWave || wave0 < pe - pb;
         if (on_next) load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, nxt);
         __builtin_amdgcn_sched_barrier(0);
-        if (on) *lds_d(cur.at + kCtlBytes) = solve_item<K, kOne, kOvf>(W, cur, c8, xv);
+        if (on) put(cur.at, solve_item<K, kOne, kOvf>(W, cur, c8, xv));
         on = on_next;
         if (kOneWave)
           wave_lds_barrier();
@@ -228,7 +248,7 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
         load_item<K, kOne>(W, pb + s, c8, it);
         double xv[K > 0 ? K : 1];
         load_x<K, kOne>(it, c8, xv);
-        *lds_d(it.at + kCtlBytes) = solve_item<K, kOne, kOvf>(W, it, c8, xv);
+        put(it.at, solve_item<K, kOne, kOvf>(W, it, c8, xv));
       }
       lds_barrier();
       stamp(l);
@@ -247,18 +267,24 @@ constexpr int p1_copy() {
   return WG >= 1024 ? 8 : 12;
 }
 
-// The windows [win, win + nwin) of one thin run, by the calling workgroup,
-// for the ng right-hand sides c0 .. c0 + ng - 1 of the nrhs (kOne: ng = 1).
-// The columns are independent, so a run can be split over several
-// workgroups by columns; LDS holds ng values per row (windows are cut for ng
-// columns). Returns the latched error bits; a window that does not fit aborts
-// the run.
-// kSplit: the run is split over workgroups by columns (ng < nrhs); without it
-// the strides and the first column are compile-time where they can be.
-template <int WG, bool kOne, bool kTimed, bool kSplit = false>
-__device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restrict__ win, int32_t nwin, int32_t nrhs,
-                                             int32_t ng, int32_t c0_arg, const ThinArgs &A, float *times,
-                                             float ns_per_tick, unsigned *prog = nullptr, unsigned ptag = 0) {
+// How long a wave that waits sleeps between polls, in units of 64 cycles.
+constexpr int kPollSleep = 1;
+
+// One window, by the calling workgroup, for the ng right-hand sides c0 .. c0 +
+// ng - 1 of the nrhs (kOne: ng = 1): the columns are independent, LDS holds ng
+// values per row. Returns the latched error bits; a window that does not fit is
+// an error.
+// kSplit: ng < nrhs; without it the strides and the first column are
+// compile-time where they can be.
+// kPoll: earlier windows may still be in progress on other workgroups. Every
+// unfinished x then reads as kPendingX, so a load of it returns "done" and the
+// value at once: a row's sum takes the finished values first (they come first:
+// ascending positions), then waits for the others past the caches, until the
+// wall clock reaches t0 + tlimit (time-out).
+template <int WG, bool kOne, bool kTimed, bool kSplit, bool kPoll>
+__device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restrict__ win, int32_t w, int32_t nrhs,
+                                            int32_t ng, int32_t c0_arg, const ThinArgs &A, float *times,
+                                            float ns_per_tick, unsigned long long t0, unsigned long long tlimit) {
   const int32_t nr = kOne && !kSplit ? 1 : nrhs;  // stride of the global vectors
   const int32_t gw = kOne ? 1 : ng;               // columns in LDS and per row of items
   const int32_t c0 = kSplit ? c0_arg : 0;         // the first of those columns
@@ -272,225 +298,298 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
   int bits = 0;
   unsigned long long t_w0 = 0, t_prev = 0;
   float p1_per_row = 0.f;
-  for (int32_t w = 0; w < nwin; ++w) {
-    if (prog && tid == 0) __hip_atomic_store(prog, ptag | (unsigned)w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (kTimed && tid == 0) t_w0 = wall_clock64();
-    const int4 W = win[w];
-    const int32_t lA = W.x, lB = win[w + 1].x, flags = W.y;
-    const int32_t P0 = level_ptr[lA], P1 = level_ptr[lB];
-    const int32_t R = P1 - P0;
-    const int32_t NO = W.z;  // the window's overflow records
-    const int32_t NL = lB - lA;
-    const int kc = (flags >> 2) & 3;
-    // the host sizes windows to fit, and 16-bit slots and offsets must hold R and NO
-    if (thin_window_bytes(R, NO, NL, gw, kc) > kWinBytes - kCtlBytes || R >= 65536 || NO >= 65536) return bits | EB_ARG;
-    Win X;
-    X.rec = kCtlBytes + (uint32_t)window_x_bytes(R, gw);
-    X.ovf = X.rec + 16 * (uint32_t)window_record_units(R, kc);
-    int32_t *lv = reinterpret_cast<int32_t *>(lds_raw + X.ovf + 16 * NO);
-    X.lv = lv;
-    X.NL = NL, X.gw = gw;
-    const int32_t nu = (int32_t)window_image_units(R, NO, kc);
-    double *v = reinterpret_cast<double *>(lds_raw + kCtlBytes);
-    // phase 1. Each thread requests its items' right-hand side and range of
-    // dependencies before the window; in the first round it streams
-    // the window's static image into LDS while those are in flight; then it
-    // subtracts the dependencies before the window (in the row's column order).
-    const int32_t nitems = R * gw;
-    constexpr int kI = p1_items<WG, kOne>();
-    for (int32_t base = 0; base < nitems; base += WG * kI) {
-      double acc[kI];
-      int32_t e0[kI], e1[kI];
+  if (kTimed && tid == 0) t_w0 = wall_clock64();
+  const int4 W = win[w];
+  const int32_t lA = W.x, lB = win[w + 1].x, flags = W.y;
+  const int32_t P0 = level_ptr[lA], P1 = level_ptr[lB];
+  const int32_t R = P1 - P0;
+  const int32_t NO = W.z;  // the window's overflow records
+  const int32_t NL = lB - lA;
+  const int kc = (flags >> 2) & 3;
+  // the host sizes windows to fit, and 16-bit slots and offsets must hold R and NO
+  if (thin_window_bytes(R, NO, NL, gw, kc) > kWinBytes - kCtlBytes || R >= 65536 || NO >= 65536) return EB_ARG;
+  Win X;
+  X.rec = kCtlBytes + (uint32_t)window_x_bytes(R, gw);
+  X.ovf = X.rec + 16 * (uint32_t)window_record_units(R, kc);
+  int32_t *lv = reinterpret_cast<int32_t *>(lds_raw + X.ovf + 16 * NO);
+  X.lv = lv;
+  X.NL = NL, X.gw = gw;
+  const int32_t nu = (int32_t)window_image_units(R, NO, kc);
+  double *v = reinterpret_cast<double *>(lds_raw + kCtlBytes);
+  // phase 1. Each thread requests its items' right-hand side and range of
+  // dependencies before the window; in the first round it streams
+  // the window's static image into LDS while those are in flight; then it
+  // subtracts the dependencies before the window (in the row's order).
+  const int32_t nitems = R * gw;
+  constexpr int kI = p1_items<WG, kOne>();
+  for (int32_t base = 0; base < nitems; base += WG * kI) {
+    double acc[kI];
+    int32_t e0[kI], e1[kI];
 #pragma unroll
-      for (int j = 0; j < kI; ++j) {
-        const int32_t it = base + j * WG + tid;
-        const int32_t itc = it < nitems ? it : nitems - 1;
-        const int32_t sj = kOne ? itc : itc / gw;
-        const int32_t pos = P0 + sj;
-        const int32_t cj = c0 + (kOne ? 0 : itc - sj * gw);
-        // right-hand sides stored by rows: the caller's b through the level
-        // order, except rows of T with off-diagonals (b' in bp)
-        if (A.rio.b && !(A.rio.tflag && A.rio.tflag[pos]))
-          acc[j] = A.rio.b[(int64_t)A.rio.perm[pos] * nr + cj];
-        else
-          acc[j] = bp[(int64_t)pos * nr + cj];
-        e0[j] = ext_ptr[pos];
-        e1[j] = it < nitems ? ext_ptr[pos + 1] : e0[j];
-      }
-      if (base == 0) {
-        for (int32_t i = tid; i <= NL + 1; i += WG) lv[i] = level_ptr[lA + (i <= NL ? i : NL)] - P0;
-        for (int32_t i = tid; i < gw; i += WG) v[(int64_t)R * gw + i] = 0.0;
-        const uint4 *__restrict__ im = A.img + W.w;
-        uint4 *dst = reinterpret_cast<uint4 *>(lds_raw + X.rec);
-        constexpr int kC = p1_copy<WG>();
-        for (int32_t u0 = 0; u0 < nu; u0 += WG * kC) {
-          uint4 t[kC];
+    for (int j = 0; j < kI; ++j) {
+      const int32_t it = base + j * WG + tid;
+      const int32_t itc = it < nitems ? it : nitems - 1;
+      const int32_t sj = kOne ? itc : itc / gw;
+      const int32_t pos = P0 + sj;
+      const int32_t cj = c0 + (kOne ? 0 : itc - sj * gw);
+      // right-hand sides stored by rows: the caller's b through the level
+      // order, except rows of T with off-diagonals (b' in bp)
+      if (A.rio.b && !(A.rio.tflag && A.rio.tflag[pos]))
+        acc[j] = A.rio.b[(int64_t)A.rio.perm[pos] * nr + cj];
+      else
+        acc[j] = bp[(int64_t)pos * nr + cj];
+      e0[j] = ext_ptr[pos];
+      e1[j] = it < nitems ? ext_ptr[pos + 1] : e0[j];
+    }
+    if (base == 0) {
+      for (int32_t i = tid; i <= NL + 1; i += WG) lv[i] = level_ptr[lA + (i <= NL ? i : NL)] - P0;
+      for (int32_t i = tid; i < gw; i += WG) v[(int64_t)R * gw + i] = 0.0;
+      const uint4 *__restrict__ im = A.img + W.w;
+      uint4 *dst = reinterpret_cast<uint4 *>(lds_raw + X.rec);
+      constexpr int kC = p1_copy<WG>();
+      for (int32_t u0 = 0; u0 < nu; u0 += WG * kC) {
+        uint4 t[kC];
 #pragma unroll
-          for (int j = 0; j < kC; ++j) {
-            const int32_t u = u0 + j * WG + tid;
-            t[j] = im[u < nu ? u : nu - 1];
-          }
+        for (int j = 0; j < kC; ++j) {
+          const int32_t u = u0 + j * WG + tid;
+          t[j] = im[u < nu ? u : nu - 1];
+        }
 #pragma unroll
-          for (int j = 0; j < kC; ++j) {
-            const int32_t u = u0 + j * WG + tid;
-            if (u < nu) dst[u] = t[j];
-          }
+        for (int j = 0; j < kC; ++j) {
+          const int32_t u = u0 + j * WG + tid;
+          if (u < nu) dst[u] = t[j];
         }
       }
+    }
+#pragma unroll
+    for (int j = 0; j < kI; ++j) {
+      const int32_t it = base + j * WG + tid;
+      if (it >= nitems) continue;
+      const int32_t c = c0 + (kOne ? 0 : it - (it / gw) * gw);
+      double a = acc[j];
+      int32_t e = e0[j];
+      while (e < e1[j]) {
+        double wv[kBatch], xv[kBatch];
+        int32_t k[kBatch];
+        const int32_t cnt = e1[j] - e < kBatch ? e1[j] - e : kBatch;
+#pragma unroll
+        for (int d = 0; d < kBatch; ++d) {
+          const ExtDep x = ext[e + (d < cnt ? d : 0)];
+          wv[d] = x.w;
+          k[d] = A.rio.x ? x.row : x.col;
+        }
+        // by rows the caller's x is the work vector, read by caller row
+#pragma unroll
+        for (int d = 0; d < kBatch; ++d) xv[d] = xs[(int64_t)k[d] * nr + c];
+        int32_t done = 0;
+#pragma unroll
+        for (int d = 0; d < kBatch; ++d) {
+          if (d < cnt && (!kPoll || (done == d && !is_pending(xv[d])))) {
+            a = fma(-wv[d], xv[d], a);
+            done = d + 1;
+          }
+        }
+        e += done;
+        if (kPoll && done < cnt) break;
+      }
+      acc[j] = a;
+      e0[j] = e;
+      v[(int64_t)it] = a;
+    }
+    if constexpr (kPoll) {
+      // what is left: an item at a time (a row far into the window seldom has
+      // a dependency just before it), polled past the caches
 #pragma unroll
       for (int j = 0; j < kI; ++j) {
+        int32_t e = e0[j];
+        const int32_t ee = e1[j];
+        if (__ballot(e < ee) == 0ull) continue;
         const int32_t it = base + j * WG + tid;
-        if (it >= nitems) continue;
         const int32_t c = c0 + (kOne ? 0 : it - (it / gw) * gw);
         double a = acc[j];
-        for (int32_t e = e0[j]; e < e1[j]; e += kBatch) {
-          double wv[kBatch], xv[kBatch];
-          int32_t k[kBatch];
+        double wv[kBatch];
+        int32_t k[kBatch], eq = -1;  // the batch at eq, kept while it is polled
+        unsigned spins = 0;
+        while (__ballot(e < ee) != 0ull) {
+          const int32_t was = e;
+          if (e < ee) {
+            const int32_t cnt = ee - e < kBatch ? ee - e : kBatch;
+            if (e != eq) {
 #pragma unroll
-          for (int d = 0; d < kBatch; ++d) {
-            const ExtDep x = ext[e + d < e1[j] ? e + d : e];
-            wv[d] = x.w;
-            k[d] = A.rio.x ? x.row : x.col;
+              for (int d = 0; d < kBatch; ++d) {
+                const ExtDep x = ext[e + (d < cnt ? d : 0)];
+                wv[d] = x.w;
+                k[d] = A.rio.x ? x.row : x.col;
+              }
+              eq = e;
+            }
+            double xv[kBatch];
+#pragma unroll
+            for (int d = 0; d < kBatch; ++d)
+              xv[d] = __longlong_as_double((long long)__hip_atomic_load(
+                  reinterpret_cast<const unsigned long long *>(xs) + (int64_t)k[d] * nr + c, __ATOMIC_RELAXED,
+                  __HIP_MEMORY_SCOPE_AGENT));
+            int32_t done = 0;
+#pragma unroll
+            for (int d = 0; d < kBatch; ++d) {
+              if (d < cnt && done == d && !is_pending(xv[d])) {
+                a = fma(-wv[d], xv[d], a);
+                done = d + 1;
+              }
+            }
+            e += done;
           }
-          // by rows the caller's x is the work vector, read by caller row
-#pragma unroll
-          for (int d = 0; d < kBatch; ++d) xv[d] = xs[(int64_t)k[d] * nr + c];
-#pragma unroll
-          for (int d = 0; d < kBatch; ++d)
-            if (e + d < e1[j]) a = fma(-wv[d], xv[d], a);
+          if (__ballot(e != was) == 0ull) __builtin_amdgcn_s_sleep(kPollSleep);
+          if ((++spins & 63u) == 0u && wall_clock64() - t0 > tlimit) {
+            bits |= EB_TIMEOUT;
+            break;
+          }
         }
-        v[(int64_t)it] = a;
+        if (it < nitems) v[(int64_t)it] = a;
       }
     }
-    __syncthreads();
-    if (kTimed && tid == 0) {
-      t_prev = wall_clock64();
-      p1_per_row = R > 0 ? (float)(t_prev - t_w0) * ns_per_tick / (float)R : 0.f;
-    }
-#define LEVELS(K, OVF)                                                                                              \
-  if (flags & 1) {                                                                                                  \
-    if (tid < 64) solve_levels<WG, kOne, K, OVF, true, kTimed>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row); \
-  } else {                                                                                                          \
-    solve_levels<WG, kOne, K, OVF, false, kTimed>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row);             \
   }
-    if (kc == 0 && NO == 0) {
-      LEVELS(2, false)
-    } else if (kc == 0) {
-      LEVELS(2, true)
-    } else if (kc == 1 && NO == 0) {
-      LEVELS(6, false)
-    } else if (kc == 1) {
-      LEVELS(6, true)
-    } else if (kc == 2) {
-      LEVELS(10, true)
-    } else {
-      LEVELS(0, false)
-    }
+  __syncthreads();
+  if (kTimed && tid == 0) {
+    t_prev = wall_clock64();
+    p1_per_row = R > 0 ? (float)(t_prev - t_w0) * ns_per_tick / (float)R : 0.f;
+  }
+  // x goes to global memory as it is solved where a window's place there is a
+  // fixed multiple of its place in LDS (all columns, or one of them), except
+  // from a lone wave, whose every instruction lengthens a level (20 ns a level,
+  // more than the 0.3 us a window's x arrives earlier): the other waves store
+  // its x at the end of the window
+  const bool now = kPoll && !(flags & 1) && !A.rio.x && (kOne || gw == nr);
+  double *gx = xp + (int64_t)P0 * nr + c0;
+  const uint32_t gmul = kSplit ? (uint32_t)nr : 1u;
+#define LEVELS(K, OVF)                                                                                               \
+  if (flags & 1) {                                                                                                   \
+    if (tid < 64)                                                                                                    \
+      solve_levels<WG, kOne, K, OVF, true, kTimed, false>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,  \
+                                                          gmul);                                                     \
+  } else if (kPoll && now) {                                                                                         \
+    solve_levels<WG, kOne, K, OVF, false, kTimed, kPoll>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,   \
+                                                         gmul);                                                      \
+  } else {                                                                                                           \
+    solve_levels<WG, kOne, K, OVF, false, kTimed, false>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,   \
+                                                         gmul);                                                      \
+  }
+  if (kc == 0 && NO == 0) {
+    LEVELS(2, false)
+  } else if (kc == 0) {
+    LEVELS(2, true)
+  } else if (kc == 1 && NO == 0) {
+    LEVELS(6, false)
+  } else if (kc == 1) {
+    LEVELS(6, true)
+  } else if (kc == 2) {
+    LEVELS(10, true)
+  } else {
+    LEVELS(0, false)
+  }
 #undef LEVELS
-    __syncthreads();  // every x of the window is in LDS
-    for (int32_t i = tid; i < nitems; i += WG) {
-      const double x = v[i];
-      if (!isfinite(x)) bits |= EB_NONFINITE;
-      if (!A.rio.x && gw == nr) {  // all columns in this workgroup: the window is one contiguous block
-        xp[(int64_t)P0 * nr + i] = x;
-        continue;
-      }
-      const int32_t sj = kOne ? i : i / gw;
-      const int32_t cj = c0 + (kOne ? 0 : i - sj * gw);
-      if (A.rio.x)  // by rows: the caller's x only
-        A.rio.x[(int64_t)A.rio.perm[P0 + sj] * nr + cj] = x;
-      else
-        xp[(int64_t)(P0 + sj) * nr + cj] = x;
-    }
-    __syncthreads();  // the window's global x is complete before the next phase 1 reads it
+  __syncthreads();  // every x of the window is in LDS
+  for (int32_t i = tid; i < nitems; i += WG) {
+    const double x = v[i];
+    if (!isfinite(x)) bits |= EB_NONFINITE;
+    if (now) continue;
+    const int32_t sj = kOne ? i : i / gw;
+    const int32_t cj = c0 + (kOne ? 0 : i - sj * gw);
+    // by rows: the caller's x only
+    double *to = A.rio.x ? A.rio.x + (int64_t)A.rio.perm[P0 + sj] * nr + cj
+                 : gw == nr ? xp + (int64_t)P0 * nr + i
+                            : xp + (int64_t)(P0 + sj) * nr + cj;
+    if (kPoll)
+      put_x(to, x);
+    else
+      *to = x;
   }
+  __syncthreads();  // the window's global x is complete before the next phase 1 of this workgroup reads it
   return bits;
 }
 
-// L2 prefetch helpers of a single thin run. One workgroup solves; a few more
-// workgroups on the same XCD (workgroups are dispatched to the 8 XCDs in turn,
-// so workgroup 8 h shares workgroup 0's L2) touch one word of every cache line
-// of the next windows' images, b', diagonals and outside-dependency lists, so
-// the solver's phase 1 finds them in L2. They keep at most kAhead windows ahead
-// of the solver, which publishes (epoch tag | window) in tp[1] as it starts
-// each window and advances the epoch tp[0] when it ends; launches on a stream
-// do not overlap, so the epoch read at the start names this launch. The solver
-// never waits for a helper; a helper stops when the epoch moves on, when it
-// has done its windows, or when one wait exceeds kWaitTicks of the device
-// wall clock, so every helper finishes.
-constexpr int kXcd = 8;
-constexpr int kHelp = 4;            // helpers per launch
-constexpr int kAhead = 4;           // windows a helper may run ahead of the solver
-constexpr int kHelpMinWin = 8;      // runs with fewer windows launch no helpers
-constexpr unsigned long long kWaitTicks = 5000;  // 50 us at the 100 MHz wall clock
-constexpr int kTagShift = 20;       // progress word: (epoch mod 2^12) << 20 | window
-
-__device__ __forceinline__ unsigned epoch_tag(unsigned ep) { return (ep & 0xfffu) << kTagShift; }
-
-template <int WG>
-__device__ void prefetch_windows(char *lds_raw, const int4 *__restrict__ win, int32_t nwin, int32_t nrhs,
-                                 const ThinArgs &A, int hh) {
-  int32_t &s_go = reinterpret_cast<Ctl *>(lds_raw)->next;
-  unsigned *tp = A.tp;
-  const int tid = threadIdx.x;
-  const unsigned ep = __hip_atomic_load(tp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  unsigned sink = 0;
-  for (int32_t j = hh; j < nwin; j += kHelp) {
-    if (tid == 0) {
-      int go = 1;
-      const unsigned long long t0 = wall_clock64();
-      for (;;) {
-        if (__hip_atomic_load(tp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ep) {
-          go = 0;  // the solver has finished
-          break;
-        }
-        const unsigned p = __hip_atomic_load(tp + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t at = (p >> kTagShift) == (ep & 0xfffu) ? (int32_t)(p & ((1u << kTagShift) - 1)) : 0;
-        if (j <= at + kAhead) break;
-        if (wall_clock64() - t0 > kWaitTicks) {
-          go = 0;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      s_go = go;
-    }
-    __syncthreads();
-    if (!s_go) break;
-    const int4 W = win[j];
-    const int32_t P0 = A.level_ptr[W.x], P1 = A.level_ptr[win[j + 1].x], R = P1 - P0;
-    const int32_t nu = (int32_t)window_image_units(R, W.z, (W.y >> 2) & 3);
-    const uint4 *im = A.img + W.w;
-    for (int32_t u = tid * 8; u < nu; u += WG * 8) sink ^= im[u].x;
-    const double *bw = A.bp + (int64_t)P0 * nrhs;
-    for (int32_t u = tid * 16; u < R * nrhs; u += WG * 16) sink ^= (unsigned)__double_as_longlong(bw[u]);
-    for (int32_t u = tid * 32; u <= R; u += WG * 32) sink ^= (unsigned)A.ext_ptr[P0 + u];
-    const int32_t e0 = A.ext_ptr[P0], e1 = A.ext_ptr[P1];
-    for (int32_t e = e0 + tid * 8; e < e1; e += WG * 8) sink ^= (unsigned)A.ext[e].col;
-    __syncthreads();  // s_go is rewritten only after every thread has read it
-  }
-  if (sink == 0x9e3779b9u) tp[2] = sink;  // keeps the loads; the value is never read
+// The windows [win, win + nwin) of one thin run one after another, by the
+// calling workgroup.
+template <int WG, bool kOne, bool kTimed, bool kSplit = false>
+__device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restrict__ win, int32_t nwin, int32_t nrhs,
+                                             int32_t ng, int32_t c0, const ThinArgs &A, float *times,
+                                             float ns_per_tick) {
+  int bits = 0;
+  for (int32_t w = 0; w < nwin && !(bits & EB_ARG); ++w)
+    bits |= solve_window<WG, kOne, kTimed, kSplit, false>(lds_raw, win, w, nrhs, ng, c0, A, times, ns_per_tick, 0, 0);
+  return bits;
 }
 
-// One thin run: workgroup g < nrhs / ng solves columns g*ng .. g*ng + ng - 1;
-// with one solver (ng = nrhs) the launcher may add prefetch helpers after it.
+// One thin run in one workgroup per group of ng columns: workgroup g solves
+// columns g*ng .. g*ng + ng - 1. For runs of one window, and for the labelling
+// runs that time levels.
 template <int WG, bool kOne, bool kTimed = false, bool kSplit = false>
 __global__ __launch_bounds__(WG) void k_thin_run(const int4 *__restrict__ win, int32_t nwin, int32_t nrhs, int32_t ng,
                                                  ThinArgs A, int *err, float *times, float ns_per_tick) {
   extern __shared__ __align__(16) char lds_raw[];
-  const int32_t nsolver = nrhs / ng;
-  if ((int32_t)blockIdx.x >= nsolver) {  // helpers exist only when the launcher gave the grid room for them
-    if (blockIdx.x % kXcd == 0) prefetch_windows<WG>(lds_raw, win, nwin, nrhs, A, (int)(blockIdx.x / kXcd) - 1);
-    return;
-  }
-  unsigned ep = 0;
-  if (A.tp) ep = __hip_atomic_load(A.tp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int bits = thin_run_body<WG, kOne, kTimed, kSplit>(lds_raw, win, nwin, nrhs, ng, (int32_t)blockIdx.x * ng, A,
-                                                           times, ns_per_tick, A.tp ? A.tp + 1 : nullptr,
-                                                           epoch_tag(ep));
+                                                           times, ns_per_tick);
+  if (bits) atomicOr(err, bits);
+}
+
+// One thin run with its windows spread over workgroups. A single workgroup
+// spends a window's phase 1 (about 100 KB of records, b' and dependencies
+// through one CU's memory pipeline: 4 to 6 us for 3,000 rows) and the store of
+// its x between the levels of one window and of the next; here the windows
+// after the one being solved are loaded by other workgroups meanwhile, and each
+// waits only for the x it reads (solve_window, kPoll), so what is left of a
+// window is its levels and one hand-over, about 0.5 us.
+// Windows are taken in order from a ticket counter, so the ones a window waits
+// for belong to running workgroups and every wait ends. Columns are
+// independent: group g of ng columns is a chain of its own. Workgroups are
+// dealt to the 8 XCDs in turn, and a chain stays on the workgroups of one
+// (blockIdx mod 8): a hand-over within an XCD takes 425 ns, across them 558, and
+// the windows' columns share its L2. Lane l of nlane holds groups l, l + nlane,
+// ...; tp[kTicketStride * (1 + l)] is its ticket counter, tp[0] counts
+// the workgroups that are done, and the last one clears both.
+// Measured, one right-hand side: the rewritten 2D stencil 1000^2 + chain 1.44 ms a
+// solve against 2.69 with one workgroup (and four that prefetched into its L2),
+// the 300^2 one with its 4,001-row tail 0.74 against 0.89.
+constexpr int kXcd = 8;
+template <int WG, bool kOne, bool kSplit>
+__global__ __launch_bounds__(WG) void k_thin_pipe(const int4 *__restrict__ win, int32_t nwin, int32_t nrhs, int32_t ng,
+                                                  int32_t nlane, ThinArgs A, int *err, unsigned long long tlimit) {
+  extern __shared__ __align__(16) char lds_raw[];
+  const int32_t lane = (int32_t)blockIdx.x % kXcd;
+  if (lane >= nlane) return;
+  int32_t &s_t = reinterpret_cast<Ctl *>(lds_raw)->next;
+  const int32_t groups = nrhs / ng;
+  const int32_t mine = (groups - lane + nlane - 1) / nlane;  // groups of this lane
+  unsigned *ticket = A.tp + kTicketStride * (1 + lane);
+  const unsigned long long t0 = wall_clock64();
+  int bits = 0;
+  while (!(bits & EB_ARG)) {
+    if (threadIdx.x == 0)
+      s_t = (int32_t)__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int32_t t = s_t;
+    __syncthreads();
+    if (t >= nwin * mine) break;
+    const int32_t w = t / mine, g = lane + nlane * (t - w * mine);
+    bits |= solve_window<WG, kOne, false, kSplit, true>(lds_raw, win, w, nrhs, ng, g * ng, A, nullptr, 0.f, t0, tlimit);
+  }
+  if (bits) atomicOr(err, bits);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    if (bits) atomicOr(err, bits);
-    if (A.tp) __hip_atomic_store(A.tp, ep + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned active = gridDim.x / kXcd * (unsigned)nlane;
+    if (__hip_atomic_fetch_add(A.tp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == active - 1) {
+      for (int32_t l = 0; l < nlane; ++l) atomicExch(A.tp + kTicketStride * (1 + l), 0u);
+      atomicExch(A.tp, 0u);
+    }
+  }
+}
+
+// Marks the x of positions [p0, p0 + rows) as unfinished; by rows through perm.
+__global__ void k_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *__restrict__ perm, double *x) {
+  unsigned long long *xb = reinterpret_cast<unsigned long long *>(x);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows * nr; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t r = i / nr;
+    xb[perm ? (int64_t)perm[p0 + r] * nr + (i - r * nr) : p0 * nr + i] = kPendingX;
   }
 }
 
@@ -548,13 +647,23 @@ __global__ __launch_bounds__(WG) void k_batch_run(int32_t nmat, const int32_t *_
 
 template <int WG, bool kOne>
 void set_lds_attr() {
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_pipe<WG, kOne, false>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_pipe<WG, kOne, true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<WG, kOne>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<WG, kOne, false, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
 }
 
+// Workgroups that hold windows of one chain of a spread thin run (6, 12 and 24
+// took the same time on the 2D stencils).
+constexpr int kPipeDepth = 8;
+
 }  // namespace
+
+bool thin_piped(int32_t nwin, unsigned long long tlimit) { return nwin >= 2 && tlimit > 0; }
 
 int thin_win_bytes() { return kWinBytes - kCtlBytes; }
 
@@ -571,49 +680,59 @@ void solve_kernels_init() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
 }
 
+hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fill_pending, dim3(grid_for(rows * nr, 256, 4096)), dim3(256), 0, s, p0, rows, nr, perm, x);
+  return hipGetLastError();
+}
+
 hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err,
-                           hipStream_t s, float *times, float ns_per_tick, int32_t ng) {
+                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit) {
   if (ng <= 0 || ng > nrhs || nrhs % ng || times) ng = nrhs;  // labelling runs are never split
   const bool one = ng == 1;
   const bool split = ng < nrhs;
-  ThinArgs aa = a;
-  unsigned grid = (unsigned)(nrhs / ng);  // one solver per group of ng columns
-  if (grid == 1) {
-    // the solver, plus kHelp prefetch helpers on its XCD for runs long enough
-    // to use them (windows are numbered below 2^20 in the progress word)
-    if (a.tp && nwin >= kHelpMinWin && nwin < (1 << kTagShift)) grid = 1 + kXcd * kHelp;
-  } else {
-    aa.tp = nullptr;  // several solvers: no helpers, no progress words
-  }
+  const int32_t groups = nrhs / ng;
   if (times) {  // labelling runs only: 512 threads
     if (one)
-      hipLaunchKernelGGL((k_thin_run<512, true, true>), dim3(grid), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, aa,
-                         err, times, ns_per_tick);
+      hipLaunchKernelGGL((k_thin_run<512, true, true>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, a, err,
+                         times, ns_per_tick);
     else
-      hipLaunchKernelGGL((k_thin_run<512, false, true>), dim3(grid), dim3(512), kWinBytes, s, win, nwin, nrhs, ng,
-                         aa, err, times, ns_per_tick);
+      hipLaunchKernelGGL((k_thin_run<512, false, true>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, a,
+                         err, times, ns_per_tick);
     return hipGetLastError();
   }
-#define THIN(W)                                                                                              \
-  if (split && one)                                                                                          \
-    hipLaunchKernelGGL((k_thin_run<W, true, false, true>), dim3(grid), dim3(W), kWinBytes, s, win, nwin, nrhs,  \
-                       ng, aa, err, (float *)nullptr, 0.f);                                                  \
-  else if (split)                                                                                            \
-    hipLaunchKernelGGL((k_thin_run<W, false, false, true>), dim3(grid), dim3(W), kWinBytes, s, win, nwin, nrhs, \
-                       ng, aa, err, (float *)nullptr, 0.f);                                                  \
-  else if (one)                                                                                              \
-    hipLaunchKernelGGL((k_thin_run<W, true>), dim3(grid), dim3(W), kWinBytes, s, win, nwin, nrhs, ng, aa, err,  \
-                       (float *)nullptr, 0.f);                                                               \
-  else                                                                                                       \
-    hipLaunchKernelGGL((k_thin_run<W, false>), dim3(grid), dim3(W), kWinBytes, s, win, nwin, nrhs, ng, aa, err, \
-                       (float *)nullptr, 0.f);
-  if (wg == 256) {
-    THIN(256)
-  } else if (wg == 1024) {
-    THIN(1024)
-  } else {
-    THIN(512)
+  // several windows: spread over kPipeDepth workgroups per lane of XCDs (more
+  // when a lane holds several chains)
+  const bool pipe = thin_piped(nwin, tlimit);
+  const int32_t nlane = groups < kXcd ? groups : kXcd;
+  const int32_t chains = (groups + nlane - 1) / nlane;
+  int64_t depth = std::min<int64_t>((int64_t)kPipeDepth * chains, (int64_t)nwin * chains);
+  depth = std::min<int64_t>(depth, 32);  // CUs of an XCD, one workgroup each
+#define THIN(W, ONE, SPLIT)                                                                                       \
+  if (pipe)                                                                                                       \
+    hipLaunchKernelGGL((k_thin_pipe<W, ONE, SPLIT>), dim3((unsigned)depth * kXcd), dim3(W), kWinBytes, s, win,     \
+                       nwin, nrhs, ng, nlane, a, err, tlimit);                                                    \
+  else                                                                                                            \
+    hipLaunchKernelGGL((k_thin_run<W, ONE, false, SPLIT>), dim3((unsigned)groups), dim3(W), kWinBytes, s, win,     \
+                       nwin, nrhs, ng, a, err, (float *)nullptr, 0.f);
+#define THINW(W)              \
+  if (split && one) {         \
+    THIN(W, true, true)       \
+  } else if (split) {         \
+    THIN(W, false, true)      \
+  } else if (one) {           \
+    THIN(W, true, false)      \
+  } else {                    \
+    THIN(W, false, false)     \
   }
+  if (wg == 256) {
+    THINW(256)
+  } else if (wg == 1024) {
+    THINW(1024)
+  } else {
+    THINW(512)
+  }
+#undef THINW
 #undef THIN
   return hipGetLastError();
 }

@@ -96,9 +96,13 @@ __global__ void k_tile_span(int32_t n, const int32_t *__restrict__ iperm, int32_
   }
 }
 
-__global__ void k_gather1(int32_t n, const double *__restrict__ b, const int32_t *__restrict__ iperm, double *bp) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x)
+// One right-hand side; xp (may be null) is marked as not solved yet on the way.
+__global__ void k_gather1(int32_t n, const double *__restrict__ b, const int32_t *__restrict__ iperm, double *bp,
+                          unsigned long long *xp) {
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
     bp[iperm[r]] = b[r];
+    if (xp) xp[r] = kPendingX;
+  }
 }
 
 // The b-transform of the rewritten system (Sec. II.B) on the rows where T has
@@ -333,10 +337,11 @@ constexpr int32_t kTileGrid = SPTRSV_TILE_GRID;  // workgroups of one tile-group
 }  // namespace
 
 hipError_t launch_gather(int32_t n, int32_t nrhs, const double *b, int64_t ldb, const int32_t *iperm, double *bp,
-                         hipStream_t s) {
+                         double *xp, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (nrhs == 1)
-    hipLaunchKernelGGL(k_gather1, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, n, b, iperm, bp);
+    hipLaunchKernelGGL(k_gather1, dim3(grid_for(n, 256, 8192)), dim3(256), 0, s, n, b, iperm, bp,
+                       reinterpret_cast<unsigned long long *>(xp));
   else
     hipLaunchKernelGGL(k_gather, dim3((n + 63) / 64), dim3(256), 0, s, n, nrhs, b, ldb, iperm, bp);
   return hipGetLastError();

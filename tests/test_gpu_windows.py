@@ -82,3 +82,33 @@ def test_infinities_stay_infinities(mode):
     assert x[0] == np.inf and x[1] == np.inf and x[2] == -np.inf
     with pytest.raises(sp.SptrsvError):
         h.check()
+
+
+@pytest.mark.parametrize("nrhs,thin_cols", [(1, 0), (2, 0), (3, 1), (8, 1), (9, 1), (17, 1), (6, 2)])
+def test_spread_windows_repeat(nrhs, thin_cols):
+    """Runs of many windows spread over workgroups: column groups below, at and
+    above the number of XCDs; repeated, by rows and in graph replays with new
+    right-hand sides in between (stale values of the solve before must not pass
+    for finished ones)."""
+    m = gen.stencil2d_chain(70, 900, 3)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    h.set_schedule(sp.ORIGINAL, mode=1)
+    b1, b2 = to_dev(gen.rhs(m, nrhs)), to_dev(gen.rhs(m, nrhs)[:, ::-1])
+    ref1, ref2 = h.solve(b1).clone(), h.solve(b2).clone()
+    h.set_schedule(sp.ORIGINAL, mode=2, wg_threads=256, thin_cols=thin_cols)
+    for _ in range(3):
+        assert torch.equal(h.solve(b1), ref1)
+        assert torch.equal(h.solve(b2), ref2)
+        if nrhs > 1:
+            assert torch.equal(h.solve_rows(b1.t().contiguous()).t(), ref1)
+            assert torch.equal(h.solve_rows(b2.t().contiguous()).t(), ref2)
+    b, x = b1.clone(), torch.empty_like(b1)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        g = h.graph_create(b, x)
+        for src, ref in ((b1, ref1), (b2, ref2), (b1, ref1)):
+            b.copy_(src)
+            h.graph_launch(g)
+            torch.cuda.synchronize()
+            assert torch.equal(x, ref)
+    h.check()
