@@ -129,15 +129,9 @@ bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs) {
   return thin_window_bytes(rows, 0, 1, nrhs, kWidths) <= thin_win_bytes();
 }
 
-// Upper bound on the overflow records of level l's rows in a window of width
-// class kc that starts at level ws: dependencies (beyond each row's K at the
-// highest levels) at most l - ws levels up, counted by whole distance buckets.
-static int64_t extras_in(const Plan &P, int kc, int32_t l, int32_t ws) {
-  const int32_t d = l - ws;
-  const int32_t *hx = P.h_xh[kc].data() + (size_t)l * kExtraBuckets;
-  int64_t e = 0;
-  for (int b = 0; b < kExtraBuckets && kExtraLo[b] <= d; ++b) e += hx[b];
-  return e;
+// Bucket of level distance d of the overflow-record histograms.
+static int extra_bucket(int32_t d) {
+  return d <= 4 ? d - 1 : d <= 8 ? 4 : d <= 16 ? 5 : d <= 32 ? 6 : d <= 64 ? 7 : d <= 256 ? 8 : 9;
 }
 
 // Cut levels [l0, l1) into LDS windows; flag windows whose levels fit one wave
@@ -165,14 +159,18 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
       int32_t l = ws;
       for (; l < l1; ++l) {
         const int64_t rl = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
-        const int64_t el = extras_in(P, k, l, ws);
+        // upper bound on the overflow records of level l's rows: dependencies
+        // (beyond each row's K at the highest levels) at most l - ws levels up
+        const int64_t el = l > ws ? P.h_xh[k][(size_t)l * kExtraBuckets + extra_bucket(l - ws)] : 0;
         if (thin_window_bytes(rows + rl, en + el, l - ws + 1, nrhs, k) > cap) break;
         rows += rl;
         en += el;
         mi = std::max<int64_t>(mi, rl * nrhs);
-        const int64_t per = (rl * nrhs + wg - 1) / wg;
-        ns += (rl * nrhs <= 64 ? 60.0 : 160.0 * (double)per) + 5.0 * width_of(k) +
-              90.0 * (double)((el + 4 * rl - 1) / (4 * rl));
+        ns += (rl * nrhs <= 64   ? 60.0
+               : rl * nrhs <= wg ? 160.0
+                                 : 160.0 * (double)((rl * nrhs + wg - 1) / wg)) +
+              5.0 * width_of(k) +
+              (el ? 90.0 * (double)((el + 4 * rl - 1) / (4 * rl)) : 0.0);
       }
       if (l > ws && (end == ws || ns / (l - ws) < best)) {
         best = ns / (l - ws);
@@ -405,6 +403,25 @@ static sptrsv_status_t build_overlap(sptrsv_ctx *h, Plan &P, int32_t nrhs, const
   return SPTRSV_OK;
 }
 
+// The synchronisation-free executor (mode 3) in LDS windows: where levels are
+// narrow a window holds several, and most hand-overs between rows stay in LDS
+// (0.1 to 0.3 us a level) instead of going through memory (1.0 to 1.4 us). A
+// window's dependencies on earlier ones go through one CU's memory pipeline,
+// though, about one a cycle, so it pays up to some off-diagonals per level.
+// Measured (one column, us; windows | a wait per row; off-diagonals per level):
+// power law n = 200,000 918 | 2,160 (740), 400,000 1,388 | 2,535 (1,370),
+// 800,000 2,390 | 3,068 (2,340), 1.6M 4,645 | 3,963 (3,700); torso2-like
+// n = 60,000 504 | 674 (1,030), 116,000 791 | 710 (1,990); 2D stencil 1000^2
+// 1,103 | 2,149 (1,000). The line lies at 1,600; every level must fit a window.
+constexpr int64_t kFreeDeps = 1600;
+constexpr int32_t kFreeThreads = 1024;  // 512: 1.25 times slower on the power law, 256: 1.75 times
+static bool free_in_windows(const Plan &P) {
+  if (P.nlev < 2 || P.nnz - P.n > kFreeDeps * P.nlev) return false;
+  for (int32_t l = 0; l < P.nlev; ++l)
+    if (!level_fits_window(P, l, 1)) return false;
+  return true;
+}
+
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s) {
   P.runs.clear();
   P.h_win.clear();
@@ -412,8 +429,14 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   const int64_t thr = sc.thin_rows;
   auto rows_of = [&](int32_t l) -> int64_t { return P.h_level_ptr[l + 1] - P.h_level_ptr[l]; };
   const bool flow = sc.mode == 4;
-  const int32_t gw = thin_width(sc, nrhs);  // columns per thin-run workgroup
-  for (int32_t l = 0; l < P.nlev; ++l) {
+  const bool freew = sc.mode == 3 && free_in_windows(P);
+  const int32_t gw = freew ? 1 : thin_width(sc, nrhs);  // columns per thin-run workgroup
+  if (freew) {
+    Run r{0, P.nlev, true};
+    r.free = true;
+    P.runs.push_back(r);
+  }
+  for (int32_t l = 0; l < P.nlev && sc.mode != 3; ++l) {
     const int64_t rows = rows_of(l);
     bool thin = sc.mode == 2 || ((sc.mode == 0 || flow) && rows <= thr);
     if (thin_window_bytes(rows, 0, 1, gw, kWidths) > cap) thin = false;  // must fit one window alone
@@ -453,7 +476,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   for (Run &r : P.runs) {
     if (!r.thin) continue;
     r.wi = (int32_t)P.h_win.size();
-    r.nw = cut_windows(P, r.l0, r.l1, gw, sc.wg_threads, P.h_win);
+    r.nw = cut_windows(P, r.l0, r.l1, gw, r.free ? kFreeThreads : sc.wg_threads, P.h_win);
   }
   P.runs_nrhs = -1;  // until the images are built
   STCHK(build_images(h, P, gw, s));
@@ -663,6 +686,9 @@ sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s) {
   for (int k = 0; k < kWidths; ++k)
     HIPCHK(h, hipMemcpyAsync(P.h_xh[k].data(), hist.p + (size_t)k * len, sizeof(int32_t) * len, hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));
+  for (auto &v : P.h_xh)  // prefix sums over the buckets of each level
+    for (size_t i = 0; i < len; ++i)
+      if (i % kExtraBuckets) v[i] += v[i - 1];
   return SPTRSV_OK;
 }
 
@@ -693,8 +719,8 @@ static sptrsv_status_t launch_run(sptrsv_ctx *h, Plan &P, const Run &r, int32_t 
     if (!pending && thin_piped(r.nw, lim))
       HIPCHK(h, launch_fill_pending(P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1] - P.h_level_ptr[(size_t)r.l0],
                                     nrhs, ta.rio.x ? ta.rio.perm : nullptr, ta.rio.x ? ta.rio.x : xp, s));
-    HIPCHK(h, launch_thin_run(sc.wg_threads, P.win.p + r.wi, r.nw, nrhs, ta, err, s, nullptr, 0.f,
-                              thin_width(sc, nrhs), lim));
+    HIPCHK(h, launch_thin_run(r.free ? kFreeThreads : sc.wg_threads, P.win.p + r.wi, r.nw, nrhs, ta, err, s, nullptr,
+                              0.f, r.free ? 1 : thin_width(sc, nrhs), lim));
   } else if (r.longr) {
     const int64_t rows = P.h_level_ptr[r.l1] - P.h_level_ptr[r.l0];
     const int32_t avg = (int32_t)std::min<int64_t>((P.h_lv_nnz[(size_t)r.l0] - rows) / std::max<int64_t>(rows, 1),
@@ -778,11 +804,11 @@ sptrsv_status_t solve_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   int slot = prof_begin(h, 0, vec_bytes + (P.has_t ? 12.0 * (double)P.nnz_t_off + 4.0 * P.n : 0.0), s);
   // one right-hand side: the gather marks x for all spread thin runs
   bool pending = false;
-  if (nrhs == 1 && sc.mode != 3)
+  if (nrhs == 1)
     for (const Run &r : P.runs) pending = pending || (r.thin && thin_piped(r.nw, wait_limit(h)));
   STCHK(gather_b(h, P, nrhs, b, ldb, bp, pending ? xp : nullptr, s));
   prof_end(h, slot, s);
-  if (sc.mode == 3) {  // synchronisation-free: one launch for the whole solve (profiled with the wide class)
+  if (sc.mode == 3 && P.runs.empty()) {  // synchronisation-free: one launch for the whole solve (profiled as wide)
     slot = h->prof ? prof_begin(h, 2, run_bytes(P, 0, P.nlev, nrhs), s) : -1;
     HIPCHK(h, launch_syncfree(P.n, nrhs, P.srp.p, P.sci.p, P.sva.p, P.sdg.p, bp, xp, P.sf_ticket.p, err,
                               sc.wide_grid, wait_limit(h), s));
@@ -790,7 +816,6 @@ sptrsv_status_t solve_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   }
   const ThinArgs ta = thin_args(P, bp, xp);
   for (const Run &r : P.runs) {
-    if (sc.mode == 3) break;
     STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, pending, s));
   }
   slot = prof_begin(h, 3, vec_bytes, s);
@@ -855,7 +880,7 @@ sptrsv_status_t solve_rows(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   HIPCHK(h, launch_gather_rows(P.n, nrhs, b, perm, bp, s));
   if (t)
     HIPCHK(h, launch_apply_t(P.n_tpos, nrhs, P.t_lanes, P.tpos.p, perm, P.trp.p, P.tci.p, P.tva.p, b, nrhs, 1, bp, s));
-  if (sc.mode == 3) {
+  if (sc.mode == 3 && P.runs.empty()) {
     HIPCHK(h, launch_syncfree(P.n, nrhs, P.srp.p, P.sci.p, P.sva.p, P.sdg.p, bp, xp, P.sf_ticket.p, h->d_err.p,
                               sc.wide_grid, wait_limit(h), s));
   } else {
@@ -1264,7 +1289,7 @@ sptrsv_status_t sptrsv_level_floor(sptrsv_handle_t h, int which, int32_t nrhs, i
   // are thin runs and per-level wide launches
   const bool direct = (flags & SPTRSV_FLOOR_ROWS) && sc.mode != 3 && sc.mode != 4;
   double ns = launch * ((direct ? 0 : 2) + (P->has_t && P->n_tpos > 0 ? 1 : 0));
-  if (sc.mode == 3) {
+  if (sc.mode == 3 && P->runs.empty()) {
     ns += 2 * launch + (double)P->nlev * c->flag_hop_ns;  // fill of x, the solve; a hop per level
   } else {
     for (const Run &r : P->runs) {

@@ -146,7 +146,11 @@ sptrsv_status_t put_plan(sptrsv_ctx *h, Writer &w, uint32_t base, const Plan &P)
   STCHK(put(h, w, base + 11, P.lv_cost, nl));
   STCHK(put(h, w, base + 12, P.ell_c, n));
   STCHK(put(h, w, base + 13, P.ell_v, 2 * n));
-  w.vec(base + 14, P.h_xh[0]);  // the wider classes' histograms are rebuilt on load
+  // the histogram of the narrowest class, bucket by bucket (loading rebuilds all)
+  std::vector<int32_t> xh = P.h_xh[0];
+  for (size_t i = xh.size(); i-- > 0;)
+    if (i % kExtraBuckets) xh[i] -= xh[i - 1];
+  w.vec(base + 14, xh);
   w.vec(base + 15, P.h_level_ptr);
   w.vec(base + 16, P.h_lv_nnz);
   std::vector<TunedEntry> tuned;

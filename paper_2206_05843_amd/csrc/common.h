@@ -93,6 +93,7 @@ struct Run {
   int32_t cp = 0, fl = 0;
   int32_t lc = 0;          // flow: level_chunk [lc, lc + l1 - l0]: first chunk of each level of the run
   int32_t max_chunks = 0;  // flow: chunks of its widest level
+  bool free = false;       // thin: the synchronisation-free executor's windows (schedule mode 3)
   bool longr = false;      // one wide level of long rows, several right-hand sides: a workgroup per row
 };
 
@@ -147,8 +148,8 @@ struct Plan {
   DArr<int4> ell_c;                    // [n] first four off-diagonal columns per position (-1: none)
   DArr<double2> ell_v;                 // [2n] their values
   // [nlev * kExtraBuckets] per width class of an LDS window's inline records
-  // (2, 6, 10): level-distance histogram of the dependencies that need
-  // overflow records when inside a window
+  // (2, 6, 10): the dependencies of each level's rows that need overflow records
+  // when inside a window, by level distance, summed over the buckets up to each
   std::vector<int32_t> h_xh[kWidths];
   int64_t total_cost = 0;
   double avg_cost = 0.0;
@@ -429,7 +430,7 @@ hipError_t launch_tile_span(int32_t n, const int32_t *iperm, int32_t *first, int
 // k_syncfree.hip): a signalling NaN that arithmetic never produces.
 constexpr unsigned long long kPendingX = 0x7ff4dead5eed5a1dull;
 // Control words of a spread thin run: workgroups done, then a ticket counter per
-// XCD, each in a 128-byte line of its own.
+// lane (at most 8), each in a 128-byte line of its own.
 constexpr int kTicketStride = 32;
 constexpr int kThinCtlWords = kTicketStride * 9;
 int thin_win_bytes();
@@ -439,7 +440,7 @@ hipError_t launch_extra_hist(int32_t n, const int32_t *level_ptr, int32_t nlev, 
 // ng: right-hand sides per workgroup (a divisor of nrhs; 0 = all). tlimit > 0:
 // a run of several windows is spread over workgroups, whose waits end at that
 // wall-clock limit; the x of the run's rows must read as kPendingX before the
-// launch (launch_fill_pending, or launch_gather1 with it). 0: one workgroup per
+// launch (launch_fill_pending, or launch_gather with xp). 0: one workgroup per
 // group of columns solves the windows one after another.
 hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err,
                            hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit);

@@ -56,7 +56,10 @@ struct Ctl {
 // LDS round trip and its instructions. All of a row's x (K inline dependencies)
 // are requested at once and the next level's records behind them; a record has
 // one address; lanes past the level's end repeat its last row instead of being
-// masked; waves without a row of the level go straight to the barrier. K is the
+// masked (with one column: its owner is then in the same wave and writes the same
+// value; with several columns a row's items may lie in two waves, one of which
+// could read the partial sum after the other wrote x over it, so there such
+// lanes write nothing); waves without a row of the level go straight to the barrier. K is the
 // window's width class: 2, 6 or 10 (cut_windows has the rule).
 // Levels' records are requested one level ahead and the level bounds read from
 // registers when every level of the window has at most one item per thread.
@@ -124,6 +127,7 @@ struct Item {
   double w[K > 0 ? K : 1];
   uint32_t ix[K > 0 ? K / 2 + 1 : 1];
   uint32_t at;
+  bool own;  // several columns: not a repeat of another lane's item
 };
 
 template <int K, bool kOne>
@@ -211,8 +215,13 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
       const int32_t lvreg = lv[l0 + lane <= W.NL ? l0 + lane : W.NL];
       int32_t pb = __builtin_amdgcn_readlane(lvreg, 0), pe = __builtin_amdgcn_readlane(lvreg, 1);
       bool on = kOneWave || wave0 < pe - pb;
+      bool wide = !kOneWave && (pe - pb) * gw > 64;
       Item<K> a, b;
-      if (on) load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, a);
+      auto load = [&](Item<K> &it) {
+        load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, it);
+        if constexpr (!kOne) it.own = pb + s0 < pe;
+      };
+      if (on) load(a);
       auto step = [&](int32_t l, Item<K> &cur, Item<K> &nxt) {
         // the level's x first, then the next level's records, which do not
         // depend on it (LDS returns in order)
@@ -221,14 +230,21 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
         pb = pe;
         pe = __builtin_amdgcn_readlane(lvreg, l + 2);
         const bool on_next = kOneWave || wave0 < pe - pb;
-        if (on_next) load_item<K, kOne>(W, min(pb + s0, pe - 1), c8, nxt);
+        if (on_next) load(nxt);
         __builtin_amdgcn_sched_barrier(0);
-        if (on) put(cur.at, solve_item<K, kOne, kOvf>(W, cur, c8, xv));
+        if (on) {
+          const double x = solve_item<K, kOne, kOvf>(W, cur, c8, xv);
+          if (kOne || cur.own) put(cur.at, x);
+        }
         on = on_next;
-        if (kOneWave)
-          wave_lds_barrier();
-        else
+        // between two levels of at most 64 items only the first wave works, and
+        // it waits for nobody
+        const bool wide_next = !kOneWave && (pe - pb) * gw > 64;
+        if (wide || wide_next)
           lds_barrier();  // LDS only: the global x is read only across a window restart
+        else
+          wave_lds_barrier();
+        wide = wide_next;
         stamp(l0 + l);
       };
       int32_t l = 0;
@@ -260,7 +276,7 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
 // and 16-byte image units per thread per copy round.
 template <int WG, bool kOne>
 constexpr int p1_items() {
-  return WG >= 1024 ? 5 : WG >= 512 ? 6 : 8;
+  return WG >= 1024 ? (kOne ? 5 : 4) : WG >= 512 ? 6 : 8;
 }
 template <int WG>
 constexpr int p1_copy() {
@@ -397,55 +413,56 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
       v[(int64_t)it] = a;
     }
     if constexpr (kPoll) {
-      // what is left: an item at a time (a row far into the window seldom has
-      // a dependency just before it), polled past the caches
+      // what is left is polled past the caches, all items of a thread at once:
+      // the next two dependencies of each are requested together, and the
+      // finished ones taken in order
+      constexpr int kP = 2;
+      unsigned spins = 0;
+      for (;;) {
+        bool left[kI], any = false, moved = false;
+        double wv[kI][kP];
+        unsigned long long xv[kI][kP];
 #pragma unroll
-      for (int j = 0; j < kI; ++j) {
-        int32_t e = e0[j];
-        const int32_t ee = e1[j];
-        if (__ballot(e < ee) == 0ull) continue;
-        const int32_t it = base + j * WG + tid;
-        const int32_t c = c0 + (kOne ? 0 : it - (it / gw) * gw);
-        double a = acc[j];
-        double wv[kBatch];
-        int32_t k[kBatch], eq = -1;  // the batch at eq, kept while it is polled
-        unsigned spins = 0;
-        while (__ballot(e < ee) != 0ull) {
-          const int32_t was = e;
-          if (e < ee) {
-            const int32_t cnt = ee - e < kBatch ? ee - e : kBatch;
-            if (e != eq) {
+        for (int j = 0; j < kI; ++j) {
+          left[j] = __ballot(e0[j] < e1[j]) != 0ull;  // uniform over the wave
+          any = any || left[j];
+        }
+        if (!any) break;
 #pragma unroll
-              for (int d = 0; d < kBatch; ++d) {
-                const ExtDep x = ext[e + (d < cnt ? d : 0)];
-                wv[d] = x.w;
-                k[d] = A.rio.x ? x.row : x.col;
-              }
-              eq = e;
-            }
-            double xv[kBatch];
+        for (int j = 0; j < kI; ++j) {
+          if (!left[j]) continue;
+          const int32_t it = base + j * WG + tid;
+          const int32_t c = c0 + (kOne ? 0 : it - (it / gw) * gw);
 #pragma unroll
-            for (int d = 0; d < kBatch; ++d)
-              xv[d] = __longlong_as_double((long long)__hip_atomic_load(
-                  reinterpret_cast<const unsigned long long *>(xs) + (int64_t)k[d] * nr + c, __ATOMIC_RELAXED,
-                  __HIP_MEMORY_SCOPE_AGENT));
-            int32_t done = 0;
-#pragma unroll
-            for (int d = 0; d < kBatch; ++d) {
-              if (d < cnt && done == d && !is_pending(xv[d])) {
-                a = fma(-wv[d], xv[d], a);
-                done = d + 1;
-              }
-            }
-            e += done;
-          }
-          if (__ballot(e != was) == 0ull) __builtin_amdgcn_s_sleep(kPollSleep);
-          if ((++spins & 63u) == 0u && wall_clock64() - t0 > tlimit) {
-            bits |= EB_TIMEOUT;
-            break;
+          for (int d = 0; d < kP; ++d) {
+            const ExtDep x = ext[e0[j] + d < e1[j] ? e0[j] + d : e1[j] > 0 ? e1[j] - 1 : 0];
+            wv[j][d] = x.w;
+            xv[j][d] = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(xs) +
+                                             (int64_t)(A.rio.x ? x.row : x.col) * nr + c,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
-        if (it < nitems) v[(int64_t)it] = a;
+#pragma unroll
+        for (int j = 0; j < kI; ++j) {
+          if (!left[j]) continue;
+          const int32_t left_j = e1[j] - e0[j];
+          int32_t done = 0;
+#pragma unroll
+          for (int d = 0; d < kP; ++d) {
+            if (d < left_j && done == d && xv[j][d] != kPendingX) {
+              acc[j] = fma(-wv[j][d], __longlong_as_double((long long)xv[j][d]), acc[j]);
+              done = d + 1;
+            }
+          }
+          e0[j] += done;
+          moved = moved || done > 0;
+          if (done > 0 && e0[j] == e1[j]) v[(int64_t)(base + j * WG + tid)] = acc[j];
+        }
+        if (__ballot(moved) == 0ull) __builtin_amdgcn_s_sleep(kPollSleep);
+        if ((++spins & 63u) == 0u && wall_clock64() - t0 > tlimit) {
+          bits |= EB_TIMEOUT;
+          break;
+        }
       }
     }
   }
@@ -541,12 +558,13 @@ __global__ __launch_bounds__(WG) void k_thin_run(const int4 *__restrict__ win, i
 // window is its levels and one hand-over, about 0.5 us.
 // Windows are taken in order from a ticket counter, so the ones a window waits
 // for belong to running workgroups and every wait ends. Columns are
-// independent: group g of ng columns is a chain of its own. Workgroups are
-// dealt to the 8 XCDs in turn, and a chain stays on the workgroups of one
-// (blockIdx mod 8): a hand-over within an XCD takes 425 ns, across them 558, and
-// the windows' columns share its L2. Lane l of nlane holds groups l, l + nlane,
-// ...; tp[kTicketStride * (1 + l)] is its ticket counter, tp[0] counts
-// the workgroups that are done, and the last one clears both.
+// independent: group g of ng columns is a chain of its own. Lane l of nlane
+// holds groups l, l + nlane, ... on the workgroups with blockIdx mod 8 = l, those
+// of one XCD (workgroups are dealt to the 8 XCDs in turn), where a hand-over
+// takes 425 ns instead of 558 and the windows share an L2 (64 workgroups on all
+// XCDs took the same time on the power law). tp[kTicketStride * (1 + l)] is
+// lane l's ticket counter, tp[0] counts the workgroups that are done, and the
+// last one clears both.
 // Measured, one right-hand side: the rewritten 2D stencil 1000^2 + chain 1.44 ms a
 // solve against 2.69 with one workgroup (and four that prefetched into its L2),
 // the 300^2 one with its 4,001-row tail 0.74 against 0.89.
@@ -701,13 +719,13 @@ hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, 
                          err, times, ns_per_tick);
     return hipGetLastError();
   }
-  // several windows: spread over kPipeDepth workgroups per lane of XCDs (more
-  // when a lane holds several chains)
+  // several windows: spread over kPipeDepth workgroups per chain on the chain's
+  // XCD; not more than hold windows, nor more than its CUs (a workgroup takes a
+  // CU's LDS)
   const bool pipe = thin_piped(nwin, tlimit);
   const int32_t nlane = groups < kXcd ? groups : kXcd;
   const int32_t chains = (groups + nlane - 1) / nlane;
-  int64_t depth = std::min<int64_t>((int64_t)kPipeDepth * chains, (int64_t)nwin * chains);
-  depth = std::min<int64_t>(depth, 32);  // CUs of an XCD, one workgroup each
+  const int64_t depth = std::min<int64_t>({(int64_t)kPipeDepth * chains, (int64_t)nwin * chains, 32});
 #define THIN(W, ONE, SPLIT)                                                                                       \
   if (pipe)                                                                                                       \
     hipLaunchKernelGGL((k_thin_pipe<W, ONE, SPLIT>), dim3((unsigned)depth * kXcd), dim3(W), kWinBytes, s, win,     \

@@ -112,3 +112,37 @@ def test_spread_windows_repeat(nrhs, thin_cols):
             torch.cuda.synchronize()
             assert torch.equal(x, ref)
     h.check()
+
+
+@pytest.mark.parametrize("draws,window", [(3, 40), (5, 64), (9, 500), (12, 4000)])
+@pytest.mark.parametrize("nrhs", [1, 2, 9])
+def test_sync_free_in_windows_and_row_by_row(draws, window, nrhs):
+    """Mode 3 below and above the line between its two forms gives the bits of
+    the wide-level launches, by columns, by rows and without allocation."""
+    m = gen.window_random(30000, draws, window, draws)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    b = to_dev(gen.rhs(m, nrhs))
+    ref = _solve(h, b, nrhs, mode=1)
+    for grid in (0, 1, 128, 2048):
+        assert torch.equal(_solve(h, b, nrhs, mode=3, wide_grid=grid), ref)
+    h.prepare(sp.ORIGINAL, nrhs)
+    x = torch.empty_like(b)
+    assert torch.equal(h.solve(b, x=x, noalloc=True), ref)
+    if nrhs > 1:
+        assert torch.equal(h.solve_rows(b.t().contiguous()).t(), ref)
+    h.check()
+
+
+@pytest.mark.parametrize("nrhs", [5, 24, 40, 63, 65, 130])
+@pytest.mark.parametrize("wg", [256, 512, 1024])
+def test_columns_of_a_row_in_two_waves(nrhs, wg):
+    """All columns in one workgroup: a row's items straddle waves, and a level's
+    last row is repeated by lanes that must not write it."""
+    m = gen.window_random(3001, nrhs, 24, 3)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    b = to_dev(gen.rhs(m, nrhs))
+    ref = _solve(h, b, nrhs, mode=1)
+    for _ in range(4):
+        assert torch.equal(_solve(h, b, nrhs, mode=2, wg_threads=wg), ref)
