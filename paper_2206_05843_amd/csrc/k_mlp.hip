@@ -2,7 +2,9 @@
 // and Adam kernels (FP32). The network is 20 -> 64 -> 64 -> 1 with ReLU and a
 // sigmoid output; one wave evaluates one sample with lane j holding hidden unit
 // j of both layers, so every reduction is a fixed butterfly or a fixed loop
-// (deterministic). Parameters are staged in LDS with padded rows.
+// (deterministic). A lane keeps its unit's weights (and, for the backward pass,
+// its column of W2 and its gradient sums) in registers; only a sample's
+// activations go through LDS, read back four at a time by all lanes at once.
 #include "common.h"
 
 namespace {
@@ -13,7 +15,7 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + HID * NIN, OFF_W2 = OFF_B1 + HID, OF
 static_assert(OFF_B3 + 1 == NPAR, "parameter layout");
 constexpr int W1S = NIN + 1, W2S = HID + 1;  // padded LDS row strides
 constexpr int kWavesPerBlock = 4;
-constexpr int kBwdBlocks = 64;
+constexpr int kBlocks = 256;  // one workgroup per CU: a wave keeps some 270 registers
 
 struct SParams {
   float w1[HID * W1S];
@@ -45,31 +47,67 @@ __device__ __forceinline__ void wsync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Forward pass of one sample by one wave. Leaves the normalised features in
-// sf, h1 in sh; returns (a1, a2, h2) of this lane's unit and z.
+// One wave's unit of both layers in registers.
+struct Unit {
+  float w1[NIN], w2[HID], b1, b2, w3, b3;
+};
+
+__device__ __forceinline__ Unit load_unit(const SParams &sp, int j) {
+  Unit u;
+#pragma unroll
+  for (int k = 0; k < NIN; ++k) u.w1[k] = sp.w1[j * W1S + k];
+#pragma unroll
+  for (int i = 0; i < HID; ++i) u.w2[i] = sp.w2[j * W2S + i];
+  u.b1 = sp.b1[j], u.b2 = sp.b2[j], u.w3 = sp.w3[j], u.b3 = sp.b3;
+  return u;
+}
+
+// A sample's normalised features and its 64 activations of one layer, per wave.
+struct __align__(16) Acts {
+  float f[NIN], h[HID], d[HID];
+};
+
+// acc + sum_i w[i] x[i] in order, x read four at a time.
+template <int N>
+__device__ __forceinline__ float dot_lds(float acc, const float (&w)[N], const float *x) {
+#pragma unroll
+  for (int i = 0; i < N; i += 4) {
+    const float4 v = *reinterpret_cast<const float4 *>(x + i);
+    acc += w[i] * v.x;
+    acc += w[i + 1] * v.y;
+    acc += w[i + 2] * v.z;
+    acc += w[i + 3] * v.w;
+  }
+  return acc;
+}
+
+// Forward pass of one sample by one wave (feat: lane j < 20 holds feature j).
+// Leaves the normalised features in s.f, h1 in s.h; returns (a1, a2, h2) of
+// this lane's unit and z.
 struct Fwd {
   float a1, a2, h2, z;
 };
 
-__device__ __forceinline__ Fwd forward_one(const SParams &sp, const float *__restrict__ feat,
-                                           const float *__restrict__ norm, int64_t b, float *sf, float *sh) {
+__device__ __forceinline__ Fwd forward_one(const Unit &u, float feat, Acts &s) {
   const int j = threadIdx.x & 63;
-  if (j < NIN) {
-    float f = feat[b * NIN + j];
-    if (norm) f = (f - norm[j]) * norm[NIN + j];
-    sf[j] = f;
-  }
+  if (j < NIN) s.f[j] = feat;
   wsync();
-  float a1 = sp.b1[j];
-  for (int k = 0; k < NIN; ++k) a1 += sp.w1[j * W1S + k] * sf[k];
-  const float h1 = fmaxf(a1, 0.f);
-  sh[j] = h1;
+  const float a1 = dot_lds(u.b1, u.w1, s.f);
+  s.h[j] = fmaxf(a1, 0.f);
   wsync();
-  float a2 = sp.b2[j];
-  for (int i = 0; i < HID; ++i) a2 += sp.w2[j * W2S + i] * sh[i];
+  const float a2 = dot_lds(u.b2, u.w2, s.h);
   const float h2 = fmaxf(a2, 0.f);
-  const float z = wave_sum(sp.w3[j] * h2) + sp.b3;
+  const float z = wave_sum(u.w3 * h2) + u.b3;
   return Fwd{a1, a2, h2, z};
+}
+
+// Normalised feature j of sample b (0 for lanes past the features).
+__device__ __forceinline__ float feature(const float *__restrict__ feat, const float *__restrict__ norm, int64_t b,
+                                         int j) {
+  if (j >= NIN) return 0.f;
+  float f = feat[b * NIN + j];
+  if (norm) f = (f - norm[j]) * norm[NIN + j];
+  return f;
 }
 
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_mlp_forward(const float *__restrict__ P,
@@ -77,77 +115,147 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_mlp_forward(const float
                                                                        const float *__restrict__ norm, int32_t B,
                                                                        float *prob) {
   __shared__ SParams sp;
-  __shared__ float sf[kWavesPerBlock][NIN], sh[kWavesPerBlock][HID];
+  __shared__ Acts acts[kWavesPerBlock];
   load_params(sp, P);
   __syncthreads();
   const int w = threadIdx.x >> 6, j = threadIdx.x & 63;
-  for (int64_t b = (int64_t)blockIdx.x * kWavesPerBlock + w; b < B; b += (int64_t)gridDim.x * kWavesPerBlock) {
-    const Fwd f = forward_one(sp, feat, norm, b, sf[w], sh[w]);
-    if (j == 0) prob[b] = 1.f / (1.f + expf(-f.z));
+  const Unit u = load_unit(sp, j);
+  const int64_t step = (int64_t)gridDim.x * kWavesPerBlock;
+  int64_t b = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  float f = b < B ? feature(feat, norm, b, j) : 0.f;
+  for (; b < B; b += step) {
+    const float cur = f;
+    f = b + step < B ? feature(feat, norm, b + step, j) : 0.f;
+    const Fwd r = forward_one(u, cur, acts[w]);
+    if (j == 0) prob[b] = 1.f / (1.f + expf(-r.z));
     wsync();
   }
 }
 
-// Per-wave partial gradients of sum_b w_b BCE_b / B, written to part[wave][*].
-__global__ __launch_bounds__(64 * kWavesPerBlock) void k_mlp_backward(
+// Per-workgroup partial gradients of sum_b w_b BCE_b / B, written to
+// part[workgroup][*]: every wave sums its samples in registers, then the waves
+// are added in order. Bound by the 230 FMAs a sample costs each lane; with one
+// wave per SIMD and the waves' sums added in LDS, 4,096 samples take 23 us (44 with
+// 64 workgroups whose lanes read every weight from LDS for each sample).
+__global__ __launch_bounds__(64 * kWavesPerBlock, 1) void k_mlp_backward(
     const float *__restrict__ P, const float *__restrict__ feat, const float *__restrict__ norm,
     const float *__restrict__ label, const float *__restrict__ weight, int32_t B, float *part, float *part_loss) {
   __shared__ SParams sp;
-  __shared__ float sf[kWavesPerBlock][NIN], sh[kWavesPerBlock][HID], sd[kWavesPerBlock][HID];
+  __shared__ Acts acts[kWavesPerBlock];
+  __shared__ float s_loss;
   load_params(sp, P);
   __syncthreads();
   const int w = threadIdx.x >> 6, j = threadIdx.x & 63;
+  const Unit u = load_unit(sp, j);
+  float w2c[HID];  // column j of W2
+#pragma unroll
+  for (int i = 0; i < HID; ++i) w2c[i] = sp.w2[i * W2S + j];
+  Acts &s = acts[w];
   float gw1[NIN], gw2[HID];
+#pragma unroll
   for (int k = 0; k < NIN; ++k) gw1[k] = 0.f;
+#pragma unroll
   for (int i = 0; i < HID; ++i) gw2[i] = 0.f;
   float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
   const float invB = 1.f / (float)B;
-  for (int64_t b = (int64_t)blockIdx.x * kWavesPerBlock + w; b < B; b += (int64_t)gridDim.x * kWavesPerBlock) {
-    const Fwd f = forward_one(sp, feat, norm, b, sf[w], sh[w]);
+  const int64_t step = (int64_t)gridDim.x * kWavesPerBlock;
+  int64_t b = (int64_t)blockIdx.x * kWavesPerBlock + w;
+  float f = b < B ? feature(feat, norm, b, j) : 0.f;
+  for (; b < B; b += step) {
+    const float cur = f;
     const float y = label[b], wt = weight ? weight[b] : 1.f;
-    const float p = 1.f / (1.f + expf(-f.z));
+    f = b + step < B ? feature(feat, norm, b + step, j) : 0.f;
+    const Fwd r = forward_one(u, cur, s);
+    const float p = 1.f / (1.f + expf(-r.z));
     const float dz = wt * (p - y) * invB;
     if (j == 0) {
-      loss += wt * (fmaxf(f.z, 0.f) - f.z * y + log1pf(expf(-fabsf(f.z))));
+      loss += wt * (fmaxf(r.z, 0.f) - r.z * y + log1pf(expf(-fabsf(r.z))));
       gb3 += dz;
     }
-    gw3 += dz * f.h2;
-    const float da2 = f.a2 > 0.f ? dz * sp.w3[j] : 0.f;
+    gw3 += dz * r.h2;
+    const float da2 = r.a2 > 0.f ? dz * u.w3 : 0.f;
     gb2 += da2;
-    for (int i = 0; i < HID; ++i) gw2[i] += da2 * sh[w][i];
-    sd[w][j] = da2;
+    s.d[j] = da2;
+#pragma unroll
+    for (int i = 0; i < HID; i += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(s.h + i);
+      gw2[i] += da2 * v.x;
+      gw2[i + 1] += da2 * v.y;
+      gw2[i + 2] += da2 * v.z;
+      gw2[i + 3] += da2 * v.w;
+    }
     wsync();
-    float dh1 = 0.f;
-    for (int i = 0; i < HID; ++i) dh1 += sd[w][i] * sp.w2[i * W2S + j];
-    const float da1 = f.a1 > 0.f ? dh1 : 0.f;
+    const float dh1 = dot_lds(0.f, w2c, s.d);
+    const float da1 = r.a1 > 0.f ? dh1 : 0.f;
     gb1 += da1;
-    for (int k = 0; k < NIN; ++k) gw1[k] += da1 * sf[w][k];
+#pragma unroll
+    for (int k = 0; k < NIN; k += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(s.f + k);
+      gw1[k] += da1 * v.x;
+      gw1[k + 1] += da1 * v.y;
+      gw1[k + 2] += da1 * v.z;
+      gw1[k + 3] += da1 * v.w;
+    }
     wsync();
   }
-  float *o = part + ((int64_t)blockIdx.x * kWavesPerBlock + w) * NPAR;
-  for (int k = 0; k < NIN; ++k) o[OFF_W1 + j * NIN + k] = gw1[k];
-  for (int i = 0; i < HID; ++i) o[OFF_W2 + j * HID + i] = gw2[i];
-  o[OFF_B1 + j] = gb1;
-  o[OFF_B2 + j] = gb2;
-  o[OFF_W3 + j] = gw3;
-  if (j == 0) {
-    o[OFF_B3] = gb3;
-    part_loss[(int64_t)blockIdx.x * kWavesPerBlock + w] = loss * invB;
+  // the parameters are in registers: their place in LDS takes the sums
+  for (int q = 0; q < kWavesPerBlock; ++q) {
+    __syncthreads();
+    if (w != q) continue;
+    auto add = [&](float &to, float v) { to = q == 0 ? v : to + v; };
+#pragma unroll
+    for (int k = 0; k < NIN; ++k) add(sp.w1[j * W1S + k], gw1[k]);
+#pragma unroll
+    for (int i = 0; i < HID; ++i) add(sp.w2[j * W2S + i], gw2[i]);
+    add(sp.b1[j], gb1);
+    add(sp.b2[j], gb2);
+    add(sp.w3[j], gw3);
+    if (j == 0) {
+      add(sp.b3, gb3);
+      add(s_loss, loss);
+    }
+  }
+  __syncthreads();
+  float *o = part + (int64_t)blockIdx.x * NPAR;
+  for (int i = threadIdx.x; i < HID * NIN; i += blockDim.x) o[OFF_W1 + i] = sp.w1[(i / NIN) * W1S + i % NIN];
+  for (int i = threadIdx.x; i < HID * HID; i += blockDim.x) o[OFF_W2 + i] = sp.w2[(i / HID) * W2S + i % HID];
+  if (threadIdx.x < HID) {
+    o[OFF_B1 + threadIdx.x] = sp.b1[threadIdx.x];
+    o[OFF_B2 + threadIdx.x] = sp.b2[threadIdx.x];
+    o[OFF_W3 + threadIdx.x] = sp.w3[threadIdx.x];
+  }
+  if (threadIdx.x == 0) {
+    o[OFF_B3] = sp.b3;
+    part_loss[blockIdx.x] = s_loss * invB;
   }
 }
 
-// grad[i] = sum over waves of part[wave][i], in wave order.
-__global__ void k_mlp_reduce(const float *__restrict__ part, int32_t nparts, const float *__restrict__ part_loss,
-                             float *grad, float *loss) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= NPAR; i += gridDim.x * blockDim.x) {
-    float s = 0.f;
-    if (i < NPAR) {
-      for (int q = 0; q < nparts; ++q) s += part[(int64_t)q * NPAR + i];
+// grad[i] = sum over workgroups of part[q][i]: kRedRows threads of a column sum
+// every kRedRows-th part, then their sums are added in order. A workgroup takes
+// 32 columns (a 128-byte line a part), so the 5,570 sums of 256 parts are read
+// by 175 workgroups at once (4 us; one thread per column read them one by one, 63 us).
+constexpr int kRedCols = 32, kRedRows = 16;
+__global__ __launch_bounds__(kRedCols * kRedRows) void k_mlp_reduce(const float *__restrict__ part, int32_t nparts,
+                                                                     const float *__restrict__ part_loss, float *grad,
+                                                                     float *loss) {
+  __shared__ float sum[kRedRows][kRedCols];
+  const int c = threadIdx.x % kRedCols, r = threadIdx.x / kRedCols;
+  const int i = blockIdx.x * kRedCols + c;
+  float s = 0.f;
+  if (i <= NPAR) {
+    const float *from = i < NPAR ? part + i : part_loss;
+    const int64_t stride = i < NPAR ? NPAR : 1;
+#pragma unroll 8
+    for (int q = r; q < nparts; q += kRedRows) s += from[(int64_t)q * stride];
+  }
+  sum[r][c] = s;
+  __syncthreads();
+  if (r == 0 && i <= NPAR) {
+    for (int q = 1; q < kRedRows; ++q) s += sum[q][c];
+    if (i < NPAR)
       grad[i] = s;
-    } else {
-      for (int q = 0; q < nparts; ++q) s += part_loss[q];
+    else
       *loss = s;
-    }
   }
 }
 
@@ -213,13 +321,12 @@ __global__ void k_feat_finalize(int32_t nlev, const int64_t *__restrict__ rows, 
 
 }  // namespace
 
-int mlp_backward_parts() { return kBwdBlocks * kWavesPerBlock; }
+int mlp_backward_parts() { return kBlocks; }
 
 hipError_t launch_mlp_forward(const float *P, const float *feat, const float *norm, int32_t B, float *prob,
                               hipStream_t s) {
   if (B <= 0) return hipSuccess;
-  int g = (B + kWavesPerBlock - 1) / kWavesPerBlock;
-  g = g > 1024 ? 1024 : g;
+  const int g = grid_for(B, kWavesPerBlock, 2 * kBlocks);
   hipLaunchKernelGGL(k_mlp_forward, dim3(g), dim3(64 * kWavesPerBlock), 0, s, P, feat, norm, B, prob);
   return hipGetLastError();
 }
@@ -227,11 +334,12 @@ hipError_t launch_mlp_forward(const float *P, const float *feat, const float *no
 hipError_t launch_mlp_backward(const float *P, const float *feat, const float *norm, const float *label,
                                const float *weight, int32_t B, float *part, float *part_loss, float *grad,
                                float *loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_backward, dim3(kBwdBlocks), dim3(64 * kWavesPerBlock), 0, s, P, feat, norm, label, weight,
-                     B, part, part_loss);
+  const int g = grid_for(B, kWavesPerBlock, kBlocks);
+  hipLaunchKernelGGL(k_mlp_backward, dim3(g), dim3(64 * kWavesPerBlock), 0, s, P, feat, norm, label, weight, B, part,
+                     part_loss);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + 256) / 256), dim3(256), 0, s, part, kBwdBlocks * kWavesPerBlock,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((NPAR + kRedCols) / kRedCols), dim3(kRedCols * kRedRows), 0, s, part, g,
                      part_loss, grad, loss);
   return hipGetLastError();
 }
