@@ -300,7 +300,7 @@ typedef struct {
   int32_t thin_cols;      /* right-hand sides per thin-run workgroup: 0 = all; c, a divisor of nrhs smaller than
                              it = nrhs / c workgroups each solve c columns of every thin run (columns are
                              independent), with LDS windows cut for c columns; otherwise all. The batched
-                             launch (SPTRSV_BATCH) solves every column of a matrix in one workgroup */
+                             launch (SPTRSV_BATCH) takes its columns in groups of four by itself */
 } sptrsv_schedule_t;
 sptrsv_status_t sptrsv_set_schedule(sptrsv_handle_t h, int which, const sptrsv_schedule_t *sched);
 sptrsv_status_t sptrsv_get_schedule(sptrsv_handle_t h, int which, int32_t nrhs, sptrsv_schedule_t *sched);
@@ -410,8 +410,8 @@ sptrsv_status_t sptrsv_residual(sptrsv_handle_t h, int32_t nrhs, const double *d
  * column indices local. Each matrix is level-scheduled as in sptrsv_analyze.
  * batch_solve solves all matrices in one persistent launch; matrix i's b and x
  * are n_i x nrhs column-major at offset nrhs*h_row_off[i], ld = n_i. ASYNC.
- * A matrix with a level too wide for one workgroup's LDS window at this nrhs
- * (about 1,000 rows at 16 right-hand sides) is taken out of the persistent
+ * A matrix with a level too wide for one workgroup's LDS window (about 3,300
+ * rows with four columns of it) is taken out of the persistent
  * launch and solved level by level (thin runs, one device-wide launch per
  * wide level) in the same call, with the same result.
  * ------------------------------------------------------------------------- */

@@ -145,15 +145,17 @@ static int extra_bucket(int32_t d) {
 // about 60 ns on one wave and 160 on several, 5 more per inline dependency,
 // and each round of four overflow records beyond the inline ones two dependent
 // LDS round trips, about 90 ns.
-int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, std::vector<int4> &out) {
-  const int64_t cap = thin_win_bytes();
+int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, int64_t cap, bool one_class,
+                    std::vector<int4> &out) {
   const size_t first = out.size();
+  int keep = -1;
   int32_t ws = l0;
   while (ws < l1) {
     int32_t end = ws, kc = kWidths;
     int64_t ents = 0, maxit = 0;
     double best = 0.0;
     for (int k = 0; k < kWidths; ++k) {
+      if (keep >= 0 && k != keep) continue;
       int64_t rows = 0, en = 0, mi = 0;
       double ns = 1000.0;
       int32_t l = ws;
@@ -180,6 +182,7 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
         maxit = mi;
       }
     }
+    if (one_class && keep < 0) keep = kc < kWidths ? kc : -1;
     if (end <= ws + 1) {  // a level alone: no dependency inside the window
       end = ws + 1;
       kc = kWidths;
@@ -476,7 +479,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   for (Run &r : P.runs) {
     if (!r.thin) continue;
     r.wi = (int32_t)P.h_win.size();
-    r.nw = cut_windows(P, r.l0, r.l1, gw, r.free ? kFreeThreads : sc.wg_threads, P.h_win);
+    r.nw = cut_windows(P, r.l0, r.l1, gw, r.free ? kFreeThreads : sc.wg_threads, thin_win_bytes(), false, P.h_win);
   }
   P.runs_nrhs = -1;  // until the images are built
   STCHK(build_images(h, P, gw, s));
@@ -669,7 +672,8 @@ static void prof_end(sptrsv_ctx *h, int slot, hipStream_t s) {
 
 ThinArgs thin_args(const Plan &P) { return thin_args(P, P.bp.p, P.xp.p); }
 ThinArgs thin_args(const Plan &P, double *bp, double *xp) {
-  return ThinArgs{P.level_ptr.p, P.img.p, P.ext_ptr.p, P.ext.p, bp, xp, P.tp.p};
+  return ThinArgs{P.level_ptr.p, P.img.p, P.ext_ptr.p, P.ext.p, bp, xp, P.tp.p, RowsIO{},
+                  thin_win_bytes() + thin_ctl_bytes()};
 }
 
 // The level-distance histograms of the dependencies that need overflow records
@@ -873,7 +877,7 @@ sptrsv_status_t solve_rows(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
       HIPCHK(h, launch_apply_t(P.n_tpos, nrhs, P.t_lanes, P.tpos.p, perm, P.trp.p, P.tci.p, P.tva.p, b, nrhs, 1, bp,
                                s));
     ThinArgs ta = thin_args(P, bp, xp);
-    ta.rio = RowsIO{b, x, perm, P.has_t ? P.tflag.p : nullptr, P.ell_r.p, P.sci_r.p};
+    ta.rio = RowsIO{b, x, perm, P.has_t ? P.tflag.p : nullptr, P.ell_r.p, P.sci_r.p, nrhs, 1};
     for (const Run &r : P.runs) STCHK(launch_run(h, P, r, nrhs, ta, bp, xp, false, s));
     return SPTRSV_OK;
   }

@@ -64,23 +64,47 @@ int bit_width64(int64_t v) {
   return b;
 }
 
+// Columns per group of the persistent launch: 4, so that most levels (a few rows
+// wide) fit one wave, else all of 1 to 3. Groups may overlap: 13 columns are
+// four groups of 4. 512 matrices x 16 columns took 3.91 ms in groups of 4 (256
+// threads), 4.15 in groups of 8 (512 threads), 6.3 in groups of 2.
+int32_t batch_cols(int32_t nrhs) { return nrhs >= 4 ? 4 : nrhs; }
+
 // Per-matrix LDS windows for nrhs (cached). A matrix whose levels all fit an
 // LDS window goes in the persistent queue; a matrix with a level too wide for
 // one is solved level by level instead (its narrow levels in thin runs, its
 // wide ones one device-wide launch each, as a single plan's mode-0 schedule).
+// Windows are as large as lets several workgroups share a CU (batch_lds), or as
+// the widest level that fits a whole CU's LDS needs.
 sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream_t s) {
   if (h->b_win_nrhs == nrhs && h->b_win_wg == wg) return SPTRSV_OK;
   Plan &P = h->bat;
+  const int32_t nc = batch_cols(nrhs);
   P.h_win.clear();
   h->b_h_mwin.assign((size_t)h->b_nmat + 1, 0);
   h->b_wide.clear();
   std::vector<char> fits((size_t)h->b_nmat, 1);
+  std::vector<uint8_t> flag((size_t)h->b_nmat, 0);
+  int64_t cap = batch_lds(wg) - thin_ctl_bytes();
   for (int32_t m = 0; m < h->b_nmat; ++m) {
-    const int32_t l0 = (int32_t)h->b_lvl_off[(size_t)m], l1 = (int32_t)h->b_lvl_off[(size_t)m + 1];
-    for (int32_t l = l0; l < l1 && fits[(size_t)m]; ++l)
-      if (!level_fits_window(P, l, nrhs)) fits[(size_t)m] = 0;
+    int64_t rows = 0;
+    for (int64_t l = h->b_lvl_off[(size_t)m]; l < h->b_lvl_off[(size_t)m + 1]; ++l)
+      rows = std::max<int64_t>(rows, P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l]);
+    const int64_t need = thin_window_bytes(rows, 0, 1, nc, kWidths);
+    if (need > thin_win_bytes()) {
+      fits[(size_t)m] = 0;
+      flag[(size_t)m] = 1;
+    } else {
+      cap = std::max(cap, need);
+    }
+  }
+  h->b_ncol = nc;
+  h->b_lds = (int32_t)cap + thin_ctl_bytes();
+  for (int32_t m = 0; m < h->b_nmat; ++m) {
     h->b_h_mwin[(size_t)m] = (int32_t)P.h_win.size();
-    if (fits[(size_t)m]) cut_windows(P, l0, l1, nrhs, wg, P.h_win);
+    if (fits[(size_t)m])
+      cut_windows(P, (int32_t)h->b_lvl_off[(size_t)m], (int32_t)h->b_lvl_off[(size_t)m + 1], nc, wg, cap, true,
+                  P.h_win);
   }
   h->b_h_mwin[(size_t)h->b_nmat] = (int32_t)P.h_win.size();
   for (int32_t m = 0; m < h->b_nmat; ++m) {
@@ -89,7 +113,7 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
     bw.m = m;
     const int32_t l0 = (int32_t)h->b_lvl_off[(size_t)m], l1 = (int32_t)h->b_lvl_off[(size_t)m + 1];
     for (int32_t l = l0; l < l1; ++l) {
-      const bool thin = level_fits_window(P, l, nrhs);
+      const bool thin = level_fits_window(P, l, nc);
       if (!bw.runs.empty() && thin && bw.runs.back().thin && bw.runs.back().l1 == l)
         bw.runs.back().l1 = l + 1;
       else
@@ -98,7 +122,7 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
     for (Run &r : bw.runs)
       if (r.thin) {
         r.wi = (int32_t)P.h_win.size();
-        r.nw = cut_windows(P, r.l0, r.l1, nrhs, wg, P.h_win);
+        r.nw = cut_windows(P, r.l0, r.l1, nc, wg, thin_win_bytes(), true, P.h_win);
       }
     h->b_wide.push_back(std::move(bw));
   }
@@ -109,8 +133,10 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
   h->b_nq = (int32_t)q.size();
   HIPCHK(h, h->b_order.reserve(std::max<size_t>(q.size(), 1)));
   if (!q.empty()) HIPCHK(h, hipMemcpy(h->b_order.p, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice));
+  HIPCHK(h, h->b_wide_flag.reserve((size_t)h->b_nmat));
+  HIPCHK(h, hipMemcpy(h->b_wide_flag.p, flag.data(), (size_t)h->b_nmat, hipMemcpyHostToDevice));
   h->b_win_nrhs = -1;  // until the images are built
-  STCHK(build_images(h, P, nrhs, s));
+  STCHK(build_images(h, P, nc, s));
   HIPCHK(h, h->b_mwin.alloc((size_t)h->b_nmat + 1));
   HIPCHK(h, hipMemcpy(h->b_mwin.p, h->b_h_mwin.data(), sizeof(int32_t) * ((size_t)h->b_nmat + 1),
                       hipMemcpyHostToDevice));
@@ -129,8 +155,8 @@ sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipSt
         const int32_t p0 = P.h_level_ptr[(size_t)r.l0];
         if (thin_piped(r.nw, wait_limit(h)))
           HIPCHK(h, launch_fill_pending(p0, P.h_level_ptr[(size_t)r.l1] - p0, nrhs, nullptr, P.xp.p, s));
-        HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f, 0,
-                                  wait_limit(h)));
+        HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
+                                  h->b_ncol, wait_limit(h)));
       } else
         HIPCHK(h, launch_wide_level(d.wide_threads, 1, P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1], nrhs,
                                     P.srp.p, P.sci.p, P.sva.p, P.sdg.p, P.ell_c.p, P.ell_v.p, P.bp.p, P.xp.p,
@@ -322,14 +348,22 @@ sptrsv_status_t sptrsv_batch_solve(sptrsv_handle_t h, int32_t nrhs, const double
   STCHK(ensure_work(h, P, nrhs));
   const int32_t wg = effective_sched(P, nrhs).wg_threads;
   STCHK(batch_windows(h, nrhs, wg, s));
-  HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, P.bp.p, s));
   if (h->b_nq > 0) {
-    const int32_t grid = std::min(h->b_nq, batch_resident_blocks(wg));
-    HIPCHK(h, launch_batch_run(wg, h->b_nq, grid, h->b_order.p, h->b_mwin.p, P.win.p, nrhs, thin_args(P), h->b_q.p,
-                               h->d_err.p, s));
+    const int32_t tasks = h->b_nq * ((nrhs + h->b_ncol - 1) / h->b_ncol);
+    const int32_t grid = std::min(tasks, batch_resident_blocks(wg, h->b_lds));
+    ThinArgs ta = thin_args(P);
+    ta.rio = RowsIO{d_b_cat, d_x_cat, P.perm.p, nullptr, nullptr, nullptr, 1, 1};
+    ta.lds = h->b_lds;
+    HIPCHK(h, launch_batch_run(wg, h->b_nq, grid, h->b_order.p, h->b_mwin.p, P.win.p, nrhs, h->b_ncol,
+                               h->b_row_off_d.p, ta, h->b_q.p, h->d_err.p, s));
   }
-  STCHK(batch_wide_solves(h, nrhs, wg, s));
-  HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, d_x_cat, s));
+  if (!h->b_wide.empty()) {
+    HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p,
+                                  h->b_wide_flag.p, P.bp.p, s));
+    STCHK(batch_wide_solves(h, nrhs, wg, s));
+    HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p,
+                                   h->b_wide_flag.p, d_x_cat, s));
+  }
   return SPTRSV_OK;
 }
 
@@ -342,16 +376,18 @@ sptrsv_status_t sptrsv_batch_solve_looped(sptrsv_handle_t h, int32_t nrhs, const
   STCHK(ensure_work(h, P, nrhs));
   const int32_t wg = effective_sched(P, nrhs).wg_threads;
   STCHK(batch_windows(h, nrhs, wg, s));
-  HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, P.bp.p, s));
+  HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, nullptr, P.bp.p,
+                                s));
   HIPCHK(h, launch_fill_pending(0, P.n, nrhs, nullptr, P.xp.p, s));
   for (int32_t m = 0; m < h->b_nmat; ++m) {
     const int32_t wi = h->b_h_mwin[(size_t)m], nw = h->b_h_mwin[(size_t)m + 1] - wi - 1;
     if (nw >= 1)
-      HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f, 0,
-                                wait_limit(h)));
+      HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
+                                h->b_ncol, wait_limit(h)));
   }
   STCHK(batch_wide_solves(h, nrhs, wg, s));
-  HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, d_x_cat, s));
+  HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, nullptr, d_x_cat,
+                                 s));
   return SPTRSV_OK;
 }
 

@@ -194,6 +194,10 @@ sptrsv_status_t autotune(sptrsv_ctx *h, int which, int32_t nrhs, bool rows, hipS
   if (st != SPTRSV_OK) return st;
   HIPCHK(h, hipStreamSynchronize(s));
   P->tuned[nrhs] = best_s;
+  if (batch) {  // leaves the windows of the schedule that was kept, not of the last one tried
+    STCHK(run());
+    HIPCHK(h, hipStreamSynchronize(s));
+  }
   info.best_ms = best;
   h->tune_info = info;
   if (best_ms) *best_ms = best;

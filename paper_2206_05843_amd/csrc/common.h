@@ -245,6 +245,8 @@ struct sptrsv_ctx {
   std::vector<int32_t> b_h_order;      // longest-processing-time order of all matrices
   int32_t b_nq = 0;                    // matrices in the persistent queue (b_order) for the cached nrhs
   std::vector<BatchWide> b_wide;       // the others
+  DArr<uint8_t> b_wide_flag;           // per matrix: among b_wide
+  int32_t b_ncol = 1, b_lds = 0;       // columns per group and LDS bytes of the persistent launch
   int32_t b_win_nrhs = -1, b_win_wg = -1;
   std::vector<Graph> graphs;
   // live profile of solve launches
@@ -376,6 +378,9 @@ struct RowsIO {
   const uint8_t *tflag;
   const int4 *ell_r;
   const int32_t *sci_r;  // the level-ordered copy's columns as caller rows
+  // thin runs address entry (row, c) of b and x at row * rs + c * cs: nrhs and 1
+  // by rows; 1 and n_i for a batched matrix (columns of its own length)
+  int64_t rs, cs;
 };
 
 // Device arrays a thin run reads: level bounds, the static window images and
@@ -389,6 +394,7 @@ struct ThinArgs {
   double *xp;
   unsigned *tp;  // ticket words of a spread run
   RowsIO rio;
+  int32_t lds;   // dynamic LDS of the launch in bytes
 };
 
 // Launchers (k_solve.hip) ------------------------------------------------------
@@ -542,20 +548,30 @@ hipError_t launch_img_fill(int32_t n, const int32_t *level_ptr, int32_t nlev, co
                            const long long *ovf_ex, const int32_t *ext_ptr, uint4 *img, ExtDep *ext,
                            const int32_t *perm, int32_t ncol, hipStream_t s);
 // Batched launchers (k_solve.hip) -------------------------------------------------
+// Tasks (matrix, group of ncol columns), matrices in queue order; b and x are the
+// caller's concatenated vectors (A.rio.b, A.rio.x), lds the launch's LDS bytes.
 hipError_t launch_batch_run(int wg, int32_t nmat, int32_t grid, const int32_t *order, const int32_t *mwin,
-                            const int4 *win, int32_t nrhs, const ThinArgs &a, unsigned *q, int *err, hipStream_t s);
+                            const int4 *win, int32_t nrhs, int32_t ncol, const int64_t *row_off, const ThinArgs &a,
+                            unsigned *q, int *err, hipStream_t s);
+// only (may be null): the matrices to copy, by flag
 hipError_t launch_batch_gather(int64_t total, int32_t nrhs, const double *b, const int32_t *mat_of_row,
-                               const int64_t *row_off, const int32_t *iperm, double *bp, hipStream_t s);
+                               const int64_t *row_off, const int32_t *iperm, const uint8_t *only, double *bp,
+                               hipStream_t s);
 hipError_t launch_batch_scatter(int64_t total, int32_t nrhs, const double *xp, const int32_t *mat_of_row,
-                                const int64_t *row_off, const int32_t *iperm, double *x, hipStream_t s);
-int batch_resident_blocks(int wg);
+                                const int64_t *row_off, const int32_t *iperm, const uint8_t *only, double *x,
+                                hipStream_t s);
+int batch_resident_blocks(int wg, int lds);
+int batch_lds(int wg);  // dynamic LDS with which as many workgroups fit a CU as their registers allow
+int thin_ctl_bytes();
 sptrsv_schedule_t effective_sched(const Plan &P, int32_t nrhs);
 Plan *plan_of(sptrsv_ctx *h, int which);
 Plan *sched_plan_of(sptrsv_ctx *h, int which);
 sptrsv_schedule_t default_schedule();
 // Schedule helpers (api.hip) -----------------------------------------------------
 bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs);
-int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, std::vector<int4> &out);
+// cap: LDS bytes of a window; one_class: keep the first window's width class
+int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, int64_t cap, bool one_class,
+                    std::vector<int4> &out);
 sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s);
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s);
 // ncol: right-hand sides per window (slots are premultiplied by it)

@@ -246,7 +246,7 @@ __global__ void k_residual(int32_t n, int32_t nrhs, const int32_t *__restrict__ 
 // right-hand sides at a time (contiguous at the row's position).
 __global__ void k_batch_gather(int64_t total, int32_t nrhs, const double *__restrict__ b,
                                const int32_t *__restrict__ mat_of_row, const int64_t *__restrict__ row_off,
-                               const int32_t *__restrict__ iperm, double *bp) {
+                               const int32_t *__restrict__ iperm, const uint8_t *__restrict__ only, double *bp) {
   __shared__ double tile[64][33];
   const int64_t r0 = (int64_t)blockIdx.x * 64;
   for (int32_t c0 = 0; c0 < nrhs; c0 += 32) {
@@ -254,7 +254,7 @@ __global__ void k_batch_gather(int64_t total, int32_t nrhs, const double *__rest
     for (int idx = threadIdx.x; idx < 64 * nc; idx += blockDim.x) {
       const int c = idx / 64, rr = idx % 64;
       const int64_t r = r0 + rr;
-      if (r < total) {
+      if (r < total && (!only || only[mat_of_row[r]])) {
         const int32_t m = mat_of_row[r];
         const int64_t ro = row_off[m], nm = row_off[m + 1] - ro;
         tile[rr][c] = b[nrhs * ro + (int64_t)(c0 + c) * nm + (r - ro)];
@@ -264,7 +264,7 @@ __global__ void k_batch_gather(int64_t total, int32_t nrhs, const double *__rest
     for (int idx = threadIdx.x; idx < 64 * nc; idx += blockDim.x) {
       const int rr = idx / nc, c = idx % nc;
       const int64_t r = r0 + rr;
-      if (r < total) bp[(int64_t)iperm[r] * nrhs + c0 + c] = tile[rr][c];
+      if (r < total && (!only || only[mat_of_row[r]])) bp[(int64_t)iperm[r] * nrhs + c0 + c] = tile[rr][c];
     }
     __syncthreads();
   }
@@ -272,7 +272,7 @@ __global__ void k_batch_gather(int64_t total, int32_t nrhs, const double *__rest
 
 __global__ void k_batch_scatter(int64_t total, int32_t nrhs, const double *__restrict__ xp,
                                 const int32_t *__restrict__ mat_of_row, const int64_t *__restrict__ row_off,
-                                const int32_t *__restrict__ iperm, double *x) {
+                                const int32_t *__restrict__ iperm, const uint8_t *__restrict__ only, double *x) {
   __shared__ double tile[64][33];
   const int64_t r0 = (int64_t)blockIdx.x * 64;
   for (int32_t c0 = 0; c0 < nrhs; c0 += 32) {
@@ -280,13 +280,13 @@ __global__ void k_batch_scatter(int64_t total, int32_t nrhs, const double *__res
     for (int idx = threadIdx.x; idx < 64 * nc; idx += blockDim.x) {
       const int rr = idx / nc, c = idx % nc;
       const int64_t r = r0 + rr;
-      if (r < total) tile[rr][c] = xp[(int64_t)iperm[r] * nrhs + c0 + c];
+      if (r < total && (!only || only[mat_of_row[r]])) tile[rr][c] = xp[(int64_t)iperm[r] * nrhs + c0 + c];
     }
     __syncthreads();
     for (int idx = threadIdx.x; idx < 64 * nc; idx += blockDim.x) {
       const int c = idx / 64, rr = idx % 64;
       const int64_t r = r0 + rr;
-      if (r < total) {
+      if (r < total && (!only || only[mat_of_row[r]])) {
         const int32_t m = mat_of_row[r];
         const int64_t ro = row_off[m], nm = row_off[m + 1] - ro;
         x[nrhs * ro + (int64_t)(c0 + c) * nm + (r - ro)] = tile[rr][c];
@@ -466,17 +466,19 @@ hipError_t launch_residual(int32_t n, int32_t nrhs, const int32_t *rp, const int
 }
 
 hipError_t launch_batch_gather(int64_t total, int32_t nrhs, const double *b, const int32_t *mat_of_row,
-                               const int64_t *row_off, const int32_t *iperm, double *bp, hipStream_t s) {
+                               const int64_t *row_off, const int32_t *iperm, const uint8_t *only, double *bp,
+                               hipStream_t s) {
   if (total <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_batch_gather, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, s, total, nrhs, b, mat_of_row,
-                     row_off, iperm, bp);
+                     row_off, iperm, only, bp);
   return hipGetLastError();
 }
 
 hipError_t launch_batch_scatter(int64_t total, int32_t nrhs, const double *xp, const int32_t *mat_of_row,
-                                const int64_t *row_off, const int32_t *iperm, double *x, hipStream_t s) {
+                                const int64_t *row_off, const int32_t *iperm, const uint8_t *only, double *x,
+                                hipStream_t s) {
   if (total <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_batch_scatter, dim3((unsigned)((total + 63) / 64)), dim3(256), 0, s, total, nrhs, xp,
-                     mat_of_row, row_off, iperm, x);
+                     mat_of_row, row_off, iperm, only, x);
   return hipGetLastError();
 }

@@ -174,3 +174,27 @@ def test_batch_with_levels_too_wide_for_a_window(nrhs, wide_first):
     h.batch_solve(bd, x2, nrhs, looped=True)
     h.check()
     assert torch.equal(x, x2)
+
+
+@pytest.mark.parametrize("nrhs", [2, 3, 4, 5, 7, 13, 17])
+@pytest.mark.parametrize("wg", [256, 512, 1024])
+def test_batch_column_groups(batch, nrhs, wg):
+    """Groups of four columns, the last one overlapping where four does not
+    divide, straight from and to the caller's columns; the per-matrix solves
+    give the same bits, and so does a second call."""
+    mats, _, h = batch
+    b = _rhs_cat(mats, nrhs)
+    h.set_schedule(sp.BATCH, mode=2, wg_threads=wg)
+    x = torch.zeros(b.size, dtype=torch.float64, device="cuda")
+    h.batch_solve(to_dev(b), x, nrhs)
+    x2, x3 = torch.zeros_like(x), torch.zeros_like(x)
+    h.batch_solve(to_dev(b), x2, nrhs, looped=True)
+    h.batch_solve(to_dev(b), x3, nrhs)
+    h.check()
+    assert torch.equal(x, x2) and torch.equal(x, x3)
+    off = 0
+    for m in mats:
+        xm = x[off * nrhs:(off + m.n) * nrhs].cpu().numpy().reshape(nrhs, m.n)
+        assert oracle.relerr(xm, oracle.solve(m, b[off * nrhs:(off + m.n) * nrhs].reshape(nrhs, m.n))) <= TOL
+        off += m.n
+    h.set_schedule(sp.BATCH)
