@@ -307,16 +307,27 @@ __device__ __forceinline__ bool row_held(const ScanArgs &a, int32_t r, int32_t n
 }
 
 // Size and cost of level lvl counting only its rows still there (the target a
-// refusal creates keeps the rows skipped or not yet tried).
+// refusal creates keeps the rows skipped or not yet tried), by one wave: a
+// lane per row (one thread reading the rows one after another took two memory
+// round trips for each).
 __device__ __forceinline__ void level_left(const ScanArgs &a, int32_t lvl, int64_t &size, int64_t &cost) {
-  size = 0;
-  cost = 0;
-  for (int32_t p = a.level_ptr[lvl]; p < a.level_ptr[lvl + 1]; ++p) {
+  const int lane = threadIdx.x & 63;
+  long long n = 0, c = 0;
+  const int32_t e = a.level_ptr[lvl + 1];
+  for (int32_t p = a.level_ptr[lvl] + lane; p < e; p += 64) {
     const int32_t rr = a.level_rows[p];
+    const int32_t nz = a.rp[rr + 1] - a.rp[rr];
     if (a.cur[rr] != lvl) continue;
-    size += 1;
-    cost += 2 * (int64_t)(a.rp[rr + 1] - a.rp[rr]) - 1;
+    n += 1;
+    c += 2 * (int64_t)nz - 1;
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    n += __shfl_xor(n, off, 64);
+    c += __shfl_xor(c, off, 64);
+  }
+  size = n;
+  cost = c;
 }
 
 __device__ __forceinline__ bool is_source(const ScanArgs &a, int32_t lvl) {
@@ -379,25 +390,34 @@ __device__ int32_t claim_segment(unsigned long long *claim, bool front) {
 
 // The decision scan: each workgroup takes segments (even-numbered workgroups
 // from the front, odd ones from the end) and scans each in level order
-// (targets only move forward). Thread 0 owns the scan state; waves evaluate
-// candidates. The result does not depend on the number of workgroups.
+// (targets only move forward). The first wave owns the scan state (the same in
+// all its lanes); waves evaluate candidates. The result does not depend on the
+// number of workgroups.
+// A chain of decisions: what counts is the memory round trips of one chunk. The
+// first wave reads the chunk's level bounds and rows in one each, the
+// evaluating waves leave behind what the decisions read, and a new target's rows
+// are counted a lane each. Naive rewriting of a power law of 300,007 rows: 15.1 ms
+// against 17.5 with one thread reading all of these one after another; what is
+// left is the substitutions themselves, four to five round trips for each row
+// they pass through.
 __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
   extern __shared__ __align__(16) char lds_raw[];
   __shared__ int32_t c_row[kWaves], c_lvl[kWaves], c_q[kWaves], c_st[kWaves], c_na[kWaves], c_nt[kWaves];
-  __shared__ int32_t c_lo[kWaves], c_hi[kWaves];
+  __shared__ int32_t c_lo[kWaves], c_hi[kWaves], c_old[kWaves];
+  __shared__ double c_bud[kWaves], c_cap[kWaves];
   __shared__ int32_t s_nc, s_done, s_redo, s_t;
-  __shared__ int64_t s_capA_cost;
+  __shared__ int64_t s_cost;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   Ws w = lds_ws(lds_raw, wave);
   char *const big = a.big + (size_t)blockIdx.x * a.big_stride;
   const bool front = (blockIdx.x & 1u) == 0u;
-  // scan state (thread 0); the first chunk claims a segment
+  // scan state (first wave); the first chunk claims a segment
   int32_t t = 0, l = 0, q = 0, seg_end = 0, moved = 0, maxd = 0, steps = 0, held = 0;
   int64_t size = 0, cost = 0;
   int bits = 0;
   const int64_t guard = (int64_t)a.n + 2 * (int64_t)a.nlev + 16;
   for (int64_t iter = 0;; ++iter) {
-    if (tid == 0) {
+    if (wave == 0) {
       // next chunk of candidates: rows of consecutive source levels of the
       // current segment, or of the next segment claimed
       int32_t nc = 0;
@@ -407,22 +427,31 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
           const double room = a.Wmax - (double)size;  // rows the target can still take (at most)
           if (room < (double)kWaves) limit = room < 0.0 ? 1 : (int32_t)room + 1;
         }
-        while (l < seg_end && nc < limit) {
-          const int32_t lb = a.level_ptr[l], lr = a.level_ptr[l + 1] - lb;
-          while (q < lr && nc < limit) {
-            c_row[nc] = a.level_rows[lb + q];
-            c_lvl[nc] = l;
-            c_q[nc] = q;
-            ++nc;
-            ++q;
+        if (l < seg_end) {
+          // lane i: the first position of level l + i; no level is empty, so
+          // the chunk's rows lie in its first kWaves + 1 levels
+          const int32_t bnd = a.level_ptr[l + lane <= seg_end ? l + lane : seg_end];
+          const int32_t pos = __shfl(bnd, 0, 64) + q;
+          nc = min(limit, __shfl(bnd, 63, 64) - pos);
+          int32_t up = 0, up2 = 0;  // levels passed by this lane's row, by the next chunk's first row
+          const int32_t first = __shfl(bnd, 0, 64);
+          int32_t lb = first, lb2 = first;
+#pragma unroll
+          for (int i = 1; i <= kWaves + 1; ++i) {
+            const int32_t bi = __shfl(bnd, i, 64);
+            if (l + i <= seg_end && bi <= pos + lane) up = i, lb = bi;
+            if (l + i <= seg_end && bi <= pos + nc) up2 = i, lb2 = bi;
           }
-          if (q == lr) {
-            ++l;
-            q = 0;
+          if (lane < nc) {
+            c_row[lane] = a.level_rows[pos + lane];
+            c_lvl[lane] = l + up;
+            c_q[lane] = pos + lane - lb;
           }
+          l += up2;
+          q = pos + nc - lb2;
         }
         if (nc > 0) break;
-        const int32_t k = claim_segment(a.claim, front);
+        const int32_t k = __shfl(lane == 0 ? claim_segment(a.claim, front) : 0, 0, 64);
         if (k < 0) break;
         t = a.seg[k];
         seg_end = a.seg[k + 1];
@@ -432,17 +461,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
         l = t + 1;
         q = 0;
       }
-      s_nc = nc;
-      s_t = t;
-      s_done = (nc == 0) || iter > guard;
       if (iter > guard) bits |= EB_TIMEOUT;
-      // bound on A columns: fill cap, and for a cost budget the room left
-      int64_t capA = INT64_MAX;
-      s_capA_cost = capA;
-      if (a.metric == SPTRSV_THIN_COST) {
-        // cost_t + 2*(nA+1) - 1 <= W  =>  nA <= (W - cost_t - 1) / 2
-        const double room = a.W - (double)cost - 1.0;
-        s_capA_cost = room < 0.0 ? -1 : (int64_t)(room / 2.0);
+      if (lane == 0) {
+        s_nc = nc;
+        s_t = t;
+        s_done = (nc == 0) || iter > guard;
+        s_cost = cost;
       }
     }
     __syncthreads();
@@ -451,7 +475,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
     if (wave < nc) {
       const int32_t r = c_row[wave];
       const int64_t nnz_old = a.rp[r + 1] - a.rp[r];
-      int64_t capA = s_capA_cost;
+      // bound on A columns: fill cap, and for a cost budget the room left
+      int64_t capA = INT64_MAX;
+      if (a.metric == SPTRSV_THIN_COST) {
+        // cost_t + 2*(nA+1) - 1 <= W  =>  nA <= (W - cost_t - 1) / 2
+        const double room = a.W - (double)s_cost - 1.0;
+        capA = room < 0.0 ? -1 : (int64_t)(room / 2.0);
+      }
       const double capl = level_cap(a, c_lvl[wave]);
       if (capl > 0.0) {
         // nA + 1 <= fill_cap * nnz_old
@@ -470,6 +500,9 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
       const int2 span = stt == SUB_OK && a.max_spread > 0 ? ws_a_span(used) : make_int2(0, 0);
       if (lane == 0) {
         c_st[wave] = stt;
+        c_old[wave] = (int32_t)nnz_old;
+        c_cap[wave] = capl;
+        c_bud[wave] = level_budget(a, c_lvl[wave]);
         c_na[wave] = *used.na;
         c_nt[wave] = nT;
         c_lo[wave] = span.x;
@@ -477,23 +510,23 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      s_redo = -1;
+    if (wave == 0) {
+      int32_t redo = -1;
       for (int32_t i = 0; i < nc; ++i) {
         if (c_st[i] == SUB_OVERFLOW) {
-          s_redo = i;
+          redo = i;
           break;
         }
         const int32_t r = c_row[i], lvl = c_lvl[i];
-        const int64_t nnz_old = a.rp[r + 1] - a.rp[r];
+        const int64_t nnz_old = c_old[i];
         const int64_t nnz_new = (int64_t)c_na[i] + 1;
         bool ok = c_st[i] == SUB_OK;
         if (ok) {
           if (a.metric == SPTRSV_THIN_ROWS)
-            ok = (double)(size + 1) <= level_budget(a, lvl);
+            ok = (double)(size + 1) <= c_bud[i];
           else
             ok = (double)(cost + 2 * nnz_new - 1) <= a.W;
-          const double capl = level_cap(a, lvl);
+          const double capl = c_cap[i];
           if (capl > 0.0) ok = ok && (double)nnz_new <= capl * (double)nnz_old;
           if (a.max_dist > 0) ok = ok && (lvl - t) <= a.max_dist;
         }
@@ -502,10 +535,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
           continue;
         }
         if (ok) {
-          a.cur[r] = t;
-          a.target[r] = t;
-          a.cntL[r] = (int32_t)nnz_new;
-          a.cntT[r] = c_nt[i] + 1;
+          if (lane == 0) {
+            a.cur[r] = t;
+            a.target[r] = t;
+            a.cntL[r] = (int32_t)nnz_new;
+            a.cntT[r] = c_nt[i] + 1;
+          }
           size += 1;
           cost += 2 * nnz_new - 1;
           ++moved;
@@ -515,16 +550,18 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
           // its level becomes the target with the rows not moved
           t = lvl;
           ++steps;
+          wave_sync();  // the moves above are visible to the lanes that count
           level_left(a, lvl, size, cost);
           l = lvl + 1;
           q = 0;
           break;
         }
       }
-      if (s_redo >= 0) {  // resume right at the overflowing candidate
-        l = c_lvl[s_redo];
-        q = c_q[s_redo];
+      if (redo >= 0) {  // resume right at the overflowing candidate
+        l = c_lvl[redo];
+        q = c_q[redo];
       }
+      if (lane == 0) s_redo = redo;
     }
     __syncthreads();
     if (s_redo >= 0) {
@@ -544,11 +581,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
         }
       }
       __syncthreads();
-      if (tid == 0) {
+      if (wave == 0) {
         const int32_t i = s_redo, r = c_row[i], lvl = c_lvl[i];
         if (c_st[0] == SUB_OVERFLOW) {
           bits |= EB_OVERFLOW;
-          s_done = 1;
+          if (lane == 0) s_done = 1;
         } else {
           const int64_t nnz_old = a.rp[r + 1] - a.rp[r];
           const int64_t nnz_new = (int64_t)c_na[0] + 1;
@@ -563,10 +600,12 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
           const bool keep = ok && row_held(a, r, c_na[0], c_lo[0], c_hi[0]);
           if (keep) ++held;
           if (ok && !keep) {
-            a.cur[r] = t;
-            a.target[r] = t;
-            a.cntL[r] = (int32_t)nnz_new;
-            a.cntT[r] = c_nt[0] + 1;
+            if (lane == 0) {
+              a.cur[r] = t;
+              a.target[r] = t;
+              a.cntL[r] = (int32_t)nnz_new;
+              a.cntT[r] = c_nt[0] + 1;
+            }
             size += 1;
             cost += 2 * nnz_new - 1;
             ++moved;
@@ -582,6 +621,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_rewrite_scan(ScanArgs a) {
           } else {
             t = lvl;
             ++steps;
+            wave_sync();
             level_left(a, lvl, size, cost);
             l = lvl + 1;
             q = 0;
