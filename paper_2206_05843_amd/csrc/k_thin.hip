@@ -860,13 +860,10 @@ hipError_t launch_batch_run(int wg, int32_t nmat, int32_t grid, const int32_t *o
     batch_attr<1024>();
     attr = true;
   }
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    cus = std::max(cus, 1);
-  }
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  cus = std::max(cus, 1);
 #define BATCHG(W, G)                                                                                            \
   hipLaunchKernelGGL((k_batch_run<W, G>), dim3(grid), dim3(W), a.lds, s, nmat, order, mwin, win, nrhs, ncol, \
                      row_off, a, q, err, cus);
