@@ -7,20 +7,27 @@
 
 // a / d with 1/d at hand: the quotient estimate a (1/d) corrected by its exact
 // residual (Markstein's division), three dependent operations in place of the
-// dozen of a full division on a chain that waits for a. The result is that of
-// a / d; where the residual is not finite (a or the quotient is not) the
-// estimate stands, which is then the infinity or NaN of a / d.
-// recip_of gives the 1/d to pass: NaN where d is so large or small that the
-// correction would leave the normal range; such a division is done in full.
+// dozen of a full division on a chain that waits for a. The correction is exact
+// where a, d and the quotient are far from the ends of the range: its residual
+// (106 bits below a) must not underflow, nor the quotient leave the normal
+// range. So it stands for kDivMinA <= |a| with d as recip_of takes it;
+// everything else is divided in full, except a zero, infinite or NaN a, whose
+// product with 1/d is the quotient already (zeros are common in right-hand
+// sides). The result is that of a / d for every a and d, signs of zeros included.
+// recip_of gives the 1/d to pass: NaN where |d| is so large that a small quotient
+// of a kDivMinA would leave the normal range, or so small that 1/d is near
+// overflow; such a division is done in full.
+constexpr double kDivMinA = 0x1p-900;
 __device__ __forceinline__ double recip_of(double d) {
   const double m = fabs(d);
-  return m >= 0x1p-1000 && m <= 0x1p1000 ? 1.0 / d : __builtin_nan("");
+  return m >= 0x1p-1000 && m <= 0x1p120 ? 1.0 / d : __builtin_nan("");
 }
 __device__ __forceinline__ double div_by(double a, double d, double r) {
   const double q = a * r;
   const double e = fma(-d, q, a);
   double x = fma(e, r, q);
-  if (__builtin_expect(!isfinite(e), 0)) x = r == r ? q : a / d;
+  // the residual is not finite where a, r or the quotient is not
+  if (__builtin_expect(!isfinite(e) || fabs(a) < kDivMinA, 0)) x = r == r && (a == 0.0 || !isfinite(a)) ? q : a / d;
   return x;
 }
 

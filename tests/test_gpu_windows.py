@@ -72,6 +72,43 @@ def test_division_at_the_ends_of_the_range(mode):
     assert np.array_equal(x, b / d)
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("levels", [1, 2])
+def test_division_of_small_numbers(mode, levels):
+    """Dividends near and below the normal range, zeros of both signs and
+    quotients at the ends of the range under ordinary and extreme diagonals,
+    alone in a window of one level and behind a dependency of weight 0: the
+    quotients are those of one IEEE division, bit for bit."""
+    rng = np.random.default_rng(11)
+    e = np.concatenate([rng.integers(-1074, -890, 1500), rng.integers(960, 1023, 300), rng.integers(-40, 40, 300)])
+    b = np.ldexp(rng.uniform(1, 2, e.size), e) * rng.choice([-1.0, 1.0], e.size)
+    d = np.ldexp(rng.uniform(1, 2, e.size), rng.integers(-45, 45, e.size)) * rng.choice([-1.0, 1.0], e.size)
+    ends = [(a, q) for a in (0.0, -0.0, 2.0 ** -1074, 2.0 ** -1022, 2.0 ** -900, 2.0 ** -901, 1.0, 9 * 2.0 ** -1074)
+            for q in (2.0, -3.0, 6.0, 2.0 ** 119, 2.0 ** 120, 3.0 * 2.0 ** 119, 2.0 ** 1000, 2.0 ** -1000)]
+    b = np.concatenate([b, [a for a, _ in ends], [float.fromhex("0x1.e2169b426629cp-1019")]])
+    d = np.concatenate([d, [q for _, q in ends], [float.fromhex("0x1.6ee71b15cff4bp+0")]])
+    with np.errstate(over="ignore", under="ignore"):
+        keep = np.isfinite(b / d)
+        b, d = b[keep], d[keep]
+        n = b.size
+        if levels == 1:
+            m = gen.from_dense_lower(np.diag(d))
+            want = b / d
+        else:  # row n + i reads row i with weight 0
+            rp = np.concatenate([np.arange(n), n + 2 * np.arange(n + 1)]).astype(np.int32)
+            col = np.concatenate([np.arange(n), np.stack([np.arange(n), n + np.arange(n)], 1).reshape(-1)])
+            val = np.concatenate([d, np.stack([np.zeros(n), d], 1).reshape(-1)])
+            m = gen.Csr(2 * n, rp, col.astype(np.int32), val)
+            x = b / d
+            want = np.concatenate([x, (b - 0.0 * x) / d])
+            b = np.concatenate([b, b])
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    x = _solve(h, to_dev(b), 1, mode=mode).cpu().numpy()
+    bad = np.nonzero(x.view(np.int64) != want.view(np.int64))[0]
+    assert bad.size == 0, (bad.size, b[bad[0]].hex(), d[bad[0] % n].hex(), x[bad[0]].hex(), want[bad[0]].hex())
+
+
 @pytest.mark.parametrize("mode", [1, 2, 3])
 def test_infinities_stay_infinities(mode):
     m = gen.from_dense_lower(np.array([[0.5, 0, 0], [0, 2.0, 0], [1.0, 0, 4.0]]))
