@@ -275,6 +275,9 @@ sptrsv_status_t sptrsv_check(sptrsv_handle_t h, hipStream_t s);
  * into chunks of 2 * wide_threads items (wide_threads = 128, 256 or 512) and
  * a chunk waits only for the chunks of the run holding the rows it reads, not
  * for whole levels (wide_grid: workgroups in flight, 0 = as many as fit).
+ * Waits between workgroups end in TIMEOUT after 10 s: of the launch in mode 3,
+ * in mode 4's runs of wider levels and in persistent runs of wide levels; in thin
+ * runs, whose windows are spread over workgroups, of a wait without any progress.
  * overlap = 1: when the work vectors are large (n * nrhs >= 2^22) and the
  * chain has at least four runs, the transposes between the caller's b, x and
  * the work vectors run in 64-row tile groups on a handle-owned side stream

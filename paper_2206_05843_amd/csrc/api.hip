@@ -719,12 +719,14 @@ static sptrsv_status_t launch_run(sptrsv_ctx *h, Plan &P, const Run &r, int32_t 
   int *err = h->d_err.p;
   const int slot = h->prof ? prof_begin(h, r.thin ? 1 : 2, run_bytes(P, r.l0, r.l1, nrhs), s) : -1;
   if (r.thin) {
-    const unsigned long long lim = wait_limit(h);
+    // level sets: only a wait that has stalled ends in a time-out, and the autotuner's limits do not touch it;
+    // the synchronisation-free executor's limit is on the launch in either form
+    const unsigned long long lim = r.free ? wait_limit(h) : kWaitTicks;
     if (!pending && thin_piped(r.nw, lim))
       HIPCHK(h, launch_fill_pending(P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1] - P.h_level_ptr[(size_t)r.l0],
                                     nrhs, ta.rio.x ? ta.rio.perm : nullptr, ta.rio.x ? ta.rio.x : xp, s));
     HIPCHK(h, launch_thin_run(r.free ? kFreeThreads : sc.wg_threads, P.win.p + r.wi, r.nw, nrhs, ta, err, s, nullptr,
-                              0.f, r.free ? 1 : thin_width(sc, nrhs), lim));
+                              0.f, r.free ? 1 : thin_width(sc, nrhs), lim, r.free));
   } else if (r.longr) {
     const int64_t rows = P.h_level_ptr[r.l1] - P.h_level_ptr[r.l0];
     const int32_t avg = (int32_t)std::min<int64_t>((P.h_lv_nnz[(size_t)r.l0] - rows) / std::max<int64_t>(rows, 1),
@@ -809,7 +811,7 @@ sptrsv_status_t solve_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const double *b
   // one right-hand side: the gather marks x for all spread thin runs
   bool pending = false;
   if (nrhs == 1)
-    for (const Run &r : P.runs) pending = pending || (r.thin && thin_piped(r.nw, wait_limit(h)));
+    for (const Run &r : P.runs) pending = pending || (r.thin && thin_piped(r.nw, kWaitTicks));
   STCHK(gather_b(h, P, nrhs, b, ldb, bp, pending ? xp : nullptr, s));
   prof_end(h, slot, s);
   if (sc.mode == 3 && P.runs.empty()) {  // synchronisation-free: one launch for the whole solve (profiled as wide)

@@ -153,10 +153,10 @@ sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipSt
     for (const Run &r : bw.runs) {
       if (r.thin) {
         const int32_t p0 = P.h_level_ptr[(size_t)r.l0];
-        if (thin_piped(r.nw, wait_limit(h)))
+        if (thin_piped(r.nw, kWaitTicks))
           HIPCHK(h, launch_fill_pending(p0, P.h_level_ptr[(size_t)r.l1] - p0, nrhs, nullptr, P.xp.p, s));
         HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
-                                  h->b_ncol, wait_limit(h)));
+                                  h->b_ncol, kWaitTicks));
       } else
         HIPCHK(h, launch_wide_level(d.wide_threads, 1, P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1], nrhs,
                                     P.srp.p, P.sci.p, P.sva.p, P.sdg.p, P.ell_c.p, P.ell_v.p, P.bp.p, P.xp.p,
@@ -383,7 +383,7 @@ sptrsv_status_t sptrsv_batch_solve_looped(sptrsv_handle_t h, int32_t nrhs, const
     const int32_t wi = h->b_h_mwin[(size_t)m], nw = h->b_h_mwin[(size_t)m + 1] - wi - 1;
     if (nw >= 1)
       HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
-                                h->b_ncol, wait_limit(h)));
+                                h->b_ncol, kWaitTicks));
   }
   STCHK(batch_wide_solves(h, nrhs, wg, s));
   HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, nullptr, d_x_cat,

@@ -271,10 +271,10 @@ struct sptrsv_ctx {
 // (api_noalloc.hip), looked up once per device.
 hipError_t noalloc_init(int dev);
 
-// Wait limit of a solve launch in wall-clock ticks.
-inline unsigned long long wait_limit(const sptrsv_ctx *h) {
-  return h->wait_ticks ? h->wait_ticks : 100000000ull * 10;
-}
+// Wait limit of a solve launch in wall-clock ticks, 10 s unless the autotuner
+// has set another.
+constexpr unsigned long long kWaitTicks = 100000000ull * 10;
+inline unsigned long long wait_limit(const sptrsv_ctx *h) { return h->wait_ticks ? h->wait_ticks : kWaitTicks; }
 
 // Status plumbing ------------------------------------------------------------
 sptrsv_status_t set_err(sptrsv_ctx *h, sptrsv_status_t st, const char *fmt, ...);
@@ -443,13 +443,16 @@ int thin_win_bytes();
 // hist: kWidths arrays of nlev * kExtraBuckets, back to back, zeroed by the caller
 hipError_t launch_extra_hist(int32_t n, const int32_t *level_ptr, int32_t nlev, const int32_t *srp,
                              const int32_t *sci, int32_t *lop, int32_t *hist, hipStream_t s);
-// ng: right-hand sides per workgroup (a divisor of nrhs; 0 = all). tlimit > 0:
-// a run of several windows is spread over workgroups, whose waits end at that
-// wall-clock limit; the x of the run's rows must read as kPendingX before the
-// launch (launch_fill_pending, or launch_gather with xp). 0: one workgroup per
+// ng: right-hand sides per workgroup (0 = all; where it does not divide nrhs the
+// last group overlaps the one before). tlimit > 0: a run of several windows is
+// spread over workgroups; a wave that waits without progress for tlimit
+// wall-clock ticks (whole_launch: that is still waiting tlimit ticks after the
+// start) latches a time-out; the x of the run's rows must read as kPendingX before
+// the launch (launch_fill_pending, or launch_gather with xp). 0: one workgroup per
 // group of columns solves the windows one after another.
 hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err,
-                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit);
+                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit,
+                           bool whole_launch = false);
 bool thin_piped(int32_t nwin, unsigned long long tlimit);
 // x of positions [p0, p0 + rows) = kPendingX (perm: x by caller rows)
 hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s);

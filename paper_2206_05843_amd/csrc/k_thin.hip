@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "sync.h"
+#include "wait.h"
 
 namespace {
 
@@ -322,15 +323,16 @@ constexpr int kPollSleep = 1;
 // kPoll: earlier windows may still be in progress on other workgroups. Every
 // unfinished x then reads as kPendingX, so a load of it returns "done" and the
 // value at once: a row's sum takes the finished values first (they come first:
-// ascending positions), then waits for the others past the caches, until the
-// wall clock reaches t0 + tlimit (time-out).
+// ascending positions), then waits for the others past the caches. A wave that
+// has not moved for tlimit ticks of the wall clock gives up (time-out); with
+// whole_launch it does so tlimit ticks after t0, however it moved.
 // rot: the first thread of the wave that solves the levels of at most 64 items.
 // touch_next: the other waves bring the next window's data nearer meanwhile.
 template <int WG, int kGw, bool kTimed, bool kSplit, bool kPoll>
 __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restrict__ win, int32_t w, int32_t nrhs,
                                             int32_t ng, int32_t c0_arg, const ThinArgs &A, float *times,
                                             float ns_per_tick, unsigned long long t0, unsigned long long tlimit,
-                                            int rot, bool touch_next) {
+                                            bool whole_launch, int rot, bool touch_next) {
   constexpr bool kOne = kGw == 1;
   const int32_t nr = kOne && !kSplit ? 1 : nrhs;  // stride of the global vectors
   const int32_t gw = kGw > 0 ? kGw : ng;          // columns in LDS and per row of items
@@ -464,6 +466,7 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
       // finished ones taken in order
       constexpr int kP = 2;
       unsigned spins = 0;
+      WaitLimit wait{t0, !whole_launch};
       for (;;) {
         bool left[kI], any = false, moved = false;
         double wv[kI][kP];
@@ -503,8 +506,10 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
           moved = moved || done > 0;
           if (done > 0 && e0[j] == e1[j]) v[(int64_t)(base + j * WG + tid)] = acc[j];
         }
-        if (__ballot(moved) == 0ull) __builtin_amdgcn_s_sleep(kPollSleep);
-        if ((++spins & 63u) == 0u && wall_clock64() - t0 > tlimit) {
+        const bool step = __ballot(moved) != 0ull;
+        if (!step) __builtin_amdgcn_s_sleep(kPollSleep);
+        wait.moved = wait.moved || (step && !whole_launch);
+        if ((++spins & 63u) == 0u && wait.expired(wall_clock64(), tlimit)) {
           bits |= EB_TIMEOUT;
           break;
         }
@@ -583,7 +588,7 @@ __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restri
   int bits = 0;
   for (int32_t w = 0; w < nwin && !(bits & EB_ARG); ++w)
     bits |= solve_window<WG, kGw, kTimed, kSplit, false>(lds_raw, win, w, nrhs, ng, c0, A, times, ns_per_tick, 0, 0,
-                                                               rot, touch && w + 1 < nwin);
+                                                         false, rot, touch && w + 1 < nwin);
   return bits;
 }
 
@@ -625,7 +630,8 @@ __global__ __launch_bounds__(WG) void k_thin_run(const int4 *__restrict__ win, i
 constexpr int kXcd = 8;
 template <int WG, bool kOne, bool kSplit>
 __global__ __launch_bounds__(WG) void k_thin_pipe(const int4 *__restrict__ win, int32_t nwin, int32_t nrhs, int32_t ng,
-                                                  int32_t nlane, ThinArgs A, int *err, unsigned long long tlimit) {
+                                                  int32_t nlane, ThinArgs A, int *err, unsigned long long tlimit,
+                                                  int whole_launch) {
   extern __shared__ __align__(16) char lds_raw[];
   const int32_t lane = (int32_t)blockIdx.x % kXcd;
   if (lane >= nlane) return;
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(WG) void k_thin_pipe(const int4 *__restrict__ win, 
     if (t >= nwin * mine) break;
     const int32_t w = t / mine, g = lane + nlane * (t - w * mine);
     bits |= solve_window<WG, kOne ? 1 : 0, false, kSplit, true>(lds_raw, win, w, nrhs, ng, first_col(g, nrhs, ng), A, nullptr, 0.f, t0,
-                                                        tlimit, 0, false);
+                                                        tlimit, whole_launch != 0, 0, false);
   }
   if (bits) atomicOr(err, bits);
   __syncthreads();
@@ -783,7 +789,8 @@ hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32
 }
 
 hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err,
-                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit) {
+                           hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit,
+                           bool whole_launch) {
   if (ng <= 0 || ng > nrhs || times) ng = nrhs;  // labelling runs are never split
   const bool one = ng == 1;
   const bool split = ng < nrhs;
@@ -807,7 +814,7 @@ hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, 
 #define THIN(W, ONE, SPLIT)                                                                                       \
   if (pipe)                                                                                                       \
     hipLaunchKernelGGL((k_thin_pipe<W, ONE, SPLIT>), dim3((unsigned)depth * kXcd), dim3(W), kWinBytes, s, win,     \
-                       nwin, nrhs, ng, nlane, a, err, tlimit);                                                    \
+                       nwin, nrhs, ng, nlane, a, err, tlimit, whole_launch ? 1 : 0);                                                  \
   else                                                                                                            \
     hipLaunchKernelGGL((k_thin_run<W, ONE, false, SPLIT>), dim3((unsigned)groups), dim3(W), kWinBytes, s, win,     \
                        nwin, nrhs, ng, a, err, (float *)nullptr, 0.f);
