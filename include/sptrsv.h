@@ -56,7 +56,7 @@ typedef enum {
 
 /* Which plan: the analysed matrix, its rewrite, or (schedule and autotuner
  * only) the batched matrices of sptrsv_batch_analyze, whose persistent launch
- * uses the wg_threads knob (256, 512 or 1024). */
+ * uses the wg_threads knob (256, 512 or 1024) when it has more tasks than CUs. */
 enum { SPTRSV_ORIGINAL = 0, SPTRSV_REWRITTEN = 1, SPTRSV_BATCH = 2 };
 enum { SPTRSV_THIN_ROWS = 0, SPTRSV_THIN_COST = 1 };
 /* Triangular forms a handle can solve (sptrsv_analyze_form). */
@@ -303,7 +303,7 @@ typedef struct {
   int32_t thin_cols;      /* right-hand sides per thin-run workgroup: 0 = all; c, a divisor of nrhs smaller than
                              it = nrhs / c workgroups each solve c columns of every thin run (columns are
                              independent), with LDS windows cut for c columns; otherwise all. The batched
-                             launch (SPTRSV_BATCH) takes its columns in groups of four by itself */
+                             launch (SPTRSV_BATCH) groups its columns by itself */
 } sptrsv_schedule_t;
 sptrsv_status_t sptrsv_set_schedule(sptrsv_handle_t h, int which, const sptrsv_schedule_t *sched);
 sptrsv_status_t sptrsv_get_schedule(sptrsv_handle_t h, int which, int32_t nrhs, sptrsv_schedule_t *sched);
@@ -413,10 +413,14 @@ sptrsv_status_t sptrsv_residual(sptrsv_handle_t h, int32_t nrhs, const double *d
  * column indices local. Each matrix is level-scheduled as in sptrsv_analyze.
  * batch_solve solves all matrices in one persistent launch; matrix i's b and x
  * are n_i x nrhs column-major at offset nrhs*h_row_off[i], ld = n_i. ASYNC.
- * A matrix with a level too wide for one workgroup's LDS window (about 3,300
- * rows with four columns of it) is taken out of the persistent
- * launch and solved level by level (thin runs, one device-wide launch per
- * wide level) in the same call, with the same result.
+ * Columns are taken in groups of 1, 4, 8 or all, whichever is estimated fastest
+ * (one a group when there are few), by workgroups of wg_threads threads (1,024
+ * when there is at most one task per CU). A matrix with a level too wide for one
+ * workgroup's LDS window (6,700 rows in groups of one, 3,300 of four, 1,100 of
+ * sixteen), or whose wide levels are estimated to take longer in the launch than
+ * outside, is taken out of the persistent launch and solved level by level (thin
+ * runs, one device-wide launch per wide level) in the same call, with the same
+ * result.
  * ------------------------------------------------------------------------- */
 sptrsv_status_t sptrsv_batch_analyze(sptrsv_handle_t h, int32_t nmat, const int32_t *h_n, const int64_t *h_row_off,
                                      const int64_t *h_nnz_off, const int32_t *d_row_ptr_cat, const int32_t *d_col_cat,

@@ -2,7 +2,6 @@
 // system (levels per matrix), solved in one persistent launch.
 #include <algorithm>
 #include <cstring>
-#include <numeric>
 
 #include "common.h"
 
@@ -64,46 +63,173 @@ int bit_width64(int64_t v) {
   return b;
 }
 
-// Columns per group of the persistent launch: 4, so that most levels (a few rows
-// wide) fit one wave, else all of 1 to 3. Groups may overlap: 13 columns are
-// four groups of 4. 512 matrices x 16 columns took 3.91 ms in groups of 4 (256
-// threads), 4.15 in groups of 8 (512 threads), 6.3 in groups of 2.
-int32_t batch_cols(int32_t nrhs) { return nrhs >= 4 ? 4 : nrhs; }
+// How a batch is solved: nc columns a group (groups may overlap: 13 columns are
+// four groups of 4), workgroups of wg threads, whether each has a CU's whole LDS,
+// and the matrices in the persistent queue, the longest chain first.
+struct BatchForm {
+  int32_t nc = 1, wg = 512;
+  bool whole = false;
+  std::vector<int32_t> queue;
+  std::vector<char> queued;  // per matrix
+};
 
-// Per-matrix LDS windows for nrhs (cached). A matrix whose levels all fit an
-// LDS window goes in the persistent queue; a matrix with a level too wide for
-// one is solved level by level instead (its narrow levels in thin runs, its
-// wide ones one device-wide launch each, as a single plan's mode-0 schedule).
-// Windows are as large as lets several workgroups share a CU (batch_lds), or as
-// the widest level that fits a whole CU's LDS needs.
+// Estimated microseconds, by which a form is chosen. A matrix in the queue is one
+// workgroup's chain of windows: by columns x rows a level takes 1 x 8 0.17, 1 x 40
+// 0.3, 1 x 300 1.8, 1 x 1,000 5.8, 1 x 3,000 14.3, 4 x 8 0.26, 4 x 300 5.5, 4 x 1,000
+// 20.7, 4 x 3,000 51 with 512 threads; 256 threads take about 1.4 times as long,
+// 1,024 0.85 times.
+// Workgroups that share a CU share its rate of items (columns x rows), not the
+// latency of the levels.
+constexpr double kLevelUs = 0.12, kItemUs = 0.005;
+double wg_factor(int32_t wg) { return wg <= 256 ? 1.4 : wg >= 1024 ? 0.85 : 1.0; }
+double chain_us(int64_t rows, int32_t nlev, int32_t nc, int32_t wg) {
+  return wg_factor(wg) * (kLevelUs * nlev + kItemUs * (double)(rows * nc));
+}
+// A level on the whole device: in LDS windows of nc columns spread over workgroups
+// (1 column x 500 rows 1.1, 1 x 1,000 2.3; 16 columns in groups of one x 500 2.1, x
+// 1,000 6.1), or as a launch of its own (4.2 and its data; 40 levels x 3,000 rows
+// x 4 columns 167 against 1,390 in windows of four).
+double window_level_us(int64_t rows, int32_t nrhs, int32_t nc) {
+  return 0.4 + 0.0013 * (double)rows * (nc + 0.2 * nrhs);
+}
+double launch_level_us(int64_t rows, int32_t nrhs) { return 4.2 + 1.4e-5 * (double)rows * nrhs; }
+bool level_in_windows(const Plan &P, int32_t l, int32_t nrhs, int32_t nc) {
+  const int64_t rows = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
+  return level_fits_window(P, l, nc) && window_level_us(rows, nrhs, nc) <= launch_level_us(rows, nrhs);
+}
+
+// The form with nc columns a group, and its estimated time: the queue lasts as
+// long as its longest chain, or as all its levels over the workgroups in flight and
+// all its items over the CUs, and the matrices outside it follow one after another. Outside are those with a level too
+// wide for an LDS window and, longest chain first, as many more as shorten the
+// whole: one matrix of 40 levels of 3,000 rows, 4 columns, takes 2,057 us in the
+// queue and 167 outside, 64 of them 2,663 and 10,257. Only matrices of 100 rows a
+// level and more are worth a look.
+double batch_form(const sptrsv_ctx *h, int32_t nrhs, int32_t nc, int32_t wg, int32_t cus, BatchForm &f) {
+  const Plan &P = h->bat;
+  const int32_t nm = h->b_nmat, groups = (nrhs + nc - 1) / nc;
+  f.nc = nc;
+  f.whole = (int64_t)nm * groups <= cus;
+  f.wg = f.whole ? 1024 : wg;
+  f.queued.assign((size_t)nm, 1);
+  f.queue.clear();
+  const int32_t most = f.whole ? cus : std::max(1, batch_resident_blocks(wg, batch_lds(wg)));
+  std::vector<double> in((size_t)nm), out((size_t)nm, -1.0);  // out < 0: stays in the queue
+  double outside = 0.0;
+  int64_t levels = 0, rows_in = 0;  // of the queue
+  for (int32_t m = 0; m < nm; ++m) {
+    const bool fits = thin_window_bytes(h->b_widest[(size_t)m], 0, 1, nc, kWidths) <= thin_win_bytes();
+    const int32_t nl = h->b_nlev[(size_t)m];
+    in[(size_t)m] = chain_us(h->b_n[(size_t)m], nl, nc, f.wg);
+    if (!fits || h->b_n[(size_t)m] >= (int64_t)100 * nl) {
+      out[(size_t)m] = 5.0;
+      for (int64_t l = h->b_lvl_off[(size_t)m]; l < h->b_lvl_off[(size_t)m + 1]; ++l) {
+        const int64_t rows = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
+        out[(size_t)m] += level_in_windows(P, (int32_t)l, nrhs, nc) ? window_level_us(rows, nrhs, nc)
+                                                                    : launch_level_us(rows, nrhs);
+      }
+    }
+    if (!fits) {
+      f.queued[(size_t)m] = 0;
+      outside += out[(size_t)m];
+    } else {
+      f.queue.push_back(m);
+      levels += nl;
+      rows_in += h->b_n[(size_t)m];
+    }
+  }
+  std::stable_sort(f.queue.begin(), f.queue.end(),
+                   [&](int32_t a, int32_t b) { return in[(size_t)a] > in[(size_t)b]; });
+  // widest level of the queue from its j-th matrix on, which decides how many workgroups share a CU
+  std::vector<int64_t> widest(f.queue.size() + 1, 0);
+  for (size_t j = f.queue.size(); j-- > 0;) widest[j] = std::max(widest[j + 1], h->b_widest[(size_t)f.queue[j]]);
+  auto total = [&](size_t j) {  // the first j of the queue outside; 12: copies of b and x
+    const int64_t need = thin_window_bytes(widest[j], 0, 1, nc, kWidths) + thin_ctl_bytes();
+    const int64_t fit = (int64_t)cus * std::max<int64_t>(1, (thin_win_bytes() + thin_ctl_bytes()) / need);
+    const double longest = j < f.queue.size() ? in[(size_t)f.queue[j]] : 0.0;
+    const double slots = (double)std::min<int64_t>(most, fit);
+    const double all = wg_factor(f.wg) * kLevelUs * (double)levels * groups / slots +
+                       (f.whole ? wg_factor(f.wg) : 1.0) * kItemUs * (double)rows_in * nc * groups / cus;
+    return outside + (outside > 0.0 ? 12.0 : 0.0) + std::max(longest, all);
+  };
+  double us = total(0);
+  size_t leave = 0;
+  const double outside0 = outside;
+  for (size_t j = 0; j < f.queue.size() && out[(size_t)f.queue[j]] >= 0.0; ++j) {
+    outside += out[(size_t)f.queue[j]];
+    levels -= h->b_nlev[(size_t)f.queue[j]];
+    rows_in -= h->b_n[(size_t)f.queue[j]];
+    const double t = total(j + 1);
+    if (t < (outside0 == 0.0 && leave == 0 ? 0.8 : 1.0) * us) {
+      us = t;
+      leave = j + 1;
+    }
+  }
+  for (size_t j = 0; j < leave; ++j) f.queued[(size_t)f.queue[j]] = 0;
+  f.queue.erase(f.queue.begin(), f.queue.begin() + (ptrdiff_t)leave);
+  return us;
+}
+
+// The best of 1 and 4 columns a group or, where no CU is shared, 8 and all. Few
+// tasks take one column each: the chains run side by side on CUs that would be idle
+// (16 matrices of 40 levels of 600 rows, 16 columns: 145 us against 541 in groups of
+// 4 and 1,307 with all columns of a matrix in one workgroup). With many deep ones 4
+// columns are best, as most levels (a few rows wide) then fit one wave (512 matrices
+// of 1,000 to 50,000 rows x 16 columns: 3.91 ms in groups of 4 with 256 threads,
+// 4.15 in groups of 8 with 512, 6.3 in groups of 2); where a workgroup has a CU to
+// itself and there are several for each CU, more (512 matrices of 600 levels of 8
+// rows, 16 columns, 1,024 threads: 1,220 us in groups of 4, 731 in one).
+// What stays slower than one task a matrix with all its columns and narrower
+// records: one column, a few matrices, levels of 600 to 1,500 rows, 1,024 threads
+// (16 matrices of 40 levels of 600 rows: 135 us against 111).
+BatchForm best_form(const sptrsv_ctx *h, int32_t nrhs, int32_t wg, int32_t cus) {
+  BatchForm best;
+  double best_us = 0.0;
+  int32_t last = 0;
+  for (int32_t nc : {1, 4, 8, nrhs}) {
+    if (nc > nrhs || nc == last) continue;
+    last = nc;
+    BatchForm f;
+    const double us = batch_form(h, nrhs, nc, wg, cus, f);
+    if (nc > 4 && !f.whole && wg < 1024) continue;
+    if (best_us == 0.0 || us < best_us) {
+      best_us = us;
+      best = std::move(f);
+    }
+  }
+  return best;
+}
+
+// Per-matrix LDS windows for nrhs (cached). The matrices of the queue have windows
+// as large as lets several workgroups share a CU (batch_lds), or as the widest
+// queued level needs; with no more tasks than CUs they take a whole CU's LDS (and
+// 1,024 threads). The others are solved level by level: narrow levels in thin runs,
+// the others one device-wide launch each, as a single plan's mode-0 schedule.
 sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream_t s) {
   if (h->b_win_nrhs == nrhs && h->b_win_wg == wg) return SPTRSV_OK;
   Plan &P = h->bat;
-  const int32_t nc = batch_cols(nrhs);
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const BatchForm form = best_form(h, nrhs, wg, std::max(cus, 1));
+  const int32_t nc = form.nc;
+  const std::vector<char> &fits = form.queued;
   P.h_win.clear();
   h->b_h_mwin.assign((size_t)h->b_nmat + 1, 0);
   h->b_wide.clear();
-  std::vector<char> fits((size_t)h->b_nmat, 1);
   std::vector<uint8_t> flag((size_t)h->b_nmat, 0);
-  int64_t cap = batch_lds(wg) - thin_ctl_bytes();
+  int64_t cap = form.whole ? thin_win_bytes() : batch_lds(wg) - thin_ctl_bytes();
   for (int32_t m = 0; m < h->b_nmat; ++m) {
-    int64_t rows = 0;
-    for (int64_t l = h->b_lvl_off[(size_t)m]; l < h->b_lvl_off[(size_t)m + 1]; ++l)
-      rows = std::max<int64_t>(rows, P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l]);
-    const int64_t need = thin_window_bytes(rows, 0, 1, nc, kWidths);
-    if (need > thin_win_bytes()) {
-      fits[(size_t)m] = 0;
-      flag[(size_t)m] = 1;
-    } else {
-      cap = std::max(cap, need);
-    }
+    flag[(size_t)m] = fits[(size_t)m] ? 0 : 1;
+    if (fits[(size_t)m]) cap = std::max(cap, thin_window_bytes(h->b_widest[(size_t)m], 0, 1, nc, kWidths));
   }
   h->b_ncol = nc;
+  h->b_wg = form.wg;
   h->b_lds = (int32_t)cap + thin_ctl_bytes();
   for (int32_t m = 0; m < h->b_nmat; ++m) {
     h->b_h_mwin[(size_t)m] = (int32_t)P.h_win.size();
     if (fits[(size_t)m])
-      cut_windows(P, (int32_t)h->b_lvl_off[(size_t)m], (int32_t)h->b_lvl_off[(size_t)m + 1], nc, wg, cap, true,
+      cut_windows(P, (int32_t)h->b_lvl_off[(size_t)m], (int32_t)h->b_lvl_off[(size_t)m + 1], nc, form.wg, cap, true,
                   P.h_win);
   }
   h->b_h_mwin[(size_t)h->b_nmat] = (int32_t)P.h_win.size();
@@ -113,7 +239,7 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
     bw.m = m;
     const int32_t l0 = (int32_t)h->b_lvl_off[(size_t)m], l1 = (int32_t)h->b_lvl_off[(size_t)m + 1];
     for (int32_t l = l0; l < l1; ++l) {
-      const bool thin = level_fits_window(P, l, nc);
+      const bool thin = level_in_windows(P, l, nrhs, nc);
       if (!bw.runs.empty() && thin && bw.runs.back().thin && bw.runs.back().l1 == l)
         bw.runs.back().l1 = l + 1;
       else
@@ -122,14 +248,11 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
     for (Run &r : bw.runs)
       if (r.thin) {
         r.wi = (int32_t)P.h_win.size();
-        r.nw = cut_windows(P, r.l0, r.l1, nc, wg, thin_win_bytes(), true, P.h_win);
+        r.nw = cut_windows(P, r.l0, r.l1, nc, form.wg, thin_win_bytes(), true, P.h_win);
       }
     h->b_wide.push_back(std::move(bw));
   }
-  // the persistent queue: the matrices that fit, in the analysis' order
-  std::vector<int32_t> q;
-  for (int32_t m : h->b_h_order)
-    if (fits[(size_t)m]) q.push_back(m);
+  const std::vector<int32_t> &q = form.queue;
   h->b_nq = (int32_t)q.size();
   HIPCHK(h, h->b_order.reserve(std::max<size_t>(q.size(), 1)));
   if (!q.empty()) HIPCHK(h, hipMemcpy(h->b_order.p, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice));
@@ -146,7 +269,7 @@ sptrsv_status_t batch_windows(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream
 }
 
 // The matrices taken out of the persistent launch, level by level.
-sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipStream_t s) {
+sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, hipStream_t s) {
   Plan &P = h->bat;
   const sptrsv_schedule_t d = default_schedule();
   for (const BatchWide &bw : h->b_wide)
@@ -155,7 +278,7 @@ sptrsv_status_t batch_wide_solves(sptrsv_ctx *h, int32_t nrhs, int32_t wg, hipSt
         const int32_t p0 = P.h_level_ptr[(size_t)r.l0];
         if (thin_piped(r.nw, kWaitTicks))
           HIPCHK(h, launch_fill_pending(p0, P.h_level_ptr[(size_t)r.l1] - p0, nrhs, nullptr, P.xp.p, s));
-        HIPCHK(h, launch_thin_run(wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
+        HIPCHK(h, launch_thin_run(h->b_wg, P.win.p + r.wi, r.nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
                                   h->b_ncol, kWaitTicks));
       } else
         HIPCHK(h, launch_wide_level(d.wide_threads, 1, P.h_level_ptr[(size_t)r.l0], P.h_level_ptr[(size_t)r.l1], nrhs,
@@ -321,14 +444,11 @@ sptrsv_status_t sptrsv_batch_analyze(sptrsv_handle_t h, int32_t nmat, const int3
   HIPCHK(h, hipStreamSynchronize(s));
   if (bits) return set_err(h, status_from_bits(bits), "batch: plan construction failed (bits 0x%x)", bits);
   STCHK(build_extra_hist(h, P, s));
-  // longest-processing-time order: deepest matrices first, then largest
-  std::vector<int32_t> order((size_t)nmat);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-    if (h->b_nlev[(size_t)a] != h->b_nlev[(size_t)b]) return h->b_nlev[(size_t)a] > h->b_nlev[(size_t)b];
-    return h->b_n[(size_t)a] > h->b_n[(size_t)b];
-  });
-  h->b_h_order = order;
+  h->b_widest.assign((size_t)nmat, 0);
+  for (int32_t m = 0; m < nmat; ++m)
+    for (int64_t l = h->b_lvl_off[(size_t)m]; l < h->b_lvl_off[(size_t)m + 1]; ++l)
+      h->b_widest[(size_t)m] =
+          std::max<int64_t>(h->b_widest[(size_t)m], P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l]);
   HIPCHK(h, h->b_q.alloc(2));
   HIPCHK(h, hipMemset(h->b_q.p, 0, 2 * sizeof(unsigned)));
   P.ready = true;
@@ -350,17 +470,17 @@ sptrsv_status_t sptrsv_batch_solve(sptrsv_handle_t h, int32_t nrhs, const double
   STCHK(batch_windows(h, nrhs, wg, s));
   if (h->b_nq > 0) {
     const int32_t tasks = h->b_nq * ((nrhs + h->b_ncol - 1) / h->b_ncol);
-    const int32_t grid = std::min(tasks, batch_resident_blocks(wg, h->b_lds));
+    const int32_t grid = std::min(tasks, batch_resident_blocks(h->b_wg, h->b_lds));
     ThinArgs ta = thin_args(P);
     ta.rio = RowsIO{d_b_cat, d_x_cat, P.perm.p, nullptr, nullptr, nullptr, 1, 1};
     ta.lds = h->b_lds;
-    HIPCHK(h, launch_batch_run(wg, h->b_nq, grid, h->b_order.p, h->b_mwin.p, P.win.p, nrhs, h->b_ncol,
+    HIPCHK(h, launch_batch_run(h->b_wg, h->b_nq, grid, h->b_order.p, h->b_mwin.p, P.win.p, nrhs, h->b_ncol,
                                h->b_row_off_d.p, ta, h->b_q.p, h->d_err.p, s));
   }
   if (!h->b_wide.empty()) {
     HIPCHK(h, launch_batch_gather(P.n, nrhs, d_b_cat, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p,
                                   h->b_wide_flag.p, P.bp.p, s));
-    STCHK(batch_wide_solves(h, nrhs, wg, s));
+    STCHK(batch_wide_solves(h, nrhs, s));
     HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p,
                                    h->b_wide_flag.p, d_x_cat, s));
   }
@@ -382,10 +502,10 @@ sptrsv_status_t sptrsv_batch_solve_looped(sptrsv_handle_t h, int32_t nrhs, const
   for (int32_t m = 0; m < h->b_nmat; ++m) {
     const int32_t wi = h->b_h_mwin[(size_t)m], nw = h->b_h_mwin[(size_t)m + 1] - wi - 1;
     if (nw >= 1)
-      HIPCHK(h, launch_thin_run(wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
+      HIPCHK(h, launch_thin_run(h->b_wg, P.win.p + wi, nw, nrhs, thin_args(P), h->d_err.p, s, nullptr, 0.f,
                                 h->b_ncol, kWaitTicks));
   }
-  STCHK(batch_wide_solves(h, nrhs, wg, s));
+  STCHK(batch_wide_solves(h, nrhs, s));
   HIPCHK(h, launch_batch_scatter(P.n, nrhs, P.xp.p, h->b_mat_of_row.p, h->b_row_off_d.p, P.iperm.p, nullptr, d_x_cat,
                                  s));
   return SPTRSV_OK;

@@ -242,11 +242,11 @@ struct sptrsv_ctx {
   DArr<int64_t> b_row_off_d;           // [nmat+1]
   DArr<unsigned> b_q;                  // persistent-launch queue counters
   std::vector<int32_t> b_h_mwin;       // window index of each matrix's run, for the cached nrhs
-  std::vector<int32_t> b_h_order;      // longest-processing-time order of all matrices
+  std::vector<int64_t> b_widest;       // rows of each matrix's widest level
   int32_t b_nq = 0;                    // matrices in the persistent queue (b_order) for the cached nrhs
   std::vector<BatchWide> b_wide;       // the others
   DArr<uint8_t> b_wide_flag;           // per matrix: among b_wide
-  int32_t b_ncol = 1, b_lds = 0;       // columns per group and LDS bytes of the persistent launch
+  int32_t b_ncol = 1, b_lds = 0, b_wg = 512;  // columns per group, LDS bytes and threads of the persistent launch
   int32_t b_win_nrhs = -1, b_win_wg = -1;
   std::vector<Graph> graphs;
   // live profile of solve launches
