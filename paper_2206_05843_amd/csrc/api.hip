@@ -414,8 +414,9 @@ static sptrsv_status_t build_overlap(sptrsv_ctx *h, Plan &P, int32_t nrhs, const
 // Measured (one column, us; windows | a wait per row; off-diagonals per level):
 // power law n = 200,000 918 | 2,160 (740), 400,000 1,388 | 2,535 (1,370),
 // 800,000 2,390 | 3,068 (2,340), 1.6M 4,645 | 3,963 (3,700); torso2-like
-// n = 60,000 504 | 674 (1,030), 116,000 791 | 710 (1,990); 2D stencil 1000^2
-// 1,103 | 2,149 (1,000). The line lies at 1,600; every level must fit a window.
+// n = 60,000 504 | 674 (1,030), 90,000 666 | 686 (1,386), 116,000 791 | 710 (1,990);
+// 2D stencil 1000^2 1,103 | 2,149 (1,000). The line lies at 1,600; every level must
+// fit a window.
 constexpr int64_t kFreeDeps = 1600;
 constexpr int32_t kFreeThreads = 1024;  // 512: 1.25 times slower on the power law, 256: 1.75 times
 static bool free_in_windows(const Plan &P) {
@@ -423,6 +424,19 @@ static bool free_in_windows(const Plan &P) {
   for (int32_t l = 0; l < P.nlev; ++l)
     if (!level_fits_window(P, l, 1)) return false;
   return true;
+}
+
+// With several columns every column is a chain of windows of its own, which reads
+// the images again and fetches a line of x for fewer values, while a wait per row
+// is shared by the row's columns; so windows must save more hand-overs to pay: at
+// least so many levels a window. Measured on the matrices above and others (time
+// row by row over time in windows; levels a window): 2 columns 0.89 (8.4), 1.05
+// (7.1), 1.16 (10.6), 1.20 (11.7); 4 columns 0.80 (8.9), 1.07 (10.6), 1.08 (11.7),
+// 1.26 (14.4); 8 columns 0.94 (11.7), 1.07 (14.7), 1.12 (14.4), 1.57 (22); 16
+// columns 0.82 (14.7), 1.03 (14.4), 1.40 (22); 32 columns 0.66 (14.7), 1.26 (22),
+// 2.5 (26); 64 columns 1.06 (14.3), 1.19 (22).
+static int64_t free_levels_per_window(int32_t nrhs) {
+  return nrhs <= 1 ? 0 : nrhs <= 2 ? 10 : nrhs <= 4 ? 11 : nrhs <= 8 ? 14 : 20;
 }
 
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s) {
@@ -480,6 +494,10 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
     if (!r.thin) continue;
     r.wi = (int32_t)P.h_win.size();
     r.nw = cut_windows(P, r.l0, r.l1, gw, r.free ? kFreeThreads : sc.wg_threads, thin_win_bytes(), false, P.h_win);
+  }
+  if (freew && P.nlev < free_levels_per_window(nrhs) * P.runs[0].nw) {  // row by row: no runs
+    P.runs.clear();
+    P.h_win.clear();
   }
   P.runs_nrhs = -1;  // until the images are built
   STCHK(build_images(h, P, gw, s));

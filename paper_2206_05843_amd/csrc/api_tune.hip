@@ -140,13 +140,16 @@ sptrsv_status_t autotune(sptrsv_ctx *h, int which, int32_t nrhs, bool rows, hipS
     *ms = t[1];
     return true;
   };
+  bool windows = false;  // mode 3 takes LDS windows here: its grid sizes are one schedule
   for (const sptrsv_schedule_t &cand : cands) {
     float ms = 0.f;
+    if (!batch && cand.mode == 3 && windows) continue;
     if (time_cand(cand, &ms) && ms < best) {
       best = ms;
       best_s = cand;
     }
     if (st != SPTRSV_OK) break;
+    windows = windows || (!batch && cand.mode == 3 && !P->runs.empty());
   }
   // the workgroup size of the wide-level launches, around the best split
   // schedule (smaller workgroups spread a level over more CUs)
