@@ -466,7 +466,8 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
       // finished ones taken in order
       constexpr int kP = 2;
       unsigned spins = 0;
-      WaitLimit wait{t0, !whole_launch};
+      int32_t rest0 = -1;  // dependencies left at the last look at the clock
+      WaitLimit wait{t0, false};
       for (;;) {
         bool left[kI], any = false, moved = false;
         double wv[kI][kP];
@@ -506,12 +507,17 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
           moved = moved || done > 0;
           if (done > 0 && e0[j] == e1[j]) v[(int64_t)(base + j * WG + tid)] = acc[j];
         }
-        const bool step = __ballot(moved) != 0ull;
-        if (!step) __builtin_amdgcn_s_sleep(kPollSleep);
-        wait.moved = wait.moved || (step && !whole_launch);
-        if ((++spins & 63u) == 0u && wait.expired(wall_clock64(), tlimit)) {
-          bits |= EB_TIMEOUT;
-          break;
+        if (__ballot(moved) == 0ull) __builtin_amdgcn_s_sleep(kPollSleep);
+        if ((++spins & 63u) == 0u) {
+          int32_t rest = 0;
+#pragma unroll
+          for (int j = 0; j < kI; ++j) rest += e1[j] - e0[j];
+          wait.moved = !whole_launch && __ballot(rest != rest0) != 0ull;
+          rest0 = rest;
+          if (wait.expired(wall_clock64(), tlimit)) {
+            bits |= EB_TIMEOUT;
+            break;
+          }
         }
       }
     }
