@@ -518,16 +518,18 @@ sptrsv_status_t sptrsv_level_times(sptrsv_handle_t h, int which, int32_t nrhs, c
  * the learned policy from probabilities (ASYNC). */
 sptrsv_status_t sptrsv_mlp_mask(const float *d_prob, int32_t nlev, float threshold, uint8_t *d_mask, hipStream_t s);
 /* Per-level finish times under the synchronisation-free executor (the
- * schedule the autotuner picks on power-law matrices; with its tuned grid when
- * the handle holds a tuned mode-3 schedule for this nrhs): one solve in which
- * every item records the device wall clock when its value is written, then
- * d_times[l] (device, nlev floats) = latest stamp of level l - earliest stamp
- * of the solve, in ns. A level's share of the solve is the growth of the
- * running maximum of these times across it. b as in sptrsv_solve (ld = n); the
- * solution is discarded. Allocates 8 n nrhs bytes for the stamps.
- * Synchronous. These times label levels when the policy is trained on the
- * executor it will run under (Sec. III.A: a rewrite pays only where it shortens
- * the solve). */
+ * schedule the autotuner picks on power-law matrices), in the form that a mode-3
+ * solve of this matrix and nrhs takes: LDS windows, or row by row (with its tuned
+ * grid when the handle holds a tuned mode-3 schedule for this nrhs). One solve in
+ * which the device wall clock is recorded at the end of every level of a window,
+ * or when every item's value is written; then d_times[l] (device, nlev floats) =
+ * latest stamp of level l - earliest stamp of the solve, in ns. A level's share of
+ * the solve is the growth of the running maximum of these times across it. b as in
+ * sptrsv_solve (ld = n); the solution is discarded, the plan's schedule and
+ * captured graphs stay. Allocates 8 n nrhs bytes for the stamps of single items, or
+ * the windows' tables. Synchronous. These times label levels when the policy is
+ * trained on the executor it will run under (Sec. III.A: a rewrite pays only where
+ * it shortens the solve). */
 sptrsv_status_t sptrsv_level_finish_times(sptrsv_handle_t h, int which, int32_t nrhs, const double *d_b,
                                           float *d_times, hipStream_t s);
 

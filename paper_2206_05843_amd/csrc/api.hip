@@ -439,6 +439,52 @@ static int64_t free_levels_per_window(int32_t nrhs) {
   return nrhs <= 1 ? 0 : nrhs <= 2 ? 10 : nrhs <= 4 ? 11 : nrhs <= 8 ? 14 : 20;
 }
 
+// Appends the windows of the synchronisation-free executor for nrhs columns and
+// their terminator to out; returns their number, 0 where it works row by row.
+static int32_t cut_free(const Plan &P, int32_t nrhs, std::vector<int4> &out) {
+  if (!free_in_windows(P)) return 0;
+  const size_t first = out.size();
+  const int32_t nw = cut_windows(P, 0, P.nlev, 1, kFreeThreads, thin_win_bytes(), false, out);
+  if (P.nlev >= free_levels_per_window(nrhs) * nw) return nw;
+  out.resize(first);
+  return 0;
+}
+
+// The finish times of the levels (wall clock, the latest over the columns, into
+// finish[l]; the earliest of level 0 into finish[nlev]) of one solve of bp by the
+// synchronisation-free executor in its windows; *windows false: it works row by
+// row, nothing is done. The windows are built apart: the plan's own runs, which a
+// captured graph may hold, stay. Synchronous.
+sptrsv_status_t stamp_free_windows(sptrsv_ctx *h, Plan &P, int32_t nrhs, unsigned long long *finish, bool *windows,
+                                   hipStream_t s) {
+  std::vector<int4> h_win;
+  const int32_t nw = cut_free(P, nrhs, h_win);
+  *windows = nw > 0;
+  if (nw == 0) return SPTRSV_OK;
+  DArr<int4> win;
+  DArr<uint4> img;
+  DArr<int32_t> ext_ptr;
+  DArr<ExtDep> ext;
+  auto swap_all = [&] {
+    std::swap(P.h_win, h_win);
+    std::swap(P.win, win);
+    std::swap(P.img, img);
+    std::swap(P.ext_ptr, ext_ptr);
+    std::swap(P.ext, ext);
+  };
+  swap_all();
+  sptrsv_status_t st = build_images(h, P, 1, s);
+  if (st == SPTRSV_OK) {
+    hipError_t e = launch_fill_pending(0, P.n, nrhs, nullptr, P.xp.p, s);
+    if (e == hipSuccess)
+      e = launch_thin_stamped(P.win.p, nw, nrhs, thin_args(P), h->d_err.p, s, finish, P.nlev, wait_limit(h));
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) st = set_err(h, SPTRSV_ERR_HIP, "stamped windows: %s", hipGetErrorString(e));
+  }
+  swap_all();
+  return st;
+}
+
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s) {
   P.runs.clear();
   P.h_win.clear();
@@ -446,11 +492,12 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   const int64_t thr = sc.thin_rows;
   auto rows_of = [&](int32_t l) -> int64_t { return P.h_level_ptr[l + 1] - P.h_level_ptr[l]; };
   const bool flow = sc.mode == 4;
-  const bool freew = sc.mode == 3 && free_in_windows(P);
-  const int32_t gw = freew ? 1 : thin_width(sc, nrhs);  // columns per thin-run workgroup
-  if (freew) {
+  const int32_t nfree = sc.mode == 3 ? cut_free(P, nrhs, P.h_win) : 0;
+  const int32_t gw = nfree > 0 ? 1 : thin_width(sc, nrhs);  // columns per thin-run workgroup
+  if (nfree > 0) {
     Run r{0, P.nlev, true};
     r.free = true;
+    r.nw = nfree;
     P.runs.push_back(r);
   }
   for (int32_t l = 0; l < P.nlev && sc.mode != 3; ++l) {
@@ -491,13 +538,9 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
     P.runs.swap(cut);
   }
   for (Run &r : P.runs) {
-    if (!r.thin) continue;
+    if (!r.thin || r.free) continue;
     r.wi = (int32_t)P.h_win.size();
-    r.nw = cut_windows(P, r.l0, r.l1, gw, r.free ? kFreeThreads : sc.wg_threads, thin_win_bytes(), false, P.h_win);
-  }
-  if (freew && P.nlev < free_levels_per_window(nrhs) * P.runs[0].nw) {  // row by row: no runs
-    P.runs.clear();
-    P.h_win.clear();
+    r.nw = cut_windows(P, r.l0, r.l1, gw, sc.wg_threads, thin_win_bytes(), false, P.h_win);
   }
   P.runs_nrhs = -1;  // until the images are built
   STCHK(build_images(h, P, gw, s));

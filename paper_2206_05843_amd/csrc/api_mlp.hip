@@ -121,12 +121,18 @@ sptrsv_status_t sptrsv_level_finish_times(sptrsv_handle_t h, int which, int32_t 
   const auto tk = P->tuned.find(nrhs);
   const int32_t blocks = tk != P->tuned.end() && tk->second.mode == 3 ? tk->second.wide_grid : 0;
   DArr<unsigned long long> stamp, lmax;
-  HIPCHK(h, stamp.alloc((size_t)P->n * (size_t)nrhs));
   HIPCHK(h, lmax.alloc((size_t)P->nlev + 1));
+  HIPCHK(h, hipMemsetAsync(lmax.p, 0, sizeof(unsigned long long) * (size_t)P->nlev, s));
   HIPCHK(h, hipMemsetAsync(lmax.p + P->nlev, 0xff, sizeof(unsigned long long), s));
   STCHK(gather_b(h, *P, nrhs, d_b, P->n, P->bp.p, nullptr, s));
-  HIPCHK(h, launch_syncfree(P->n, nrhs, P->srp.p, P->sci.p, P->sva.p, P->sdg.p, P->bp.p, P->xp.p, P->sf_ticket.p,
-                            h->d_err.p, blocks, wait_limit(h), s, stamp.p));
+  // the form a mode-3 solve of this matrix and nrhs takes
+  bool windows = false;
+  STCHK(stamp_free_windows(h, *P, nrhs, lmax.p, &windows, s));
+  if (!windows) {
+    HIPCHK(h, stamp.alloc((size_t)P->n * (size_t)nrhs));
+    HIPCHK(h, launch_syncfree(P->n, nrhs, P->srp.p, P->sci.p, P->sva.p, P->sdg.p, P->bp.p, P->xp.p, P->sf_ticket.p,
+                              h->d_err.p, blocks, wait_limit(h), s, stamp.p));
+  }
   HIPCHK(h, launch_stamp_levels(P->nlev, nrhs, P->level_ptr.p, stamp.p, lmax.p, lmax.p + P->nlev, ns_per_tick,
                                 d_times, s));
   HIPCHK(h, hipStreamSynchronize(s));

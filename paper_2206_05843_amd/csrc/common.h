@@ -454,6 +454,11 @@ hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, 
                            hipStream_t s, float *times, float ns_per_tick, int32_t ng, unsigned long long tlimit,
                            bool whole_launch = false);
 bool thin_piped(int32_t nwin, unsigned long long tlimit);
+// The synchronisation-free executor's windows with the wall clock at the end of
+// every level: finish[l] = the latest over the columns, finish[nlev] = the
+// earliest of level 0 (zero and ~0 before the launch).
+hipError_t launch_thin_stamped(const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err, hipStream_t s,
+                               unsigned long long *finish, int32_t nlev, unsigned long long tlimit);
 // x of positions [p0, p0 + rows) = kPendingX (perm: x by caller rows)
 hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s);
 hipError_t launch_fill_ell(int32_t n, const int32_t *srp, const int32_t *sci, const double *sva, int4 *ell_c,
@@ -577,6 +582,8 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
                     std::vector<int4> &out);
 sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s);
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s);
+sptrsv_status_t stamp_free_windows(sptrsv_ctx *h, Plan &P, int32_t nrhs, unsigned long long *finish, bool *windows,
+                                   hipStream_t s);
 // ncol: right-hand sides per window (slots are premultiplied by it)
 sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s);
 sptrsv_status_t ensure_work(sptrsv_ctx *h, Plan &P, int32_t nrhs);
@@ -601,7 +608,8 @@ hipError_t launch_syncfree(int32_t n, int32_t nrhs, const int32_t *srp, const in
                            int32_t blocks, unsigned long long tlimit, hipStream_t s,
                            unsigned long long *stamp = nullptr);
 // times[l] = (latest stamp of level l - earliest stamp of all) * ns_per_tick;
-// lmax has nlev entries, *gmin must hold ~0 before the call.
+// lmax has nlev entries, *gmin must hold ~0 before the call. stamp null: lmax and
+// *gmin hold the levels' latest and the earliest stamp already.
 hipError_t launch_stamp_levels(int32_t nlev, int32_t nrhs, const int32_t *level_ptr, const unsigned long long *stamp,
                                unsigned long long *lmax, unsigned long long *gmin, float ns_per_tick, float *times,
                                hipStream_t s);

@@ -217,8 +217,9 @@ hipError_t launch_stamp_levels(int32_t nlev, int32_t nrhs, const int32_t *level_
                                unsigned long long *lmax, unsigned long long *gmin, float ns_per_tick, float *times,
                                hipStream_t s) {
   if (nlev <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_stamp_level_max, dim3(nlev < 4096 ? nlev : 4096), dim3(256), 0, s, nlev, nrhs, level_ptr,
-                     stamp, lmax, gmin);
+  if (stamp)
+    hipLaunchKernelGGL(k_stamp_level_max, dim3(nlev < 4096 ? nlev : 4096), dim3(256), 0, s, nlev, nrhs, level_ptr,
+                       stamp, lmax, gmin);
   hipLaunchKernelGGL(k_stamp_finish, dim3((nlev + 255) / 256), dim3(256), 0, s, nlev, lmax, gmin, ns_per_tick, times);
   return hipGetLastError();
 }

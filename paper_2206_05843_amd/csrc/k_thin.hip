@@ -72,8 +72,17 @@ struct Ctl {
 // with addresses of their own (about 110 and 280 ns a level); the 2D stencil's
 // 4,602 levels 888 us against 1,130, its rewritten form 2.69 ms against 2.95.
 // win[i] = {first level, flags}; the run's last entry holds the end level.
-// kTimed (used only to label levels for the learned policy): thread 0 stamps the
-// device wall clock around every level and writes per-level times (ns).
+// kTime (used only to label levels for the learned policy): kDurations: thread 0
+// stamps the device wall clock around every level and writes per-level times
+// (ns); kFinish: it records the clock at the end of every level, the latest over
+// the columns.
+enum TimeKind { kNoTimes, kDurations, kFinish };
+struct Times {
+  float *ns;                   // kDurations, per level
+  float ns_per_tick;
+  unsigned long long *finish;  // kFinish, per level, then the earliest of level 0
+  int32_t nlev;
+};
 constexpr int kBatch = 4;
 
 // x of a row not yet solved, where other workgroups wait for it: a signalling
@@ -186,8 +195,8 @@ __device__ __forceinline__ void put_x(double *p, double x) {
 // is solved, to byte gmul times its place in the window behind gx, for the
 // workgroups that wait for it. tid: the thread's number, counted from the first
 // wave to work.
-template <int WG, int kGw, int K, bool kOvf, bool kOneWave, bool kTimed, bool kNow>
-__device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_t lA, float *times, float ns_per_tick,
+template <int WG, int kGw, int K, bool kOvf, bool kOneWave, int kTime, bool kNow>
+__device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_t lA, const Times &T,
                                              unsigned long long t_prev, float p1_per_row, double *gx, uint32_t gmul,
                                              int tid) {
   constexpr bool kOne = kGw == 1;
@@ -198,10 +207,15 @@ __device__ __forceinline__ void solve_levels(const Win &W, int32_t flags, int32_
     if constexpr (kNow) put_x(reinterpret_cast<double *>(reinterpret_cast<char *>(gx) + (uint64_t)at * gmul), x);
   };
   auto stamp = [&](int32_t lg) {
-    if (kTimed && tid == 0) {
+    if (kTime != kNoTimes && tid == 0) {
       const unsigned long long now = wall_clock64();
-      times[lA + lg] = (float)(now - t_prev) * ns_per_tick + p1_per_row * (float)(lv[lg + 1] - lv[lg]);
-      t_prev = now;
+      if (kTime == kDurations) {
+        T.ns[lA + lg] = (float)(now - t_prev) * T.ns_per_tick + p1_per_row * (float)(lv[lg + 1] - lv[lg]);
+        t_prev = now;
+      } else {
+        atomicMax(T.finish + lA + lg, now);
+        if (lA + lg == 0) atomicMin(T.finish + T.nlev, now);
+      }
     }
   };
   if (kOneWave || (flags & 2)) {
@@ -328,11 +342,11 @@ constexpr int kPollSleep = 1;
 // whole_launch it does so tlimit ticks after t0, however it moved.
 // rot: the first thread of the wave that solves the levels of at most 64 items.
 // touch_next: the other waves bring the next window's data nearer meanwhile.
-template <int WG, int kGw, bool kTimed, bool kSplit, bool kPoll>
+template <int WG, int kGw, int kTime, bool kSplit, bool kPoll>
 __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restrict__ win, int32_t w, int32_t nrhs,
-                                            int32_t ng, int32_t c0_arg, const ThinArgs &A, float *times,
-                                            float ns_per_tick, unsigned long long t0, unsigned long long tlimit,
-                                            bool whole_launch, int rot, bool touch_next) {
+                                            int32_t ng, int32_t c0_arg, const ThinArgs &A, const Times &T,
+                                            unsigned long long t0, unsigned long long tlimit, bool whole_launch,
+                                            int rot, bool touch_next) {
   constexpr bool kOne = kGw == 1;
   const int32_t nr = kOne && !kSplit ? 1 : nrhs;  // stride of the global vectors
   const int32_t gw = kGw > 0 ? kGw : ng;          // columns in LDS and per row of items
@@ -352,7 +366,7 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
   int bits = 0;
   unsigned long long t_w0 = 0, t_prev = 0;
   float p1_per_row = 0.f;
-  if (kTimed && tid == 0) t_w0 = wall_clock64();
+  if (kTime == kDurations && tid == 0) t_w0 = wall_clock64();
   const int4 W = win[w];
   const int32_t lA = W.x, lB = win[w + 1].x, flags = W.y;
   const int32_t P0 = level_ptr[lA], P1 = level_ptr[lB];
@@ -523,9 +537,9 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
     }
   }
   __syncthreads();
-  if (kTimed && tid == 0) {
+  if (kTime == kDurations && tid == 0) {
     t_prev = wall_clock64();
-    p1_per_row = R > 0 ? (float)(t_prev - t_w0) * ns_per_tick / (float)R : 0.f;
+    p1_per_row = R > 0 ? (float)(t_prev - t_w0) * T.ns_per_tick / (float)R : 0.f;
   }
   // x goes to global memory as it is solved where a window's place there is a
   // fixed multiple of its place in LDS (all columns, or one of them), except
@@ -538,17 +552,14 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
   const int vt = (tid + WG - rot) & (WG - 1);
   unsigned sink = 0;
   if (touch_next && vt >= 64) sink = touch_window(win, w + 1, gw, c0, A, vt - 64, WG - 64);
-#define LEVELS(K, OVF)                                                                                               \
-  if (flags & 1) {                                                                                                   \
-    if (vt < 64)                                                                                                     \
-      solve_levels<WG, kGw, K, OVF, true, kTimed, false>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,  \
-                                                          gmul, vt);                                                 \
-  } else if (kPoll && now) {                                                                                         \
-    solve_levels<WG, kGw, K, OVF, false, kTimed, kPoll>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,   \
-                                                         gmul, vt);                                                  \
-  } else {                                                                                                           \
-    solve_levels<WG, kGw, K, OVF, false, kTimed, false>(X, flags, lA, times, ns_per_tick, t_prev, p1_per_row, gx,   \
-                                                         gmul, vt);                                                  \
+#define LEVELS(K, OVF)                                                                                             \
+  if (flags & 1) {                                                                                                 \
+    if (vt < 64)                                                                                                   \
+      solve_levels<WG, kGw, K, OVF, true, kTime, false>(X, flags, lA, T, t_prev, p1_per_row, gx, gmul, vt);       \
+  } else if (kPoll && now) {                                                                                       \
+    solve_levels<WG, kGw, K, OVF, false, kTime, kPoll>(X, flags, lA, T, t_prev, p1_per_row, gx, gmul, vt);        \
+  } else {                                                                                                         \
+    solve_levels<WG, kGw, K, OVF, false, kTime, false>(X, flags, lA, T, t_prev, p1_per_row, gx, gmul, vt);        \
   }
   if (kc == 0 && NO == 0) {
     LEVELS(2, false)
@@ -587,14 +598,14 @@ __device__ __forceinline__ int solve_window(char *lds_raw, const int4 *__restric
 
 // The windows [win, win + nwin) of one thin run one after another, by the
 // calling workgroup.
-template <int WG, int kGw, bool kTimed, bool kSplit = false>
+template <int WG, int kGw, int kTime, bool kSplit = false>
 __device__ __forceinline__ int thin_run_body(char *lds_raw, const int4 *__restrict__ win, int32_t nwin, int32_t nrhs,
-                                             int32_t ng, int32_t c0, const ThinArgs &A, float *times,
-                                             float ns_per_tick, int rot = 0, bool touch = false) {
+                                             int32_t ng, int32_t c0, const ThinArgs &A, const Times &T, int rot = 0,
+                                             bool touch = false) {
   int bits = 0;
   for (int32_t w = 0; w < nwin && !(bits & EB_ARG); ++w)
-    bits |= solve_window<WG, kGw, kTimed, kSplit, false>(lds_raw, win, w, nrhs, ng, c0, A, times, ns_per_tick, 0, 0,
-                                                         false, rot, touch && w + 1 < nwin);
+    bits |= solve_window<WG, kGw, kTime, kSplit, false>(lds_raw, win, w, nrhs, ng, c0, A, T, 0, 0, false, rot,
+                                                        touch && w + 1 < nwin);
   return bits;
 }
 
@@ -604,13 +615,12 @@ __device__ __forceinline__ int32_t first_col(int32_t g, int32_t nrhs, int32_t ng
 
 // One thin run in one workgroup per group of ng columns. For runs of one window, and for the labelling
 // runs that time levels.
-template <int WG, bool kOne, bool kTimed = false, bool kSplit = false>
+template <int WG, bool kOne, int kTime = kNoTimes, bool kSplit = false>
 __global__ __launch_bounds__(WG) void k_thin_run(const int4 *__restrict__ win, int32_t nwin, int32_t nrhs, int32_t ng,
-                                                 ThinArgs A, int *err, float *times, float ns_per_tick) {
+                                                 ThinArgs A, int *err, Times T) {
   extern __shared__ __align__(16) char lds_raw[];
-  const int bits = thin_run_body<WG, kOne ? 1 : 0, kTimed, kSplit>(lds_raw, win, nwin, nrhs, ng,
-                                                           first_col((int32_t)blockIdx.x, nrhs, ng), A, times,
-                                                           ns_per_tick);
+  const int bits = thin_run_body<WG, kOne ? 1 : 0, kTime, kSplit>(
+      lds_raw, win, nwin, nrhs, ng, first_col((int32_t)blockIdx.x, nrhs, ng), A, T);
   if (bits) atomicOr(err, bits);
 }
 
@@ -634,10 +644,10 @@ __global__ __launch_bounds__(WG) void k_thin_run(const int4 *__restrict__ win, i
 // solve against 2.69 with one workgroup (and four that prefetched into its L2),
 // the 300^2 one with its 4,001-row tail 0.74 against 0.89.
 constexpr int kXcd = 8;
-template <int WG, bool kOne, bool kSplit>
+template <int WG, bool kOne, bool kSplit, int kTime = kNoTimes>
 __global__ __launch_bounds__(WG) void k_thin_pipe(const int4 *__restrict__ win, int32_t nwin, int32_t nrhs, int32_t ng,
                                                   int32_t nlane, ThinArgs A, int *err, unsigned long long tlimit,
-                                                  int whole_launch) {
+                                                  int whole_launch, Times T) {
   extern __shared__ __align__(16) char lds_raw[];
   const int32_t lane = (int32_t)blockIdx.x % kXcd;
   if (lane >= nlane) return;
@@ -655,8 +665,8 @@ __global__ __launch_bounds__(WG) void k_thin_pipe(const int4 *__restrict__ win, 
     __syncthreads();
     if (t >= nwin * mine) break;
     const int32_t w = t / mine, g = lane + nlane * (t - w * mine);
-    bits |= solve_window<WG, kOne ? 1 : 0, false, kSplit, true>(lds_raw, win, w, nrhs, ng, first_col(g, nrhs, ng), A, nullptr, 0.f, t0,
-                                                        tlimit, whole_launch != 0, 0, false);
+    bits |= solve_window<WG, kOne ? 1 : 0, kTime, kSplit, true>(lds_raw, win, w, nrhs, ng, first_col(g, nrhs, ng), A, T,
+                                                                t0, tlimit, whole_launch != 0, 0, false);
   }
   if (bits) atomicOr(err, bits);
   __syncthreads();
@@ -738,8 +748,8 @@ __global__ __launch_bounds__(WG, 4) void k_batch_run(int32_t nmat, const int32_t
     A.rio.x = x0 + (nrhs - 1) * off;
     A.rio.rs = 1;
     A.rio.cs = n;
-    bits |= thin_run_body<WG, kGw, false, true>(lds_raw, win + mwin[m], mwin[m + 1] - mwin[m] - 1, nrhs, ng,
-                                                 first_col(t - i * groups, nrhs, ng), A, nullptr, 0.f, rot, true);
+    bits |= thin_run_body<WG, kGw, kNoTimes, true>(lds_raw, win + mwin[m], mwin[m + 1] - mwin[m] - 1, nrhs, ng,
+                                                   first_col(t - i * groups, nrhs, ng), A, Times{}, rot, true);
   }
   if (threadIdx.x == 0) {
     if (bits) atomicOr(err, bits);
@@ -760,7 +770,7 @@ void set_lds_attr() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<WG, kOne>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<WG, kOne, false, true>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<WG, kOne, kNoTimes, true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
 }
 
@@ -782,15 +792,41 @@ void solve_kernels_init() {
   set_lds_attr<512, false>();
   set_lds_attr<1024, true>();
   set_lds_attr<1024, false>();
-  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<512, true, true>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<512, true, kDurations>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<512, false, true>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_run<512, false, kDurations>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_pipe<1024, true, true, kFinish>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
 }
 
 hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_pending, dim3(grid_for(rows * nr, 256, 4096)), dim3(256), 0, s, p0, rows, nr, perm, x);
+  return hipGetLastError();
+}
+
+namespace {
+// A spread run: lanes (XCDs) and workgroups. kPipeDepth workgroups per chain on
+// the chain's XCD; not more than hold windows, nor more than its CUs (a workgroup
+// takes a CU's LDS).
+struct PipeGrid {
+  int32_t nlane;
+  unsigned blocks;
+};
+PipeGrid pipe_grid(int32_t nwin, int32_t groups) {
+  const int32_t nlane = groups < kXcd ? groups : kXcd;
+  const int32_t chains = (groups + nlane - 1) / nlane;
+  const int64_t depth = std::min<int64_t>({(int64_t)kPipeDepth * chains, (int64_t)nwin * chains, 32});
+  return PipeGrid{nlane, (unsigned)depth * kXcd};
+}
+}  // namespace
+
+hipError_t launch_thin_stamped(const int4 *win, int32_t nwin, int32_t nrhs, const ThinArgs &a, int *err, hipStream_t s,
+                               unsigned long long *finish, int32_t nlev, unsigned long long tlimit) {
+  const PipeGrid g = pipe_grid(nwin, nrhs);
+  hipLaunchKernelGGL((k_thin_pipe<1024, true, true, kFinish>), dim3(g.blocks), dim3(1024), kWinBytes, s, win, nwin,
+                     nrhs, 1, g.nlane, a, err, tlimit, 1, Times{nullptr, 0.f, finish, nlev});
   return hipGetLastError();
 }
 
@@ -802,28 +838,24 @@ hipError_t launch_thin_run(int wg, const int4 *win, int32_t nwin, int32_t nrhs, 
   const bool split = ng < nrhs;
   const int32_t groups = (nrhs + ng - 1) / ng;
   if (times) {  // labelling runs only: 512 threads
+    const Times T{times, ns_per_tick, nullptr, 0};
     if (one)
-      hipLaunchKernelGGL((k_thin_run<512, true, true>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, a, err,
-                         times, ns_per_tick);
+      hipLaunchKernelGGL((k_thin_run<512, true, kDurations>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, a,
+                         err, T);
     else
-      hipLaunchKernelGGL((k_thin_run<512, false, true>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng, a,
-                         err, times, ns_per_tick);
+      hipLaunchKernelGGL((k_thin_run<512, false, kDurations>), dim3(1), dim3(512), kWinBytes, s, win, nwin, nrhs, ng,
+                         a, err, T);
     return hipGetLastError();
   }
-  // several windows: spread over kPipeDepth workgroups per chain on the chain's
-  // XCD; not more than hold windows, nor more than its CUs (a workgroup takes a
-  // CU's LDS)
   const bool pipe = thin_piped(nwin, tlimit);
-  const int32_t nlane = groups < kXcd ? groups : kXcd;
-  const int32_t chains = (groups + nlane - 1) / nlane;
-  const int64_t depth = std::min<int64_t>({(int64_t)kPipeDepth * chains, (int64_t)nwin * chains, 32});
+  const PipeGrid g = pipe_grid(nwin, groups);
 #define THIN(W, ONE, SPLIT)                                                                                       \
   if (pipe)                                                                                                       \
-    hipLaunchKernelGGL((k_thin_pipe<W, ONE, SPLIT>), dim3((unsigned)depth * kXcd), dim3(W), kWinBytes, s, win,     \
-                       nwin, nrhs, ng, nlane, a, err, tlimit, whole_launch ? 1 : 0);                                                  \
+    hipLaunchKernelGGL((k_thin_pipe<W, ONE, SPLIT>), dim3(g.blocks), dim3(W), kWinBytes, s, win, nwin, nrhs, ng,   \
+                       g.nlane, a, err, tlimit, whole_launch ? 1 : 0, Times{});                                   \
   else                                                                                                            \
-    hipLaunchKernelGGL((k_thin_run<W, ONE, false, SPLIT>), dim3((unsigned)groups), dim3(W), kWinBytes, s, win,     \
-                       nwin, nrhs, ng, a, err, (float *)nullptr, 0.f);
+    hipLaunchKernelGGL((k_thin_run<W, ONE, kNoTimes, SPLIT>), dim3((unsigned)groups), dim3(W), kWinBytes, s, win,  \
+                       nwin, nrhs, ng, a, err, Times{});
 #define THINW(W)              \
   if (split && one) {         \
     THIN(W, true, true)       \

@@ -10,9 +10,10 @@ fastest in geometric mean, each variant autotuned.
 
 Data. For each seeded power-law training matrix (n ~ U[50k, 500k]) the
 library times one synchronisation-free solve of L and one of L' after the
-(B, C) rewrite -- the executor the autotuner picks on these matrices -- with
-every item stamping the device clock when its value is written
-(sptrsv_level_finish_times). A level's time is the growth of the running
+(B, C) rewrite -- the executor the autotuner picks on these matrices, each in
+the form it takes there, LDS windows or row by row -- with the device clock
+recorded when a level, or an item, is done (sptrsv_level_finish_times; the
+shipped checkpoint's labels were all taken row by row). A level's time is the growth of the running
 maximum of its levels' finish times across it (its share of the critical
 path). A level that the rewrite empties is labelled 1 when the time its rows
 cost in their new levels of L' (their share, by row entries, of those levels'
