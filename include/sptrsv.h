@@ -387,9 +387,11 @@ typedef struct {
 sptrsv_status_t sptrsv_measure_level_costs(sptrsv_handle_t h, hipStream_t s, sptrsv_level_costs_t *out);
 /* The level floor of one solve of (which, nrhs) under the schedule it uses
  * (built if needed): the costs above summed over the plan's levels as its
- * runs separate them (thin-run levels by window kind, one launch or graph node
- * per wide level and per launch of a run, device-wide barriers inside
- * persistent runs, one hop per level for the synchronisation-free executor),
+ * runs separate them (thin-run levels by whether a workgroup barrier follows them,
+ * one hand-over per further window of a run spread over workgroups and the launch
+ * that marks its x, one launch or graph node per wide level and per launch of a
+ * run, device-wide barriers inside persistent runs, one hop per level for the
+ * synchronisation-free executor row by row),
  * plus the launches of the gather, b-transform and scatter. flags:
  * SPTRSV_FLOOR_GRAPH prices launches as graph nodes; SPTRSV_FLOOR_ROWS prices a
  * solve with the right-hand sides by rows (sptrsv_solve_rows), which has no

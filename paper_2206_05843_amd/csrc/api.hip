@@ -1356,16 +1356,29 @@ sptrsv_status_t sptrsv_level_floor(sptrsv_handle_t h, int which, int32_t nrhs, i
   // are thin runs and per-level wide launches
   const bool direct = (flags & SPTRSV_FLOOR_ROWS) && sc.mode != 3 && sc.mode != 4;
   double ns = launch * ((direct ? 0 : 2) + (P->has_t && P->n_tpos > 0 ? 1 : 0));
+  const bool marked = nrhs == 1 && !(flags & SPTRSV_FLOOR_ROWS) && !P->ovl;  // the gather marks x
   if (sc.mode == 3 && P->runs.empty()) {
     ns += 2 * launch + (double)P->nlev * c->flag_hop_ns;  // fill of x, the solve; a hop per level
   } else {
     for (const Run &r : P->runs) {
       if (r.thin) {
         ns += launch;
+        if (thin_piped(r.nw, kWaitTicks)) {  // x marked by the gather or a launch; a hand-over per window
+          if (!marked) ns += launch;
+          ns += (double)(r.nw - 1) * c->flag_hop_ns;
+        }
+        const int64_t gw = r.free ? 1 : thin_width(sc, nrhs);
         for (int32_t w = 0; w < r.nw; ++w) {
           const int4 W = P->h_win[(size_t)(r.wi + w)];
-          const int32_t nl = P->h_win[(size_t)(r.wi + w + 1)].x - W.x;
-          ns += (double)nl * ((W.y & 1) ? c->thin_wave_level_ns : c->thin_level_ns);
+          const int32_t end = P->h_win[(size_t)(r.wi + w + 1)].x;
+          // one wave solves levels of at most 64 items; a barrier follows a level if it or the next has more
+          auto wide = [&](int32_t l) {
+            return l < end && (P->h_level_ptr[(size_t)l + 1] - P->h_level_ptr[(size_t)l]) * gw > 64;
+          };
+          for (int32_t l = W.x; l < end; ++l) {
+            const bool barrier = !(W.y & 1) && (!(W.y & 2) || wide(l) || wide(l + 1));
+            ns += barrier ? c->thin_level_ns : c->thin_wave_level_ns;
+          }
         }
       } else if (r.flow) {
         ns += launch + (double)(r.l1 - r.l0 - 1) * c->flag_hop_ns;
