@@ -184,7 +184,7 @@ struct Plan {
   DArr<double> bp, xp;                 // [n * nrhs] permuted, RHS-interleaved
   DArr<unsigned> tp;                   // [kThinCtlWords] tickets of spread thin runs (zero between launches)
   DArr<unsigned long long> sf_ticket;  // [1] ticket counter of the synchronisation-free solve
-  DArr<unsigned> wbar;                 // [2] barrier counters of persistent wide runs (zero between launches)
+  DArr<unsigned> wbar;                 // [kGridBarWords] barrier of persistent wide runs (zero between launches)
   int32_t work_nrhs = 0;
 };
 
@@ -577,7 +577,9 @@ Plan *sched_plan_of(sptrsv_ctx *h, int which);
 sptrsv_schedule_t default_schedule();
 // Schedule helpers (api.hip) -----------------------------------------------------
 bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs);
-// cap: LDS bytes of a window; one_class: keep the first window's width class
+// cap: LDS bytes of a window; one_class: keep the first window's width class (a
+// batch cuts the windows of all its matrices on the host in one call: one trial
+// cut per window instead of three)
 int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, int64_t cap, bool one_class,
                     std::vector<int4> &out);
 sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s);

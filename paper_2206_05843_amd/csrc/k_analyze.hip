@@ -362,14 +362,15 @@ __global__ void k_ptr_from_scan(const long long *__restrict__ ex, const long lon
   }
 }
 
-// Level-ordered copy: the row at position p keeps its column order; columns
-// become positions so the solve reads its work vectors contiguously per level.
-// The level-ordered copy of row perm[p] at position p, its off-diagonals in
+// The level-ordered copy: row perm[p] at position p, columns as positions (the
+// solve reads its work vectors contiguously per level), off-diagonals in
 // ascending position: dependencies at low levels come first, so an executor
 // that subtracts them in this order has summed everything else when the last
 // one it waits for (the row of the level before) arrives, and a window's
-// dependencies on earlier windows precede those inside it. Every executor sums
-// in this order, so the schedule does not change a solution's bits.
+// dependencies on earlier windows precede those inside it. Executors that give a
+// row to one lane sum it in this order, so for sorted rows the schedule does not
+// change a solution's bits (a row in column order has its dependencies before an
+// LDS window subtracted first, wherever they stand).
 // kFillLanes lanes share a row: each ranks its entries against the row's
 // others, kFillLanes at a time through shuffles. Rows longer than kSortMax
 // (the ranking is quadratic) keep the caller's column order.

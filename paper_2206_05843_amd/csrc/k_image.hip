@@ -18,7 +18,7 @@
 // K is the window's width class (2, 6 or 10), chosen when windows are cut; a
 // window of one level has only the diagonals.
 // The dependencies of a row on positions before its window go to a CSR over
-// positions (ext_ptr, ext) in the row's column order. Positions and window
+// positions (ext_ptr, ext) in the row's order. Positions and window
 // layouts come from exclusive scans, so the images do not depend on thread
 // timing.
 #include "common.h"

@@ -10,7 +10,7 @@
 // every NaN), so one device-coherent 64-bit load returns both "done" and the
 // value (a plain load is tried first and trusted when it is not the pending
 // pattern). A lane requests its next four dependencies' values at once and takes
-// the ready ones in column order, so the sum keeps the row's order; while it
+// the ready ones in the row's order, so the sum keeps it; while it
 // waits on a batch it keeps the batch's columns and weights in registers and
 // polls past the caches directly, so a pass costs one memory round trip. A wave
 // none of whose lanes moved in an iteration sleeps briefly before it polls

@@ -8,11 +8,12 @@
 // row's right-hand sides share cache lines.
 //
 // Two schedules per level:
-//  * thin runs: consecutive narrow levels inside ONE workgroup; the levels are
-//    separated by workgroup barriers (no device-wide synchronisation). Values a
-//    run produces are kept in LDS as well, so later levels of the run read
-//    them from LDS; the LDS window restarts (after a full barrier that makes the
-//    global copies visible) when it is full.
+//  * thin runs: consecutive narrow levels in LDS windows, each solved by one
+//    workgroup, whose levels are separated by workgroup barriers or by nothing
+//    (no device-wide synchronisation). Values a window produces are kept in LDS,
+//    where its later levels read them, and go to global memory for the windows
+//    after it, which one workgroup solves in turn or, spread over workgroups, as
+//    the values they read become final.
 //  * wide levels: one launch over the device per level (kernel boundaries order
 //    the levels).
 #include <algorithm>
@@ -51,7 +52,7 @@ struct Ctl {
 //    finiteness check happens too), before the next window reads it.
 // Rows are in ascending position, so the earlier windows' dependencies come
 // first whatever the cut, and the sums and quotients are those of the other
-// executors bit for bit.
+// one-lane executors bit for bit (rows kept in column order excepted).
 // A level of phase 2 waits for the x of the level before, and a single wave
 // issues an instruction every four or five cycles, so what a level costs is one
 // LDS round trip and its instructions. All of a row's x (K inline dependencies)
@@ -712,10 +713,9 @@ __global__ void k_fill_ell(int32_t n, const int32_t *__restrict__ srp, const int
 // are read and written in the caller's layout. The last workgroup to finish
 // resets the queue, so the launch can be replayed (graph capture) without a
 // host-side reset. q[0] = next ticket, q[1] = finished workgroups.
-// A task is a chain of levels of a few rows, so what counts is how many chains
-// are under way: groups of 4 columns (most levels then fit one wave), and as
-// many workgroups per CU as registers and LDS allow (1 of 1,024 threads, 2 of
-// 512, 4 of 256). Workgroups fill the CUs one after another, so those of a CU
+// A task is a chain of levels, so what counts is how many chains are under way:
+// groups of a few columns (the host chooses), and as many workgroups per CU as
+// registers and LDS allow (1 of 1,024 threads, 2 of 512, 4 of 256). Workgroups fill the CUs one after another, so those of a CU
 // are `cus` apart; each has another of its first four waves, which sit on the
 // four SIMDs, solve its narrow levels. Waves without levels touch the next
 // window's data meanwhile. The vectors pass through HBM once each way instead of
@@ -785,6 +785,16 @@ bool thin_piped(int32_t nwin, unsigned long long tlimit) { return nwin >= 2 && t
 int thin_win_bytes() { return kWinBytes - kCtlBytes; }
 int thin_ctl_bytes() { return kCtlBytes; }
 
+namespace {
+template <int WG>
+void batch_attr() {
+  const void *f[] = {reinterpret_cast<const void *>(&k_batch_run<WG, 0>),
+                     reinterpret_cast<const void *>(&k_batch_run<WG, 1>),
+                     reinterpret_cast<const void *>(&k_batch_run<WG, 4>)};
+  for (const void *k : f) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
+}
+}  // namespace
+
 void solve_kernels_init() {
   set_lds_attr<256, true>();
   set_lds_attr<256, false>();
@@ -798,6 +808,9 @@ void solve_kernels_init() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
   (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_thin_pipe<1024, true, true, kFinish>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
+  batch_attr<256>();
+  batch_attr<512>();
+  batch_attr<1024>();
 }
 
 hipError_t launch_fill_pending(int64_t p0, int64_t rows, int32_t nr, const int32_t *perm, double *x, hipStream_t s) {
@@ -885,26 +898,11 @@ hipError_t launch_fill_ell(int32_t n, const int32_t *srp, const int32_t *sci, co
   return hipGetLastError();
 }
 
-template <int WG>
-void batch_attr() {
-  const void *f[] = {reinterpret_cast<const void *>(&k_batch_run<WG, 0>),
-                     reinterpret_cast<const void *>(&k_batch_run<WG, 1>),
-                     reinterpret_cast<const void *>(&k_batch_run<WG, 4>)};
-  for (const void *k : f) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kWinBytes);
-}
-
 int batch_lds(int wg) { return wg == 256 ? 39 * 1024 : wg == 512 ? 79 * 1024 : kWinBytes; }
 
 hipError_t launch_batch_run(int wg, int32_t nmat, int32_t grid, const int32_t *order, const int32_t *mwin,
                             const int4 *win, int32_t nrhs, int32_t ncol, const int64_t *row_off, const ThinArgs &a,
                             unsigned *q, int *err, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    batch_attr<256>();
-    batch_attr<512>();
-    batch_attr<1024>();
-    attr = true;
-  }
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);

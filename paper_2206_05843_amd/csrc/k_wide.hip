@@ -25,7 +25,7 @@ __device__ inline int32_t wide_block() {
 // stencil with 32): a row's first four dependencies come from the fixed-width copy
 // indexed by position (no row pointer on the load chain), the rest from the
 // CSR four at a time; all loads of a step are issued before they are used and
-// the products are subtracted in the row's column order.
+// the products are subtracted in the row's order.
 template <bool kOne>
 __global__ void k_wide_level(int32_t pb, int32_t pe, int32_t nrhs, const int32_t *__restrict__ srp,
                              const int32_t *__restrict__ sci, const double *__restrict__ sva,
@@ -225,7 +225,7 @@ __device__ __forceinline__ void wide_fetch(int64_t it, int32_t pb, int32_t nr, c
 
 // Solves the fetched items: the x values they read (device-coherent loads,
 // since other workgroups of the launch wrote them), all requested before
-// they are used, subtracted in the row's column order; x stored coherently
+// they are used, subtracted in the row's order; x stored coherently
 // (and to the caller's x by rows).
 template <int kK>
 __device__ __forceinline__ void wide_solve(const WideItem (&w)[kK], const bool (&ok)[kK], int32_t nr,
@@ -250,7 +250,7 @@ __device__ __forceinline__ void wide_solve(const WideItem (&w)[kK], const bool (
 #pragma unroll
     for (int d = 0; d < 4; ++d)
       if (d < w[j].deg) a -= vv[d] * xv[j][d];
-    // dependencies beyond the first four, four at a time, in column order
+    // dependencies beyond the first four, four at a time, in the row's order
     // (prefetching the next four's columns and weights here cost registers,
     // and with them resident waves, on every level)
     const int32_t qe = w[j].qb + w[j].deg;
