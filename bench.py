@@ -71,11 +71,37 @@ def alg_bytes(n, nnz, nlev, nrhs, nnz_t=0, rewritten=False):
 
 # Sources whose text decides what a kernel reads and writes (thin runs read
 # the window images k_image.hip builds).
-KERNEL_SOURCE = {"k_thin_run": ("k_thin.hip", "k_image.hip", "sync.h"),
-                 "k_batch_run": ("k_thin.hip", "k_image.hip", "sync.h"),
+KERNEL_SOURCE = {"k_thin_run": ("k_thin.hip", "k_image.hip", "sync.h", "wait.h"),
+                 "k_thin_pipe": ("k_thin.hip", "k_image.hip", "sync.h", "wait.h"),
+                 "k_batch_run": ("k_thin.hip", "k_image.hip", "sync.h", "wait.h"),
                  "k_wide_level": ("k_wide.hip", "sync.h"), "k_wide_run": ("k_wide.hip", "sync.h"),
                  "k_flow_run": ("k_flow.hip",), "k_gather": ("k_vec.hip",), "k_scatter": ("k_vec.hip",),
                  "k_sf_solve": ("k_syncfree.hip",)}
+
+
+def dominant_kernel(dom, sched, spread):
+    """Name of the kernel behind a profile class under a schedule (spread: its
+    thin runs have windows spread over workgroups). The synchronisation-free
+    launch is profiled with the device-wide class when it works row by row, with
+    the thin runs when it takes LDS windows."""
+    if dom == "thin_run":
+        return "k_thin_pipe" if spread else "k_thin_run"
+    if dom != "wide_level":
+        return {"gather": "k_gather", "scatter": "k_scatter"}[dom]
+    if sched["mode"] == 3:
+        return "k_sf_solve"
+    if sched["mode"] == 4:
+        return "k_flow_run"  # dataflow runs of the wide levels
+    return "k_wide_run" if sched["wide_grid"] > 0 else "k_wide_level"  # one persistent launch, or one per level
+
+
+def thin_runs_spread(h, which, nrhs):
+    """Whether the plan's thin runs hand x over between workgroups: its level
+    floor counts hand-overs (modes 0, 1 and 2 have no others)."""
+    unit = dict.fromkeys(("thin_level_ns", "thin_wave_level_ns", "launch_ns", "graph_node_ns", "grid_barrier_ns",
+                          "flag_hop_ns"), 0.0)
+    unit["flag_hop_ns"] = 1.0
+    return h.level_floor(unit, which, nrhs) > 0.0
 
 
 def source_hash(kernel):
@@ -255,6 +281,7 @@ def bench_precond(args, np, torch, gen, oracle, sp):
                 info[f"nnz_T_{key}"] = st["nnz_T"]
             h.autotune(which, nrhs, rows=rows)
             info[f"schedule_{key}"] = h.get_schedule(which, nrhs)
+            info[f"spread_{key}"] = thin_runs_spread(h, which, nrhs)
             hs.append((h, which))
         solve(hs[0][0], hs[0][1], r, y)
         solve(hs[1][0], hs[1][1], y, z)
@@ -305,14 +332,7 @@ def bench_precond(args, np, torch, gen, oracle, sp):
     per_launch_ms = dp["ms"] / max(1, dp["launches"])
     bpl = dp["bytes"] / max(1, dp["launches"])
     achieved = bpl / (per_launch_ms * 1e-3) / 1e9 if per_launch_ms > 0 else 0.0
-    kname = {"thin_run": "k_thin_run", "wide_level": "k_wide_level", "gather": "k_gather", "scatter": "k_scatter"}[dom]
-    hsched = head["schedule_L"]
-    if dom == "wide_level" and hsched["mode"] == 3:
-        kname = "k_sf_solve"
-    elif dom == "wide_level" and hsched["mode"] == 4:
-        kname = "k_flow_run"
-    elif dom == "wide_level" and hsched["wide_grid"] > 0:
-        kname = "k_wide_run"
+    kname = dominant_kernel(dom, head["schedule_L"], head["spread_L"])
     cpu = None
     if not args.no_cpu:
         cpu = {"value": round(1.0 / t_oracle, 5), "unit": "applications/s", "cores": 1, "kind": "oracle",
@@ -505,6 +525,7 @@ def main():
             raise SystemExit(f"[bench] variant {name} failed parity: relerr={info['relerr']:.3e}")
         info["bytes"] = alg_bytes(m.n, info["nnz"], info["nlev"], nrhs, info["nnz_t"], rewrite)
         info["level_floor_us"] = h.level_floor(costs, which, nrhs, graph=use_graph, rows=layout == "rows")
+        info["spread"] = thin_runs_spread(h, which, nrhs)
         variants[name] = (h, which, info)
         log(f"[bench] {name}: nlev={info['nlev']} relerr={info['relerr']:.2e} pre={info['preprocess_s']:.2f}s "
             f"schedule={info['schedule']} level floor {info['level_floor_us']:.1f} us")
@@ -618,15 +639,7 @@ def main():
     per_launch_ms = dp["ms"] / max(1, dp["launches"])
     bytes_per_launch = dp["bytes"] / max(1, dp["launches"])
     achieved = bytes_per_launch / (per_launch_ms * 1e-3) / 1e9 if per_launch_ms > 0 else 0.0
-    kname = {"thin_run": "k_thin_run", "wide_level": "k_wide_level", "gather": "k_gather",
-             "scatter": "k_scatter"}[dom]
-    hsched = variants[headline][2]["schedule"]
-    if dom == "wide_level" and hsched["mode"] == 3:
-        kname = "k_sf_solve"  # the synchronisation-free launch is profiled with the device-wide class
-    elif dom == "wide_level" and hsched["mode"] == 4:
-        kname = "k_flow_run"  # dataflow runs of the wide levels
-    elif dom == "wide_level" and hsched["wide_grid"] > 0:
-        kname = "k_wide_run"  # persistent runs of consecutive wide levels
+    kname = dominant_kernel(dom, variants[headline][2]["schedule"], variants[headline][2]["spread"])
     traffic = load_traffic(kname, f"config{args.config}_{headline}")
     total_prof_ms = sum(v["ms"] for v in prof.values())
     roofline = {"bound": "hbm", "achieved": round(achieved, 3), "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -40,3 +40,19 @@ def test_traffic_lookup_follows_the_source(tmp_path, monkeypatch):
         monkeypatch.setattr(bench, "source_hash", lambda k, h=good["source_hash"]: h)
         assert bench.load_traffic(kernel, "config4_learned") == want
     assert bench.load_traffic(kernel, "config9_none") is None
+
+
+def test_dominant_kernel_names():
+    """The kernel a profile class stands for under each schedule: thin runs with
+    windows spread over workgroups are another kernel than those in one."""
+    mode = lambda m, grid=0: {"mode": m, "wide_grid": grid}  # noqa: E731
+    assert bench.dominant_kernel("thin_run", mode(0), False) == "k_thin_run"
+    assert bench.dominant_kernel("thin_run", mode(0), True) == "k_thin_pipe"
+    assert bench.dominant_kernel("thin_run", mode(3, 256), True) == "k_thin_pipe"
+    assert bench.dominant_kernel("wide_level", mode(3, 256), False) == "k_sf_solve"
+    assert bench.dominant_kernel("wide_level", mode(4), True) == "k_flow_run"
+    assert bench.dominant_kernel("wide_level", mode(0, 64), True) == "k_wide_run"
+    assert bench.dominant_kernel("wide_level", mode(1), False) == "k_wide_level"
+    assert bench.dominant_kernel("gather", mode(0), False) == "k_gather"
+    assert {"k_thin_run", "k_thin_pipe", "k_sf_solve", "k_flow_run", "k_wide_run", "k_wide_level"} <= set(
+        bench.KERNEL_SOURCE)
