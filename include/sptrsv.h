@@ -266,10 +266,11 @@ sptrsv_status_t sptrsv_check(sptrsv_handle_t h, hipStream_t s);
  * (row, right-hand side) waits only for the values it reads (the comparison
  * executor; wide_grid gives its workgroups of 256 threads, 0 = 512, at most
  * 2048; the other knobs are ignored). Matrices with narrow levels (at most 1,600
- * off-diagonals a level on average and, with several right-hand sides, at least 10
- * to 20 levels a window) take LDS windows of several levels instead, which wait
- * only for the values they read from earlier windows, a chain of windows per
- * right-hand side on the workgroups of one XCD (wide_grid does not matter then),
+ * off-diagonals a level on average and, with several right-hand sides, windows
+ * that read little from outside or hold 10 to 20 levels) take LDS windows
+ * instead, which wait only for the values they read from earlier windows, a chain
+ * of windows per right-hand side on the workgroups of one XCD (wide_grid does not
+ * matter then),
  * 4 = levels with at most thin_rows rows in thin runs as in mode 0, and each
  * run of consecutive wider levels as one dataflow launch: every level is cut
  * into chunks of 2 * wide_threads items (wide_threads = 128, 256 or 512) and

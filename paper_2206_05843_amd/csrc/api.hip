@@ -200,7 +200,8 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
 // Static images of every window in P.h_win (entries with y >= 0; the others
 // end a run): exact overflow counts replace the host bounds in .z, image
 // offsets (16-byte units) go to .w, and the table is uploaded.
-sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s) {
+sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s, int64_t *next_out) {
+  if (next_out) *next_out = 0;
   const int32_t nent = (int32_t)P.h_win.size();
   if (nent == 0 || P.n == 0) return SPTRSV_OK;
   std::vector<int32_t> lvl_win((size_t)P.nlev, -1);
@@ -237,6 +238,7 @@ sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s
   HIPCHK(h, hipMemcpyAsync(&bits, aux + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));
   if (bits) return set_err(h, SPTRSV_ERR_OVERFLOW, "dependencies before LDS windows exceed int32 indexing");
+  if (next_out) *next_out = next;
   int64_t units = 0;
   for (int32_t e = 0; e < nent; ++e) {
     int4 &W = P.h_win[(size_t)e];
@@ -428,26 +430,34 @@ static bool free_in_windows(const Plan &P) {
 
 // With several columns every column is a chain of windows of its own, which reads
 // the images again and fetches a line of x for fewer values, while a wait per row
-// is shared by the row's columns; so windows must save more hand-overs to pay: at
-// least so many levels a window. Measured on the matrices above and others (time
-// row by row over time in windows; levels a window): 2 columns 0.89 (8.4), 1.05
-// (7.1), 1.16 (10.6), 1.20 (11.7); 4 columns 0.80 (8.9), 1.07 (10.6), 1.08 (11.7),
-// 1.26 (14.4); 8 columns 0.94 (11.7), 1.07 (14.7), 1.12 (14.4), 1.57 (22); 16
-// columns 0.82 (14.7), 1.03 (14.4), 1.40 (22); 32 columns 0.66 (14.7), 1.26 (22),
-// 2.5 (26); 64 columns 1.06 (14.3), 1.19 (22).
-static int64_t free_levels_per_window(int32_t nrhs) {
-  return nrhs <= 1 ? 0 : nrhs <= 2 ? 10 : nrhs <= 4 ? 11 : nrhs <= 8 ? 14 : 20;
+// is shared by the row's columns; so windows pay only where they read little from
+// outside (ext: dependencies on earlier windows, of the nw windows in all) or hold
+// many levels. Measured (time row by row over time in windows; outside
+// dependencies per level, levels per window; P a power law, T torso2-like, S the
+// 3D stencil, D the 2D one): 2 columns T 0.89 (787, 8), S 0.96 (964, 4), T 0.99
+// (600, 10), S 1.08 (643, 5), P 1.37 (1,272, 14); 4 columns T 0.78 (787, 8), S 0.96
+// (800, 7), S 1.04 (635, 5), T 1.08 (419, 12), P 1.21 (1,272, 14), D 2.1 (138, 8); 8
+// columns T 0.94 (419, 12), P 1.04 (1,272, 14), T 1.16 (252, 15), D 1.7 (138, 8); 16
+// columns P 0.81 (1,272, 14), T 0.99 (252, 15), P 1.15 (893, 21), D 1.33 (138, 8), T
+// 1.4 (113, 22); 32 columns 0.70 (711, 14), T 1.26 (113, 22), P 1.27 (764, 27).
+// Windows of more than 3,400 rows on average are single wide levels, which a wait
+// per row spreads over the device (lung2-like, 4,054 rows: 0.77 with 4 columns at
+// 18 levels a window), and windows of few rows hold many overflow records (T, 4
+// columns: 0.88 at 600 and 1,415 rows a window).
+static bool free_pays(const Plan &P, int32_t nrhs, int32_t nw, int64_t ext) {
+  if (nrhs <= 1) return true;
+  const bool small = P.n < (int64_t)1900 * nw;
+  const int64_t out =
+      nrhs <= 2 ? 750 : nrhs <= 4 ? (small ? 450 : 650) : nrhs <= 8 ? 400 : nrhs <= 16 ? 220 : 150;
+  const int64_t levels = nrhs <= 2 ? 10 : nrhs <= 8 ? 14 : 20;
+  return ext <= out * P.nlev || (P.nlev >= levels * nw && P.n <= (int64_t)3400 * nw);
 }
 
-// Appends the windows of the synchronisation-free executor for nrhs columns and
-// their terminator to out; returns their number, 0 where it works row by row.
-static int32_t cut_free(const Plan &P, int32_t nrhs, std::vector<int4> &out) {
+// Appends the windows of the synchronisation-free executor and their terminator
+// to out; returns their number, 0 where it works row by row whatever nrhs.
+static int32_t cut_free(const Plan &P, std::vector<int4> &out) {
   if (!free_in_windows(P)) return 0;
-  const size_t first = out.size();
-  const int32_t nw = cut_windows(P, 0, P.nlev, 1, kFreeThreads, thin_win_bytes(), false, out);
-  if (P.nlev >= free_levels_per_window(nrhs) * nw) return nw;
-  out.resize(first);
-  return 0;
+  return cut_windows(P, 0, P.nlev, 1, kFreeThreads, thin_win_bytes(), false, out);
 }
 
 // The finish times of the levels (wall clock, the latest over the columns, into
@@ -458,8 +468,8 @@ static int32_t cut_free(const Plan &P, int32_t nrhs, std::vector<int4> &out) {
 sptrsv_status_t stamp_free_windows(sptrsv_ctx *h, Plan &P, int32_t nrhs, unsigned long long *finish, bool *windows,
                                    hipStream_t s) {
   std::vector<int4> h_win;
-  const int32_t nw = cut_free(P, nrhs, h_win);
-  *windows = nw > 0;
+  const int32_t nw = cut_free(P, h_win);
+  *windows = false;
   if (nw == 0) return SPTRSV_OK;
   DArr<int4> win;
   DArr<uint4> img;
@@ -473,8 +483,10 @@ sptrsv_status_t stamp_free_windows(sptrsv_ctx *h, Plan &P, int32_t nrhs, unsigne
     std::swap(P.ext, ext);
   };
   swap_all();
-  sptrsv_status_t st = build_images(h, P, 1, s);
-  if (st == SPTRSV_OK) {
+  int64_t next = 0;
+  sptrsv_status_t st = build_images(h, P, 1, s, &next);
+  *windows = st == SPTRSV_OK && free_pays(P, nrhs, nw, next);
+  if (*windows) {
     hipError_t e = launch_fill_pending(0, P.n, nrhs, nullptr, P.xp.p, s);
     if (e == hipSuccess)
       e = launch_thin_stamped(P.win.p, nw, nrhs, thin_args(P), h->d_err.p, s, finish, P.nlev, wait_limit(h));
@@ -492,7 +504,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   const int64_t thr = sc.thin_rows;
   auto rows_of = [&](int32_t l) -> int64_t { return P.h_level_ptr[l + 1] - P.h_level_ptr[l]; };
   const bool flow = sc.mode == 4;
-  const int32_t nfree = sc.mode == 3 ? cut_free(P, nrhs, P.h_win) : 0;
+  const int32_t nfree = sc.mode == 3 ? cut_free(P, P.h_win) : 0;
   const int32_t gw = nfree > 0 ? 1 : thin_width(sc, nrhs);  // columns per thin-run workgroup
   if (nfree > 0) {
     Run r{0, P.nlev, true};
@@ -543,7 +555,12 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
     r.nw = cut_windows(P, r.l0, r.l1, gw, sc.wg_threads, thin_win_bytes(), false, P.h_win);
   }
   P.runs_nrhs = -1;  // until the images are built
-  STCHK(build_images(h, P, gw, s));
+  int64_t next = 0;
+  STCHK(build_images(h, P, gw, s, &next));
+  if (nfree > 0 && !free_pays(P, nrhs, nfree, next)) {  // row by row: no runs
+    P.runs.clear();
+    P.h_win.clear();
+  }
   if (flow) STCHK(build_flow(h, P, nrhs, sc, s));
   STCHK(build_overlap(h, P, nrhs, sc, s));
   P.runs_nrhs = nrhs;

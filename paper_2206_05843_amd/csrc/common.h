@@ -586,8 +586,9 @@ sptrsv_status_t build_extra_hist(sptrsv_ctx *h, Plan &P, hipStream_t s);
 sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_schedule_t &sc, hipStream_t s);
 sptrsv_status_t stamp_free_windows(sptrsv_ctx *h, Plan &P, int32_t nrhs, unsigned long long *finish, bool *windows,
                                    hipStream_t s);
-// ncol: right-hand sides per window (slots are premultiplied by it)
-sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s);
+// ncol: right-hand sides per window (slots are premultiplied by it); next (may be
+// null): the dependencies before the windows, of all their rows
+sptrsv_status_t build_images(sptrsv_ctx *h, Plan &P, int32_t ncol, hipStream_t s, int64_t *next = nullptr);
 sptrsv_status_t ensure_work(sptrsv_ctx *h, Plan &P, int32_t nrhs);
 
 // Plan building (api.hip) --------------------------------------------------------
