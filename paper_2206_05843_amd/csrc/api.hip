@@ -440,17 +440,26 @@ static bool free_in_windows(const Plan &P) {
 // columns T 0.94 (419, 12), P 1.04 (1,272, 14), T 1.16 (252, 15), D 1.7 (138, 8); 16
 // columns P 0.81 (1,272, 14), T 0.99 (252, 15), P 1.15 (893, 21), D 1.33 (138, 8), T
 // 1.4 (113, 22); 32 columns 0.70 (711, 14), T 1.26 (113, 22), P 1.27 (764, 27).
-// Windows of more than 3,400 rows on average are single wide levels, which a wait
-// per row spreads over the device (lung2-like, 4,054 rows: 0.77 with 4 columns at
-// 18 levels a window), and windows of few rows hold many overflow records (T, 4
-// columns: 0.88 at 600 and 1,415 rows a window).
+// Windows of few rows hold many overflow records (T, 4 columns: 0.88 at 600 and
+// 1,415 rows a window). Where most rows are in levels that fill a window alone a
+// wait per row, which spreads them over the device, is faster whatever else holds
+// (lung2-like, 26 levels of n / 26 rows among 453 of two; n = 80,000 | 109,460 |
+// 140,000 | 170,000: one column 1.15 | 0.94 | 0.73 | 0.60, 4 columns 0.92 | 0.76 | 0.58
+// | 0.45).
 static bool free_pays(const Plan &P, int32_t nrhs, int32_t nw, int64_t ext) {
+  const int64_t alone = nrhs <= 2 ? 3400 : 2600;
+  int64_t fat = 0;
+  for (int32_t l = 0; l < P.nlev; ++l) {
+    const int64_t rows = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
+    if (rows > alone) fat += rows;
+  }
+  if (2 * fat > P.n) return false;
   if (nrhs <= 1) return true;
   const bool small = P.n < (int64_t)1900 * nw;
   const int64_t out =
-      nrhs <= 2 ? 750 : nrhs <= 4 ? (small ? 450 : 650) : nrhs <= 8 ? 400 : nrhs <= 16 ? 220 : 150;
+      nrhs <= 2 ? 750 : nrhs <= 4 ? (small ? 450 : 680) : nrhs <= 8 ? 400 : nrhs <= 16 ? 220 : 150;
   const int64_t levels = nrhs <= 2 ? 10 : nrhs <= 8 ? 14 : 20;
-  return ext <= out * P.nlev || (P.nlev >= levels * nw && P.n <= (int64_t)3400 * nw);
+  return ext <= out * P.nlev || P.nlev >= levels * nw;
 }
 
 // Appends the windows of the synchronisation-free executor and their terminator
