@@ -129,6 +129,16 @@ bool level_fits_window(const Plan &P, int32_t l, int32_t nrhs) {
   return thin_window_bytes(rows, 0, 1, nrhs, kWidths) <= thin_win_bytes();
 }
 
+// Whether a level of `rows` rows may be part of a thin run. It has to fit one
+// window alone, which takes 16 bytes a row beside its x; a run takes levels up
+// to 24 bytes a row only. In a window a level is one workgroup's work, and the
+// widest that fit are several times slower there than over the device: mode 2,
+// two columns, 26 levels of 4,175 rows 225 us as launches, 902 in windows; the
+// 3D stencil of 80^3 rows, with levels up to 4,800, 2,104 us and 2,919.
+bool thin_level(int64_t rows, int32_t ncol, int64_t cap) {
+  return rows * (8 * (int64_t)ncol + 24) + 8 * (int64_t)ncol + 24 <= cap;
+}
+
 // Bucket of level distance d of the overflow-record histograms.
 static int extra_bucket(int32_t d) {
   return d <= 4 ? d - 1 : d <= 8 ? 4 : d <= 16 ? 5 : d <= 32 ? 6 : d <= 64 ? 7 : d <= 256 ? 8 : 9;
@@ -524,7 +534,7 @@ sptrsv_status_t make_runs(sptrsv_ctx *h, Plan &P, int32_t nrhs, const sptrsv_sch
   for (int32_t l = 0; l < P.nlev && sc.mode != 3; ++l) {
     const int64_t rows = rows_of(l);
     bool thin = sc.mode == 2 || ((sc.mode == 0 || flow) && rows <= thr);
-    if (thin_window_bytes(rows, 0, 1, gw, kWidths) > cap) thin = false;  // must fit one window alone
+    if (thin && !thin_level(rows, gw, cap)) thin = false;
     // a wide level whose rows average many dependencies, with several
     // right-hand sides, is a launch of its own with a workgroup per row
     const bool longr = !thin && long_rows(P, l, nrhs);

@@ -183,3 +183,30 @@ def test_columns_of_a_row_in_two_waves(nrhs, wg):
     ref = _solve(h, b, nrhs, mode=1)
     for _ in range(4):
         assert torch.equal(_solve(h, b, nrhs, mode=2, wg_threads=wg), ref)
+
+
+@pytest.mark.parametrize("nrhs,width,wide", [(1, 5000, False), (1, 5200, True), (2, 4000, False), (2, 4175, True),
+                                             (8, 1800, False), (8, 1900, True)])
+def test_widest_levels_of_a_thin_run(nrhs, width, wide):
+    """A thin run takes levels up to 24 bytes of LDS a row beside x, wider ones
+    are launches: 26 levels of 4,175 rows, two columns, 225 us against 902 in
+    windows of their own."""
+    rng = np.random.default_rng(width)
+    i = np.arange(width, 3 * width)
+    r = np.concatenate([np.arange(3 * width), i])
+    c = np.concatenate([np.arange(3 * width), i - i % width - width + rng.integers(0, width, i.size)])
+    val = np.concatenate([1.0 + rng.random(3 * width), rng.uniform(-1, 1, i.size)])
+    o = np.lexsort((c, r))
+    m = gen.Csr(3 * width, np.searchsorted(r[o], np.arange(3 * width + 1)).astype(np.int32), c[o].astype(np.int32),
+                val[o])
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    b_np = gen.rhs(m, nrhs)
+    b = to_dev(b_np)
+    ref = _solve(h, b, nrhs, mode=1)
+    assert oracle.relerr(ref.cpu().numpy(), oracle.solve(m, b_np)) <= TOL
+    assert torch.equal(_solve(h, b, nrhs, mode=2), ref)
+    h.profile_start()
+    h.solve(b)
+    n = {k: v["launches"] for k, v in h.profile_stop().items()}
+    assert (n["wide_level"], n["thin_run"]) == ((3, 0) if wide else (0, 1))
