@@ -155,11 +155,27 @@ static int extra_bucket(int32_t d) {
 // about 60 ns on one wave and 160 on several, 5 more per inline dependency,
 // and each round of four overflow records beyond the inline ones two dependent
 // LDS round trips, about 90 ns.
+// Where kTailLevels levels (several columns: twice as many) of at most 64
+// items begin, a window that holds wider levels ends: on one wave such a level
+// takes about 110 ns, in a window of several waves about 200, and a window
+// costs 1 us, with several columns 5 to 6 where the run had only one.
+// Measured, one column: 26 levels of 735 rows, then 453 of two, 204 us in
+// windows cut by size alone, 142 so; 4 levels of 100, then 32 or 64 of two,
+// 19.0 -> 19.4 and 25.1 -> 22.7. Four columns: 300 -> 241; 64 levels of two
+// 28.7 -> 29.3, 200 63.0 -> 52.4. A batch keeps its windows: there a window
+// costs its workgroup a phase 1.
+constexpr int32_t kTailLevels = 64;
 int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t wg, int64_t cap, bool one_class,
                     std::vector<int4> &out) {
   const size_t first = out.size();
   int keep = -1;
   int32_t ws = l0;
+  // tail[l - l0]: how many levels from l on have at most 64 items
+  std::vector<int32_t> tail((size_t)(l1 - l0) + 1, 0);
+  for (int32_t l = l1 - 1; l >= l0 && !one_class; --l)
+    if ((P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l]) * (int64_t)nrhs <= 64)
+      tail[(size_t)(l - l0)] = tail[(size_t)(l - l0) + 1] + 1;
+  const int32_t tail_min = nrhs == 1 ? kTailLevels : 2 * kTailLevels;
   while (ws < l1) {
     int32_t end = ws, kc = kWidths;
     int64_t ents = 0, maxit = 0;
@@ -175,6 +191,7 @@ int32_t cut_windows(const Plan &P, int32_t l0, int32_t l1, int32_t nrhs, int32_t
         // (beyond each row's K at the highest levels) at most l - ws levels up
         const int64_t el = l > ws ? P.h_xh[k][(size_t)l * kExtraBuckets + extra_bucket(l - ws)] : 0;
         if (thin_window_bytes(rows + rl, en + el, l - ws + 1, nrhs, k) > cap) break;
+        if (mi > 64 && tail[(size_t)(l - l0)] >= tail_min) break;
         rows += rl;
         en += el;
         mi = std::max<int64_t>(mi, rl * nrhs);

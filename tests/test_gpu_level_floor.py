@@ -3,9 +3,11 @@ and barrier-free levels of thin-run windows, hand-overs between the windows of a
 spread run, launches."""
 import numpy as np
 import pytest
+import torch
 
 import gen
-from tests.gpu_util import dev
+import oracle
+from tests.gpu_util import dev, to_dev
 
 pytestmark = pytest.mark.gpu
 sp = pytest.importorskip("paper_2206_05843_amd")
@@ -76,3 +78,25 @@ def test_hand_overs_of_a_spread_run():
     assert _counts(h, 2, rows=True)["launch_ns"] == 2
     assert _counts(h, 2, graph=True)["graph_node_ns"] == 4
     assert one["thin_level_ns"] + one["thin_wave_level_ns"] == 10
+
+
+@pytest.mark.parametrize("nrhs,width,tail,windows", [(1, 2, 63, 1), (1, 2, 64, 2), (1, 60, 20, 1), (1, 65, 20, 1),
+                                                     (4, 2, 127, 1), (4, 2, 128, 2), (4, 17, 40, 1)])
+def test_a_long_narrow_tail_has_windows_of_its_own(nrhs, width, tail, windows):
+    """Levels of at most 64 items that follow wider ones are one wave's work in
+    windows of their own if they are 64 or more (128 with several columns)."""
+    m = _chain_of_levels([100] * 4 + [width] * tail)
+    h = sp.Handle()
+    h.analyze(*dev(m))
+    b_np = gen.rhs(m, nrhs)
+    b = to_dev(b_np)
+    h.set_schedule(sp.ORIGINAL, mode=1)
+    ref = h.solve(b)
+    assert oracle.relerr(ref.cpu().numpy(), oracle.solve(m, b_np)) <= 1e-10
+    for wg in (256, 512, 1024):
+        h.set_schedule(sp.ORIGINAL, mode=2, wg_threads=wg)
+        assert _counts(h, nrhs)["flag_hop_ns"] == windows - 1
+        assert torch.equal(h.solve(b), ref)
+    h.set_schedule(sp.ORIGINAL, mode=3)
+    assert torch.equal(h.solve(b), ref)
+    h.check()
