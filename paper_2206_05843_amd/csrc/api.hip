@@ -470,11 +470,12 @@ static bool free_in_windows(const Plan &P) {
 // Windows of few rows hold many overflow records (T, 4 columns: 0.88 at 600 and
 // 1,415 rows a window). Where most rows are in levels that fill a window alone a
 // wait per row, which spreads them over the device, is faster whatever else holds
-// (lung2-like, 26 levels of n / 26 rows among 453 of two; n = 80,000 | 109,460 |
-// 140,000 | 170,000: one column 1.15 | 0.94 | 0.73 | 0.60, 4 columns 0.92 | 0.76 | 0.58
-// | 0.45).
+// (lung2-like, 26 levels of n / 26 rows, then 453 of two; n = 60,000 | 80,000 |
+// 96,000 | 109,460 | 170,000: one column 1.44 | 1.21 | 1.02 | 0.93 | 0.55, 2 columns 1.24
+// | 1.04 | 0.91 | 0.79 | 0.49, 4 columns 1.18 | 1.00 | 0.85 | 0.77 | 0.45, 8 columns 1.04 |
+// 0.91 | 0.81 | 0.71 | 0.42).
 static bool free_pays(const Plan &P, int32_t nrhs, int32_t nw, int64_t ext) {
-  const int64_t alone = nrhs <= 2 ? 3400 : 2600;
+  const int64_t alone = nrhs <= 1 ? 3700 : nrhs <= 2 ? 3200 : nrhs <= 4 ? 3000 : 2500;
   int64_t fat = 0;
   for (int32_t l = 0; l < P.nlev; ++l) {
     const int64_t rows = P.h_level_ptr[(size_t)l + 1] - P.h_level_ptr[(size_t)l];
